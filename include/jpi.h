@@ -185,8 +185,7 @@ jpi_status jpi_bind_prefix(jpi_ctx* ctx, const void* k, const void* v, const int
  *     from the given values at every step and are never Euler-updated.
  * Both are copied stream-ordered into context buffers.  Must follow
  * jpi_bind_prefix, which sets the batch (binding a prefix with a different
- * batch clears both).  Correction rows run on both paths (the single-launch
- * kernel while batch * (n_corr + horizon) <= 64).  Errors: JPI_ERR_ARG
+ * batch clears both).  Correction rows run on every path.  Errors: JPI_ERR_ARG
  * (NULL ctx or data, counts out of range), JPI_ERR_STATE (no prefix bound). */
 jpi_status jpi_bind_state(jpi_ctx* ctx, const float* committed_dev, int n_fixed, const void* corr_tokens,
                           int n_corr, void* stream);
@@ -220,7 +219,8 @@ jpi_status jpi_set_committed_t0(jpi_ctx* ctx, int enable);
  * HIP graph; later calls replay it.  Errors: JPI_ERR_STATE (weights not
  * finalized or no prefix bound), JPI_ERR_ARG (NULL, n_steps < 1).
  *
- * Co-residency: on the single-launch path (bf16, batch * (n_corr + H) <= 64)
+ * Co-residency: on the single-launch path (bf16, batch * (n_corr + H) <= 64,
+ * widths that are not a multiple of 256, or JPI_PERSIST=1 in the environment)
  * the whole loop is one kernel of one workgroup per compute unit whose
  * workgroups wait for each other through memory.  That needs every
  * workgroup resident at once: do not let other device work (another stream,
@@ -322,7 +322,7 @@ typedef enum {
   JPI_KERNEL_OPROJ = 2,      /* attention output x W_o, gated residual */
   JPI_KERNEL_GATEUP = 3,     /* activations x [gate|up], GeGLU epilogue */
   JPI_KERNEL_DOWN = 4,       /* GeGLU output x W_down, gated residual */
-  JPI_KERNEL_PERSISTENT = 5  /* the single-launch denoise kernel (batch*horizon <= 64, bf16) */
+  JPI_KERNEL_PERSISTENT = 5  /* the single-launch denoise kernel, where it runs */
 } jpi_kernel_kind;
 
 /* Ask jpi_denoise to record a pair of HIP events around every launch of

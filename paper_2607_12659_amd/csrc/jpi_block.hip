@@ -29,6 +29,16 @@ __global__ __launch_bounds__(256) void k_norm_rows(const float* __restrict__ h, 
   for (int i = threadIdx.x; i < W; i += 256) yr[i] = from_f32<T>(hr[i] * r * (1.0f + w[i]));
 }
 
+// values carried by the launch itself: no staging buffer to wait for
+struct SetI32 {
+  static constexpr int N = 128;
+  int n, v[N];
+};
+__global__ void k_set_i32(int* __restrict__ p, SetI32 s) {
+  const int i = threadIdx.x;
+  if (i < s.n) p[i] = s.v[i];
+}
+
 __global__ void k_fill_i32(int* p, int n, int v) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -67,6 +77,16 @@ hipError_t launch_norm_rows(const float* h, const float* w, void* y, int M, int 
   if (M < 1) return hipSuccess;
   if (f32) hipLaunchKernelGGL(k_norm_rows<float>, dim3(M), dim3(256), 0, s, h, w, (float*)y, W, eps);
   else hipLaunchKernelGGL(k_norm_rows<bf16>, dim3(M), dim3(256), 0, s, h, w, (bf16*)y, W, eps);
+  return hipGetLastError();
+}
+
+hipError_t launch_set_i32(int* p, const int* values, int n, hipStream_t s) {
+  for (int i = 0; i < n; i += SetI32::N) {
+    SetI32 v;
+    v.n = n - i < SetI32::N ? n - i : SetI32::N;
+    for (int j = 0; j < v.n; ++j) v.v[j] = values[i + j];
+    hipLaunchKernelGGL(k_set_i32, dim3(1), dim3(SetI32::N), 0, s, p + i, v);
+  }
   return hipGetLastError();
 }
 

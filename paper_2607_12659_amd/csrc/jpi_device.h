@@ -124,5 +124,71 @@ __device__ __forceinline__ float gelu_tanh(float z) {
   return z * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * u2));
 }
 
+// Rotation factors of an EPI_QKV result pair (row, col_lo), or (1, 0) where
+// none applies (V columns, rows past M).  They do not depend on the product,
+// so a kernel can load them before its K loop and pass them to the epilogue.
+__device__ __forceinline__ float2 qkv_rope_factor(const EpiParams& ep, int M, int N, int row, int col_lo) {
+  const int Dh = ep.head_dim, qcols = ep.n_heads * Dh;
+  if (row >= M || col_lo >= N || col_lo >= qcols + Dh) return float2{1.f, 0.f};
+  const int hn = col_lo < qcols ? col_lo / Dh : -1;
+  const int within = col_lo < qcols ? col_lo - hn * Dh : col_lo - qcols;
+  const int d = (within >> 5) * 16 + (within & 15);
+  return ep.rope[(size_t)row * (Dh >> 1) + d];  // row = b * H + i
+}
+
+// EPI_QKV epilogue with the rotation factors already in hand
+template <typename T>
+__device__ __forceinline__ void epilogue_qkv_pre(const EpiParams& ep, int M, int N, int row, int col_lo, float lo,
+                                                 float hi, float2 cs) {
+  if (row >= M || col_lo >= N) return;
+  const int Dh = ep.head_dim, half = Dh >> 1, H = ep.horizon;
+  const int b = row / H, i = row - b * H;
+  const int qcols = ep.n_heads * Dh;
+  if (col_lo < qcols + Dh) {
+    const int hn = col_lo < qcols ? col_lo / Dh : -1;
+    const int within = col_lo < qcols ? col_lo - hn * Dh : col_lo - qcols;
+    const int d = (within >> 5) * 16 + (within & 15);
+    const float r_lo = lo * cs.x - hi * cs.y;
+    const float r_hi = lo * cs.y + hi * cs.x;
+    const size_t kbs = ep.ks_bstride ? (size_t)ep.ks_bstride : (size_t)H * Dh;
+    T* dst = hn >= 0 ? reinterpret_cast<T*>(ep.q) + (((size_t)b * ep.n_heads + hn) * H + i) * Dh
+                     : reinterpret_cast<T*>(ep.ks) + b * kbs + (size_t)i * Dh;
+    dst[d] = from_f32<T>(r_lo);
+    dst[d + half] = from_f32<T>(r_hi);
+  } else {
+    const int within = col_lo - qcols - Dh;
+    T* dst = reinterpret_cast<T*>(ep.vst) + (size_t)b * Dh * ep.vst_ld + i;
+    dst[(size_t)within * ep.vst_ld] = from_f32<T>(lo);
+    dst[(size_t)(within + 16) * ep.vst_ld] = from_f32<T>(hi);
+  }
+}
+
+// s_waitcnt with vmcnt = N and the other counters not waited for
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// wait until at most `later` (<= L) stages of INS loads each are outstanding
+template <int INS, int L>
+__device__ __forceinline__ void wait_later(int later) {
+  if constexpr (L == 0) {
+    wait_vm<0>();
+  } else {
+    if (later >= L) wait_vm<L * INS>();
+    else wait_later<INS, L - 1>(later);
+  }
+}
+
+typedef __attribute__((address_space(3))) char dma_lds_t;
+typedef __attribute__((address_space(3))) const bf16x8 dma_lds_frag;
+
+// One 1 KB direct-to-LDS load: 16 bytes per lane from base + byte offset
+// `off` (zero past `bytes`) into LDS at dst + 16 * lane.
+__device__ __forceinline__ void dma_load_1k(const void* base, unsigned bytes, unsigned off, dma_lds_t* dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000), dst, 16, off, 0, 0, 0);
+}
 
 }  // namespace jpi

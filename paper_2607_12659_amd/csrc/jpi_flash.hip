@@ -501,4 +501,356 @@ hipError_t launch_flash(const AttnLaunch& a, int S, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+// ---------------------------------------------------------------------------
+// Few query rows (the five-launch layers).  With one to eight rollouts the tiles of k_flash
+// leave the chip idle or need many key ranges, and its ring pays a barrier and
+// a memory round trip per 32-key block.  Here a workgroup takes 16 query rows and its
+// four waves split the keys: a wave loads a whole 32-key block (K and V^T,
+// 32 KiB at Dh 256) straight into registers, all at once, multiplies it, and takes the
+// block 4 S further on; the waves' running outputs meet once in LDS.  No barrier
+// inside the loop.  The keys come from their fragment-ordered blocks (KvBlock), so every
+// load reads one contiguous KiB; gathered from the row-major K and V^T the same
+// kernel ran at a third of that rate (batch 8: 29 us).  Every workgroup reads its range's keys
+// from the XCD's L2, so this pays while B * (rows / 16) * keys stays small; from
+// there k_flash, which shares each block between 112 rows, reads less.
+// ---------------------------------------------------------------------------
+typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+
+// address of columns col .. col + 3 (col a multiple of 4) of a row of the attention output
+__device__ __forceinline__ size_t attn_out_at(const AttnLaunch& a, int DH, int m, int col) {
+  const int C = a.nH * DH;
+  if (!a.out_frag) return (size_t)m * C + col;
+  return (((size_t)(m >> 4) * (C / 32) + (col >> 5)) * 64 + ((col & 31) >> 3) * 16 + (m & 15)) * 8 + (col & 7);
+}
+
+constexpr int ROWS_NW = 4;  // waves of k_flash_rows
+
+template <int DH>
+__global__ __launch_bounds__(64 * ROWS_NW, 2) void k_flash_rows(AttnLaunch a, int S, int ntile, bf16* part, float2* ml) {
+  using FS = Flash<DH>;
+  using MF = Mfma<bf16>;
+  constexpr int NST = FS::NST, NT = FS::NT, NW = ROWS_NW, KB = 32;
+  __shared__ f32x4 red[NW][NT][64];
+  __shared__ float2 mls[NW][16];
+  // items (rollout, key range, tile), consecutive ones on one XCD: they share the range's keys
+  const int item = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
+  if (item >= a.B * ntile * S) return;
+  const int b = item / (ntile * S), split = (item / ntile) % S, row0 = (item % ntile) * 16;
+  const int H = a.H, R = a.nH * H;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, fr = lane & 15;
+  const int nbs = (H + KB - 1) / KB;
+  const bf16* act_base = reinterpret_cast<const bf16*>(a.skvf) + (size_t)b * nbs * KvBlock<DH>::ELEMS + lane * 8;
+  const bf16* pre_base = reinterpret_cast<const bf16*>(a.kvf) + (size_t)b * a.kvf_bstride + lane * 8;
+  MF::frag kf[2][NST];
+  u32x4 vf[NT];
+  // action blocks first, then the prefix
+  auto block = [&](int jb) {
+    return jb < nbs ? act_base + (size_t)jb * KvBlock<DH>::ELEMS : pre_base + (size_t)(jb - nbs) * KvBlock<DH>::ELEMS;
+  };
+  auto load_k = [&](const bf16* p) {
+#pragma unroll
+    for (int st = 0; st < NST; ++st)
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) kf[kt][st] = MF::load(p + (kt * NST + st) * 512);
+  };
+  auto load_v = [&](const bf16* p) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) vf[nt] = *reinterpret_cast<const u32x4*>(p + (2 * NST + nt) * 512);
+  };
+  // the first block does not wait for prefix_len: any block below the bound P may be read
+  const int jb0 = split * NW + w;
+  MF::frag qf[NST];
+  const bf16* qb = reinterpret_cast<const bf16*>(a.q) + ((size_t)b * R + min(row0 + fr, R - 1)) * DH + 8 * g;
+#pragma unroll
+  for (int st = 0; st < NST; ++st) qf[st] = MF::load(qb + st * 32);
+  const bf16* p0 = block(min(jb0, nbs + (a.P + KB - 1) / KB - 1));
+  load_k(p0);
+  load_v(p0);
+  __builtin_amdgcn_sched_barrier(0);
+  const int pl = a.prefix_len[b];
+  const int nb = nbs + (pl + KB - 1) / KB;
+  const float qscale = 1.4426950408889634f / sqrtf((float)DH);
+  f32x4 o[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) o[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_ref = -INFINITY, l = 0.f;
+
+  for (int jb = jb0; jb < nb; jb += S * NW) {
+    const bool act = jb < nbs;
+    const int n_valid = min(act ? H - jb * KB : pl - (jb - nbs) * KB, KB);
+    // the next block's K is requested as soon as this one's is multiplied, its V^T after P V: the
+    // registers are free by then (the last turn reads its own block again)
+    const bf16* next = block(jb + S * NW < nb ? jb + S * NW : jb);
+    f32x4 sc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int st = 0; st < NST; ++st)
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) sc[kt] = MF::run(kf[kt][st], qf[st], sc[kt]);
+    __builtin_amdgcn_sched_barrier(0);
+    load_k(next);
+    __builtin_amdgcn_sched_barrier(0);
+    if (n_valid < KB) {  // keys past the valid ones: score -inf, V zero (their memory may hold anything)
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sc[kt][e] = 8 * g + 4 * kt + e < n_valid ? sc[kt][e] : -INFINITY;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) vf[nt] = mask8(vf[nt], n_valid - 8 * g);
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sc[kt][e]);
+    mx = row4_max(mx) * qscale;  // finite: the block holds a valid key
+    const bool over = mx > m_ref + FLASH_LIMIT;  // always on the first block
+    if (__any(over)) {
+      const float f = over ? __builtin_amdgcn_exp2f(m_ref - mx) : 1.f;
+      l *= f;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) o[nt] *= f;
+      m_ref = over ? mx : m_ref;
+    }
+    MF::frag pb;
+    float sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bf16 lo = static_cast<bf16>(__builtin_amdgcn_exp2f(fmaf(sc[0][e], qscale, -m_ref)));
+      const bf16 hi = static_cast<bf16>(__builtin_amdgcn_exp2f(fmaf(sc[1][e], qscale, -m_ref)));
+      pb[e] = lo;
+      pb[4 + e] = hi;
+      sum += static_cast<float>(lo) + static_cast<float>(hi);
+    }
+    l += sum;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) o[nt] = MF::run(__builtin_bit_cast(MF::frag, vf[nt]), pb, o[nt]);
+    __builtin_amdgcn_sched_barrier(0);
+    load_v(next);
+  }
+
+  // the waves' outputs against one reference per row: the largest
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  if (g == 0) mls[w][fr] = float2{m_ref, l};
+  __syncthreads();
+  float m = -INFINITY, lsum = 0.f;
+#pragma unroll
+  for (int v = 0; v < NW; ++v) m = fmaxf(m, mls[v][fr].x);
+#pragma unroll
+  for (int v = 0; v < NW; ++v) {
+    const float2 t = mls[v][fr];
+    lsum += t.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(t.x - m) * t.y;
+  }
+  const int r = row0 + fr;
+  if (S > 1 && w == 0 && g == 0 && r < R) ml[((size_t)split * a.B + b) * R + r] = float2{m, lsum};
+  if (m == -INFINITY) return;  // a range without keys (the same for every row): skipped by the merge
+  const float f = (m_ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref - m)) / lsum;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) red[w][nt][lane] = o[nt] * f;
+  __syncthreads();
+  if (r >= R) return;
+  const int hn = r / H, i = r - hn * H;
+#pragma unroll
+  for (int t = 0; t < (NT + NW - 1) / NW; ++t) {
+    const int nt = w + NW * t;
+    if (nt >= NT) break;
+    f32x4 v = red[0][nt][lane];
+#pragma unroll
+    for (int u = 1; u < NW; ++u) v += red[u][nt][lane];
+    if (S == 1 && a.out_f32) {
+      *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.out) + attn_out_at(a, DH, b * H + i, hn * DH + nt * 16 + 4 * g)) = v;
+      continue;
+    }
+    const bf16x4_t p4 = bf16x4_t{static_cast<bf16>(v[0]), static_cast<bf16>(v[1]), static_cast<bf16>(v[2]), static_cast<bf16>(v[3])};
+    bf16* dst = S == 1 ? reinterpret_cast<bf16*>(a.out) + attn_out_at(a, DH, b * H + i, hn * DH + nt * 16 + 4 * g)
+                       : part + (((size_t)split * a.B + b) * R + r) * DH + nt * 16 + 4 * g;
+    *reinterpret_cast<bf16x4_t*>(dst) = p4;
+  }
+}
+
+// Merge of S key ranges, as k_flash_merge, with S known when compiling: the
+// loads of a row's partials are one round trip (16 predicated ones took 7 us
+// at three rollouts whatever S was).
+template <int DH, int S, typename TO>
+__global__ __launch_bounds__(256) void k_flash_rows_merge(AttnLaunch a, const bf16* part, const float2* ml) {
+  constexpr int TPR = DH / 4, RPB = 256 / TPR;
+  const int R = a.nH * a.H;
+  const int t = threadIdx.x, rr = blockIdx.x * RPB + t / TPR, q4 = t % TPR;
+  if (rr >= a.B * R) return;
+  const int b = rr / R, r = rr - b * R;
+  const int hn = r / a.H, i = r - hn * a.H;
+  float2 mv[S];
+  u32x2 ov[S];
+  float m = -INFINITY;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const size_t rowi = ((size_t)s * a.B + b) * R + r;
+    mv[s] = ml[rowi];
+    ov[s] = *reinterpret_cast<const u32x2*>(part + rowi * DH + 4 * q4);
+  }
+#pragma unroll
+  for (int s = 0; s < S; ++s) m = fmaxf(m, mv[s].x);
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  float lsum = 0.f;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const bool some = mv[s].x != -INFINITY;
+    const float wl = some ? __builtin_amdgcn_exp2f(mv[s].x - m) * mv[s].y : 0.f;
+    const f32x4 v = f32x4{__builtin_bit_cast(float, ov[s][0] << 16), __builtin_bit_cast(float, ov[s][0] & 0xffff0000u),
+                          __builtin_bit_cast(float, ov[s][1] << 16), __builtin_bit_cast(float, ov[s][1] & 0xffff0000u)};
+    if (some) acc += wl * v;  // the partial of a range without keys is not written
+    lsum += wl;
+  }
+  acc *= 1.0f / lsum;
+  TO* out = reinterpret_cast<TO*>(a.out) + attn_out_at(a, DH, b * a.H + i, hn * DH + 4 * q4);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) out[e] = from_f32<TO>(acc[e]);
+}
+
+// Key ranges per 16-row tile: workgroups for the whole chip, at least one 32-key block per wave
+int flash_rows_splits(int B, int nH, int H, int P, int n_cu) {
+  const int ntile = (nH * H + 15) / 16, nb = (H + 31) / 32 + (P + 31) / 32;
+  int s = 1;
+  while (s < 8 && B * ntile * s < n_cu && ROWS_NW * s < nb) s *= 2;
+  return s;
+}
+
+template <int DH, typename TO>
+static hipError_t launch_flash_rows_t(const AttnLaunch& a, int S, hipStream_t s) {
+  const int ntile = (a.nH * a.H + 15) / 16, items = a.B * ntile * S;
+  const size_t rows = (size_t)a.B * a.nH * a.H;
+  bf16* part = reinterpret_cast<bf16*>(a.opart);
+  float2* ml = reinterpret_cast<float2*>(part + (size_t)S * rows * DH);
+  JPI_LAUNCH((k_flash_rows<DH>), dim3((items + 7) / 8 * 8), dim3(64 * ROWS_NW), 0, s, a.ev_start,
+             S == 1 ? a.ev_stop : (hipEvent_t) nullptr, a, S, ntile, part, ml);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || S == 1) return e;
+  constexpr int RPB = 256 / (DH / 4);
+  const dim3 grid((unsigned)((rows + RPB - 1) / RPB));
+  if (S == 2) JPI_LAUNCH((k_flash_rows_merge<DH, 2, TO>), grid, dim3(256), 0, s, (hipEvent_t) nullptr, a.ev_stop, a, part, ml);
+  else if (S == 4) JPI_LAUNCH((k_flash_rows_merge<DH, 4, TO>), grid, dim3(256), 0, s, (hipEvent_t) nullptr, a.ev_stop, a, part, ml);
+  else JPI_LAUNCH((k_flash_rows_merge<DH, 8, TO>), grid, dim3(256), 0, s, (hipEvent_t) nullptr, a.ev_stop, a, part, ml);
+  return hipGetLastError();
+}
+
+hipError_t launch_flash_rows(const AttnLaunch& a, int S, hipStream_t s) {
+  if ((S != 1 && S != 2 && S != 4 && S != 8) || a.H < 1 || a.B < 1) return hipErrorInvalidValue;
+  switch (a.Dh) {
+    case 64: return a.out_f32 ? launch_flash_rows_t<64, float>(a, S, s) : launch_flash_rows_t<64, bf16>(a, S, s);
+    case 128: return a.out_f32 ? launch_flash_rows_t<128, float>(a, S, s) : launch_flash_rows_t<128, bf16>(a, S, s);
+    case 256: return a.out_f32 ? launch_flash_rows_t<256, float>(a, S, s) : launch_flash_rows_t<256, bf16>(a, S, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+// ---------------------------------------------------------------------------
+// Prefix hand-off: one workgroup per (32-key block, rollout, layer) reads the
+// caller's K and V once and writes the resident K and V (unless they are the
+// caller's), the transposed V and, for the bf16 kernels that take them, the
+// fragment-ordered block.  One launch instead of two strided copies and a
+// transpose per layer: batch 8, 816 tokens, 18 layers 316 us before.
+// ---------------------------------------------------------------------------
+template <typename T, int DH>
+__global__ __launch_bounds__(256) void k_bind(BindLaunch a) {
+  constexpr int VEC = 16 / sizeof(T), CPR = DH / VEC, LD = DH + (sizeof(T) == 2 ? 2 : 1);
+  __shared__ T vt[32 * LD];
+  const int key0 = blockIdx.x * 32, b = blockIdx.y, l = blockIdx.z, tid = threadIdx.x;
+  const size_t src = ((size_t)l * a.B + b) * a.P, dst = ((size_t)l * a.Bmax + b) * a.Pmax;
+  const bool in_place = a.in_place;
+  const T* k = reinterpret_cast<const T*>(a.k) + (in_place ? dst : src) * DH;
+  const T* v = reinterpret_cast<const T*>(a.v) + (in_place ? dst : src) * DH;
+  T* kp = reinterpret_cast<T*>(a.kp) + dst * DH;
+  T* vp = reinterpret_cast<T*>(a.vp) + dst * DH;
+  T* vpt = reinterpret_cast<T*>(a.vpt) + ((size_t)l * a.Bmax + b) * DH * a.Ppad;
+  T* blk = a.kvf ? reinterpret_cast<T*>(a.kvf) + (((size_t)l * a.Bmax + b) * a.NBmax + blockIdx.x) * KvBlock<DH>::ELEMS : nullptr;
+  const u32x4 zero = u32x4{0, 0, 0, 0};
+#pragma unroll
+  for (int e = tid; e < 32 * CPR; e += 256) {
+    // fragment order: chunk c of key kk; lanes of a wave cover 16 keys x 4 chunks
+    const int f = e / 64, ln = e % 64;
+    const int kt = f / (CPR / 4), c = (f % (CPR / 4)) * 4 + (ln >> 4), row = ln & 15;
+    const int kk = 8 * (row >> 2) + 4 * kt + (row & 3), key = key0 + kk;
+    const bool ok = key < a.P;
+    const u32x4 x = ok ? *reinterpret_cast<const u32x4*>(k + (size_t)key * DH + c * VEC) : zero;
+    const u32x4 y = ok ? *reinterpret_cast<const u32x4*>(v + (size_t)key * DH + c * VEC) : zero;
+    if (ok && !in_place) {
+      *reinterpret_cast<u32x4*>(kp + (size_t)key * DH + c * VEC) = x;
+      *reinterpret_cast<u32x4*>(vp + (size_t)key * DH + c * VEC) = y;
+    }
+    if constexpr (sizeof(T) == 2)
+      if (blk) *reinterpret_cast<u32x4*>(blk + (size_t)e * 8) = x;  // e is the piece's place: (kt, k step, lane)
+    T tmp[VEC];
+    __builtin_memcpy(tmp, &y, 16);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) vt[kk * LD + c * VEC + i] = tmp[i];
+  }
+  __syncthreads();
+  // V^T pieces of VEC keys: dim d, keys key0 + VEC q ..
+  constexpr int Q = 32 / VEC;
+#pragma unroll
+  for (int e = tid; e < DH * Q; e += 256) {
+    const int d = sizeof(T) == 2 ? (e >> 6) * 16 + (e & 15) : e / Q, q = sizeof(T) == 2 ? (e & 63) >> 4 : e % Q;
+    T tmp[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) tmp[i] = vt[(VEC * q + i) * LD + d];
+    u32x4 x;
+    __builtin_memcpy(&x, tmp, 16);
+    if (key0 + VEC * q < a.P) *reinterpret_cast<u32x4*>(vpt + (size_t)d * a.Ppad + key0 + VEC * q) = x;
+    if constexpr (sizeof(T) == 2)
+      if (blk) *reinterpret_cast<u32x4*>(blk + KvBlock<DH>::V + (size_t)e * 8) = x;
+  }
+}
+
+// The fragment-ordered blocks from the resident K and V^T (after a producer that wrote those).
+template <int DH>
+__global__ __launch_bounds__(256) void k_kv_blocks(BindLaunch a) {
+  const int key0 = blockIdx.x * 32, b = blockIdx.y, l = blockIdx.z;
+  const size_t lb = (size_t)l * a.Bmax + b;
+  const bf16* kp = reinterpret_cast<const bf16*>(a.kp) + lb * a.Pmax * DH;
+  const bf16* vpt = reinterpret_cast<const bf16*>(a.vpt) + lb * DH * a.Ppad;
+  bf16* blk = reinterpret_cast<bf16*>(a.kvf) + (lb * a.NBmax + blockIdx.x) * KvBlock<DH>::ELEMS;
+  const u32x4 zero = u32x4{0, 0, 0, 0};
+#pragma unroll
+  for (int e = threadIdx.x; e < 32 * DH / 8; e += 256) {
+    const int f = e / 64, ln = e % 64, kt = f / (DH / 32), c = (f % (DH / 32)) * 4 + (ln >> 4), row = ln & 15;
+    const int key = key0 + 8 * (row >> 2) + 4 * kt + (row & 3), d = f * 16 + row, kv = key0 + 8 * (ln >> 4);
+    *reinterpret_cast<u32x4*>(blk + (size_t)e * 8) = key < a.P ? *reinterpret_cast<const u32x4*>(kp + (size_t)key * DH + c * 8) : zero;
+    *reinterpret_cast<u32x4*>(blk + KvBlock<DH>::V + (size_t)e * 8) =
+        kv < a.P ? *reinterpret_cast<const u32x4*>(vpt + (size_t)d * a.Ppad + kv) : zero;
+  }
+}
+
+size_t kv_block_elems(int Dh) { return (size_t)64 * Dh; }
+
+hipError_t launch_bind(jpi_dtype dt, const BindLaunch& a, hipStream_t s) {
+  if (a.P < 1 || a.B < 1 || a.L < 1) return hipSuccess;
+  const dim3 grid((a.P + 31) / 32, a.B, a.L);
+#define BIND_DH(DH)                                                                              \
+  do {                                                                                           \
+    if (dt == JPI_BF16) hipLaunchKernelGGL((k_bind<bf16, DH>), grid, dim3(256), 0, s, a);        \
+    else hipLaunchKernelGGL((k_bind<float, DH>), grid, dim3(256), 0, s, a);                      \
+  } while (0)
+  switch (a.Dh) {
+    case 64: BIND_DH(64); break;
+    case 128: BIND_DH(128); break;
+    case 256: BIND_DH(256); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef BIND_DH
+  return hipGetLastError();
+}
+
+hipError_t launch_kv_blocks(const BindLaunch& a, hipStream_t s) {
+  if (a.P < 1 || a.B < 1 || a.L < 1) return hipSuccess;
+  const dim3 grid((a.P + 31) / 32, a.B, a.L);
+  switch (a.Dh) {
+    case 64: hipLaunchKernelGGL(k_kv_blocks<64>, grid, dim3(256), 0, s, a); break;
+    case 128: hipLaunchKernelGGL(k_kv_blocks<128>, grid, dim3(256), 0, s, a); break;
+    case 256: hipLaunchKernelGGL(k_kv_blocks<256>, grid, dim3(256), 0, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 }  // namespace jpi

@@ -30,6 +30,7 @@ struct EpiParams {
   int64_t ks_bstride;    // 0 means H * Dh
   void* vst;             // [B][Dh][vst_ld] (v stored transposed)
   int vst_ld;            // row stride of vst in elements (>= horizon)
+  void* skvf;            // five-launch layers: ks and vst as [B][ceil(H / 32)] KvBlocks instead
   const float2* rope;    // [B][H][Dh/2] (cos, sin) at position prefix_len[b] + i
   int n_heads, head_dim, horizon;
   // EPI_GEGLU: packed columns in 32-wide groups [gate 16 | up 16]
@@ -84,6 +85,88 @@ hipError_t launch_inproj_norm(jpi_dtype dt, const float* x, const void* w_in, co
                               hipStream_t s);
 hipError_t launch_resid_norm(jpi_dtype dt, const RowLaunch& r, bool final_step, hipStream_t s);
 
+// Five-launch layers for few rows (jpi_small.hip).
+enum SmallEpi { SE_QKV = 0, SE_GEGLU = 1, SE_RESID = 2, SE_SWISH = 3 };
+struct SmallGemm {
+  const bf16* A;         // fragment-ordered [M rounded up to 16][32 KS]
+  const bf16* W;         // fragment-ordered [N][32 KS]
+  int M, N, KS;
+  // SE_QKV, SE_GEGLU: result row scaled by 1 / sqrt(sum(ssq row) * inv_w + eps), then + c[n]
+  // (SE_SWISH: + c[n] only)
+  const float* ssq;      // [M][n_ssq] sums of squares of the residual row, 16 columns each
+  int n_ssq;
+  float inv_w, eps;
+  const float* c;        // [N]
+  int64_t c_t0;          // offset (floats) to the t = 0 row of c
+  int seq, n_lead, n_t0; // rows per rollout, correction rows, leading action rows at t = 0
+  EpiParams ep;          // SE_QKV destinations
+  // SE_RESID: h += gate * product
+  float* h;              // [M][N] updated residual rows
+  const float* h_in;     // rows before the update at h_in + row * h_ld
+  int64_t h_ld;
+  const float *gate, *scale;  // [N] scale: of the norm that follows
+  int64_t t0_delta;      // offset (floats) to the t = 0 row of gate and scale
+  float* ssq_out;        // [M][N / 16]
+  bf16* u;               // SE_RESID: h (1 + scale), or null; SE_GEGLU, SE_SWISH: the result; fragment-ordered
+  hipEvent_t ev_start, ev_stop;
+};
+struct SmallHead {
+  int M, W, A, seq, n_lead, n_fixed, n_t0;  // rows m = b * seq + r, correction rows first
+  bool do_out, do_in;
+  float* x;                                 // [B][seq - n_lead][A]
+  float* h;                                 // [M][W]
+  const float *scale_f, *shift_f;           // final norm of the step that ends
+  int64_t t0_delta;                         // to its t = 0 row
+  const bf16* w_out;                        // [A][W]
+  const float* b_out;
+  float dt;
+  const bf16* w_in;                         // [W][A]
+  const float *b_in, *corr;                 // corr [B][n_lead][W]
+  const float* scale;                       // first norm of the step that starts
+  int64_t t0_delta_in;
+  bf16* u;                                  // fragment-ordered
+  float* ssq;                               // [M][W / 16]
+  float eps, inv_w;
+};
+// action-time variant: u[m] = W_a x[m] + b_a, fragment-ordered bf16
+hipError_t launch_action_embed_frag(const float* x, const void* w, const float* b, void* u, int M, int W, int A,
+                                    hipStream_t s);
+// its state rows: h[b] = W_s state[b] + b_s with u = bf16(h (1 + scale)) and the sums of squares
+hipError_t launch_small_state(const float* state, const void* w, const float* b, int B, int W, int state_dim,
+                              const float* scale, float* h, void* u, float* ssq, hipStream_t s);
+bool small_supported(jpi_dtype dt, int W, int nH, int Dh, int F);
+hipError_t launch_small(SmallEpi epi, const SmallGemm& g, hipStream_t s);
+hipError_t launch_small_head(const SmallHead& a, hipStream_t s);
+// out[r][n] = sum_k shift[r][k] w[n][k] for each layer, w bf16 row-major [N][K]; strides in elements
+hipError_t launch_small_shift(const float* shift, int64_t shift_ld, int64_t shift_lstride, const void* w,
+                              int64_t w_lstride, float* out, int64_t out_ld, int64_t out_lstride, int layers, int rows,
+                              int N, int K, hipStream_t s);
+
+// Keys and values of 32 consecutive keys as the MFMA fragments of the attention
+// products, each 64 lanes x 16 bytes in lane order: first K, tile kt (row 4g' + e
+// is key 8g' + 4kt + e) and k step st at fragment kt * Dh/32 + st, then V^T, dims 16 nt ..
+// at fragment Dh/16 + nt (lane: dim lane % 16, keys 8 (lane / 16) ..).
+template <int DH>
+struct KvBlock {
+  static constexpr int ELEMS = 64 * DH, V = 32 * DH;  // elements; of them V^T from here
+  static __host__ __device__ int k_at(int key, int d) {  // key 0 .. 31
+    return ((((key >> 2) & 1) * (DH / 32) + (d >> 5)) * 64 + ((d & 31) >> 3) * 16 + 4 * (key >> 3) + (key & 3)) * 8 + (d & 7);
+  }
+  static __host__ __device__ int v_at(int key, int d) {
+    return V + ((d >> 4) * 64 + (key >> 3) * 16 + (d & 15)) * 8 + (key & 7);
+  }
+};
+size_t kv_block_elems(int Dh);
+struct BindLaunch {
+  const void *k, *v;      // [L][B][P][Dh], or the resident buffers themselves
+  void *kp, *vp, *vpt;    // resident [L][Bmax][Pmax][Dh] and [L][Bmax][Dh][Ppad]
+  void* kvf;              // [L][Bmax][NBmax] blocks, or null
+  bool in_place;          // k and v are kp and vp
+  int L, B, P, Dh, Bmax, Pmax, Ppad, NBmax;
+};
+hipError_t launch_bind(jpi_dtype dt, const BindLaunch& a, hipStream_t s);
+hipError_t launch_kv_blocks(const BindLaunch& a, hipStream_t s);  // kvf from kp and vpt
+
 struct AttnLaunch {
   const void* q;          // [B][nH][H][Dh]
   const void* ks;         // [B][H][Dh], rollout b at ks + b * ks_bstride elements
@@ -93,6 +176,9 @@ struct AttnLaunch {
   const void* kp;         // prefix K: rollout b at kp + b*kp_bstride, key j at + j*Dh
   const void* vpt;        // prefix V transposed: rollout b at vpt + b*vpt_bstride, dim d at + d*vpt_dstride
   int64_t kp_bstride, vpt_bstride, vpt_dstride;  // elements; vpt_dstride a multiple of 8
+  const void* skvf;       // launch_flash_rows: own keys, [B][ceil(H / 32)] blocks
+  const void* kvf;        // and the prefix's, rollout b at kvf + b * kvf_bstride (elements)
+  int64_t kvf_bstride;
   const int* prefix_len;  // device [B]
   int B, nH, H, P, Dh;
   float* opart;           // [B][nH][n_chunks][H][Dh]
@@ -100,6 +186,7 @@ struct AttnLaunch {
   float* lpart;           // [B][nH][n_chunks][H]
   void* out;              // [B*H][nH*Dh] of dtype, or fp32 if out_f32
   int out_f32;
+  int out_frag;           // launch_flash_rows: out is fragment-ordered (rows b * H + i, columns head * Dh + d)
   int n_cu;               // compute units of the device (sizes the bf16 key ranges)
   hipEvent_t ev_start, ev_stop;  // optional: start of the chunk pass, end of the combine
 };
@@ -115,6 +202,9 @@ hipError_t launch_attention(jpi_dtype dt, const AttnLaunch& a, hipStream_t s);
 int flash_splits(int B, int nH, int H, int P, int n_cu);
 size_t flash_scratch_bytes(int B, int nH, int H, int Dh, int S);
 hipError_t launch_flash(const AttnLaunch& a, int S, hipStream_t s);
+// bf16 attention for few query rows: S key ranges (1, 2, 4 or 8) per 16-row tile
+int flash_rows_splits(int B, int nH, int H, int P, int n_cu);
+hipError_t launch_flash_rows(const AttnLaunch& a, int S, hipStream_t s);
 
 // Persistent single-launch denoise (jpi_persist.hip), M <= 64, bf16.
 struct PersistArgs {
@@ -183,6 +273,7 @@ struct AePrefixTarget {
   int64_t kp_lstride, kp_bstride, vpt_lstride, vpt_bstride;
   int vpt_ld;           // Ppad
   int* prefix_len;      // device [Bmax]
+  BindLaunch blocks;    // kvf (null: not kept) is to be filled from kp and vpt with launch_kv_blocks
   float2* rope_tab;     // device [Bmax][H][Dh/2]: the expert's own rows' positions
   int H;                // suffix rows per rollout the rope table covers (correction tokens + horizon)
   float rope_base;
@@ -228,6 +319,7 @@ hipError_t enqueue_block(const BlockLaunch& b, hipStream_t s);
 hipError_t launch_norm_rows(const float* h, const float* w, void* y, int M, int W, float eps, hipStream_t s,
                             bool f32 = false);
 hipError_t launch_fill_i32(int* p, int n, int v, hipStream_t s);
+hipError_t launch_set_i32(int* p, const int* values, int n, hipStream_t s);  // host values, read before it returns
 hipError_t launch_fill_f32(float* p, int n, float v, hipStream_t s);
 hipError_t launch_identity_rope(float2* tab, int n, hipStream_t s);
 hipError_t launch_bcast_rows(const float* src, float* dst, int M, int period, int W, hipStream_t s);
@@ -246,6 +338,8 @@ hipError_t launch_swish_slices(jpi_dtype dt, const float* part, int S, int M, co
 hipError_t launch_put_state_kv(jpi_dtype dt, const void* ks, const void* vst, int vst_ld, void* kp, int64_t kp_bstride,
                                void* vpt, int64_t vpt_bstride, int vpt_dstride, const int* prefix_len, int B, int Dh,
                                hipStream_t s);
+// the same for every layer at once from the blocks skvf [L][B], also into the prefix's blocks
+hipError_t launch_put_state_blocks(const BindLaunch& a, const void* skvf, const int* prefix_len, hipStream_t s);
 
 hipError_t launch_time_embed(float* emb, int rows, int n, int W, hipStream_t s);
 // out[m][n] = act(sum_k in[m][k] w[n][k] + b[n]), fp64 accumulation; act 0 = none, 1 = swish

@@ -65,10 +65,10 @@ bool kind_in_variant(int k, int variant) {
 struct GraphKey {
   int batch, prefix, n_steps, n_fixed, n_corr;
   bool committed_t0;  // committed rows modulated at t = 0
-  bool persist;       // the single-launch path and the multi-kernel path capture different graphs
+  int path;           // each path captures a different graph
   bool operator<(const GraphKey& o) const {
-    return std::tie(batch, prefix, n_steps, n_fixed, n_corr, committed_t0, persist) <
-           std::tie(o.batch, o.prefix, o.n_steps, o.n_fixed, o.n_corr, o.committed_t0, o.persist);
+    return std::tie(batch, prefix, n_steps, n_fixed, n_corr, committed_t0, path) <
+           std::tie(o.batch, o.prefix, o.n_steps, o.n_fixed, o.n_corr, o.committed_t0, o.path);
   }
 };
 
@@ -101,6 +101,9 @@ struct jpi_ctx {
   bool finalized = false;
   // prefix and state
   void *kp = nullptr, *vp = nullptr;  // [L][Bmax][Pmax][Dh] as bound
+  void *kvf = nullptr, *skvf = nullptr, *skvf_state = nullptr;  // KvBlocks: prefix [L][Bmax][NBmax], own rows, state rows
+  int NBmax = 0;
+  bool no_blocks = false;
   void* vpt = nullptr;                 // [L][Bmax][Dh][Ppad] prefix V transposed at bind time
   int Ppad = 0;                        // Pmax + horizon rounded up to a multiple of 8
   int* d_prefix_len = nullptr;
@@ -134,6 +137,7 @@ struct jpi_ctx {
   size_t attn_cap = 0;
   // caches
   std::map<int, float*> tables;
+  std::map<int, float*> shift_tables;  // five-launch layers: [n_steps + 1][L][(nH + 2) Dh + 2F], see ensure_shift_table
   std::map<GraphKey, hipGraphExec_t> graphs;
   hipStream_t cap_stream = nullptr;
   // single-launch (persistent) path
@@ -145,6 +149,9 @@ struct jpi_ctx {
   int persist_occ = -1;        // workgroups per CU the persistent kernel fits (-1: not queried)
   void* w_frag = nullptr;      // layer weights with every matrix fragment-ordered
   bool frag_ready = false;     // w_frag matches w_layers
+  float* ssq = nullptr;        // five-launch layers: [rows][W / 16] sums of squares of the residual rows
+  size_t ssq_cap = 0;
+  void *w_atm_a_frag = nullptr, *w_atm_out_frag = nullptr;  // action-time variant: fragment-ordered copies
   void *ysw = nullptr, *osw = nullptr, *zsw = nullptr, *qsw = nullptr;  // fragment-ordered activations
   // measurement: events around every launch of one kernel kind
   int timed_kind = JPI_KERNEL_NONE;
@@ -202,6 +209,8 @@ void drop_events(jpi_ctx* c) {
 void drop_tables(jpi_ctx* c) {
   for (auto& kv : c->tables) (void)hipFree(kv.second);
   c->tables.clear();
+  for (auto& kv : c->shift_tables) (void)hipFree(kv.second);
+  c->shift_tables.clear();
 }
 
 int64_t expected_elems(const jpi_ctx* c, int k) {
@@ -303,7 +312,7 @@ jpi_status jpi_destroy(jpi_ctx* c) {
                   c->w_layers, c->w_in, c->w_t0, c->w_t1, c->w_mod, c->w_out, c->b_in, c->b_t0, c->b_t1, c->b_mod,
                   c->b_out, c->kp, c->vp, c->vpt, c->d_prefix_len, c->rope_tab, c->committed, c->corr, c->x, c->h, c->y, c->q, c->ks,
                   c->vst, c->o, c->z, c->partial, c->opart, c->pflags, c->perr, c->w_frag, c->ysw, c->osw,
-                  c->zsw, c->qsw, c->ptrace};
+                  c->zsw, c->qsw, c->ptrace, c->ssq, c->kvf, c->skvf, c->w_atm_a_frag, c->w_atm_out_frag};
   for (void* p : bufs)
     if (p) (void)hipFree(p);
   if (c->h_prefix_len) (void)hipHostFree(c->h_prefix_len);
@@ -419,12 +428,13 @@ jpi_status jpi_create(const jpi_config* cfg, int device, jpi_ctx** out) {
   ALLOC(c->corr, std::max<size_t>(1, (size_t)c->Bmax * c->Cmax * W) * 4);
   ALLOC(c->x, M * A * 4);
   ALLOC(c->h, M * W * 4);
-  ALLOC(c->y, M * W * es);
+  const size_t M16 = (M + 15) / 16 * 16;  // fragment-ordered activations fill whole 16-row groups
+  ALLOC(c->y, M16 * W * es);
   ALLOC(c->q, M * nH * Dh * es);
   ALLOC(c->ks, M * Dh * es);
   ALLOC(c->vst, (size_t)c->Bmax * Dh * ((seq_max + 7) / 8 * 8) * es);  // rows padded to 8 elements
-  ALLOC(c->o, M * nH * Dh * es);
-  ALLOC(c->z, M * F * es);
+  ALLOC(c->o, M16 * nH * Dh * es);
+  ALLOC(c->z, M16 * F * es);
   ALLOC(c->pflags, (size_t)persist_flag_words() * sizeof(unsigned));
   ALLOC(c->perr, 256);
   if (persist_trace_build()) {  // room for 64 Euler steps of every layer's 8 phases, 3 stamps each
@@ -448,10 +458,10 @@ jpi_status jpi_create(const jpi_config* cfg, int device, jpi_ctx** out) {
     ALLOC(c->d_plen1, B * 4);
     ALLOC(c->rope_s, B * (Dh / 2) * sizeof(float2));
     ALLOC(c->hs, B * W * 4);
-    ALLOC(c->ys, B * W * es);
+    ALLOC(c->ys, (B + 15) / 16 * 16 * W * es);
     ALLOC(c->ks_s, B * Dh * es);
     ALLOC(c->vst_s, B * Dh * 8 * es);
-    ALLOC(c->u2, M * W * es);
+    ALLOC(c->u2, M16 * W * es);
     if (launch_fill_f32(c->ones, (int)W, 1.0f, 0) != hipSuccess || launch_fill_f32(c->zeros, (int)W, 0.0f, 0) != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess)
       return cleanup_fail(fail(c, JPI_ERR_HIP, "fill"));
@@ -638,6 +648,58 @@ jpi_status jpi_debug_prefix_vt(jpi_ctx* c, void** vt_out, int* ld_out) {
   return JPI_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// The prefix's fragment-ordered blocks, kept where the five-launch layers can
+// run.  Where they do not fit in memory the kernels that read the row-major buffers run.
+jpi_status ensure_blocks(jpi_ctx* c) {
+  if (c->kvf || c->no_blocks || c->Pmax < 1) return JPI_OK;
+  if (!small_supported(c->dt, c->W, c->nH, c->Dh, c->F)) {
+    c->no_blocks = true;
+    return JPI_OK;
+  }
+  const size_t blk = kv_block_elems(c->Dh) * c->esz, S = c->H + c->Cmax;
+  c->NBmax = (c->Pmax + 31) / 32;
+  const size_t own = (size_t)c->Bmax * ((S + 31) / 32) * blk;
+  const size_t state = c->cfg.variant == JPI_VARIANT_ACTION_TIME ? (size_t)c->L * c->Bmax * blk : 0;
+  if (hipMalloc(&c->kvf, (size_t)c->L * c->Bmax * c->NBmax * blk) != hipSuccess) {
+    c->kvf = nullptr;
+  } else if (hipMalloc(&c->skvf, own + state) != hipSuccess) {
+    (void)hipFree(c->kvf);
+    c->kvf = c->skvf = nullptr;
+  }
+  if (!c->kvf) {
+    (void)hipGetLastError();
+    c->no_blocks = true;
+    return JPI_OK;
+  }
+  c->skvf_state = state ? (char*)c->skvf + own : nullptr;
+  return JPI_OK;
+}
+
+BindLaunch bind_launch(const jpi_ctx* c, int batch, int prefix) {
+  BindLaunch b{};
+  b.kp = c->kp;
+  b.vp = c->vp;
+  b.vpt = c->vpt;
+  b.kvf = c->kvf;
+  b.L = c->L;
+  b.B = batch;
+  b.P = prefix;
+  b.Dh = c->Dh;
+  b.Bmax = c->Bmax;
+  b.Pmax = c->Pmax;
+  b.Ppad = c->Ppad;
+  b.NBmax = c->NBmax;
+  return b;
+}
+
+}  // namespace
+
+extern "C" {
+
 jpi_status jpi_bind_prefix(jpi_ctx* c, const void* k, const void* v, const int32_t* prefix_len_host, int batch,
                            int prefix, void* stream) {
   if (!c) return fail(nullptr, JPI_ERR_ARG, "jpi_bind_prefix: ctx is NULL");
@@ -663,30 +725,17 @@ jpi_status jpi_bind_prefix(jpi_ctx* c, const void* k, const void* v, const int32
                                       "for the state token, so every prefix_len must be below max_prefix");
   HIPCHK(c, hipSetDevice(c->device));
   hipStream_t s = (hipStream_t)stream;
-  HIPCHK(c, hipStreamSynchronize(s));  // staging buffer and resident KV are free to overwrite
-  const size_t es = c->esz, Dh = c->Dh;
   const bool in_place = (k == c->kp && v == c->vp);
   if (in_place && prefix != c->Pmax)
     return fail(c, JPI_ERR_SHAPE, "jpi_bind_prefix: the resident buffers must be bound with prefix == max_prefix");
-  if (!in_place && prefix > 0) {
-    for (int l = 0; l < c->L; ++l) {
-      const size_t dst_off = (size_t)l * c->Bmax * c->Pmax * Dh * es;
-      const size_t src_off = (size_t)l * batch * prefix * Dh * es;
-      HIPCHK(c, hipMemcpy2DAsync((char*)c->kp + dst_off, c->Pmax * Dh * es, (const char*)k + src_off, prefix * Dh * es,
-                                 prefix * Dh * es, batch, hipMemcpyDeviceToDevice, s));
-      HIPCHK(c, hipMemcpy2DAsync((char*)c->vp + dst_off, c->Pmax * Dh * es, (const char*)v + src_off, prefix * Dh * es,
-                                 prefix * Dh * es, batch, hipMemcpyDeviceToDevice, s));
-    }
-  }
-  // prefix V transposed ([Dh][key]) for the attention kernels' P.V operand
-  for (int l = 0; l < c->L && prefix > 0; ++l) {
-    const size_t src_off = (size_t)l * c->Bmax * c->Pmax * Dh * es;
-    const size_t dst_off = (size_t)l * c->Bmax * c->Ppad * Dh * es;
-    HIPCHK(c, launch_transpose(c->dt, (const char*)c->vp + src_off, (char*)c->vpt + dst_off, prefix, (int)Dh,
-                               (int64_t)Dh, c->Ppad, (int64_t)c->Pmax * Dh, (int64_t)Dh * c->Ppad, batch, s));
-  }
+  TRY(ensure_blocks(c));
+  BindLaunch bl = bind_launch(c, batch, prefix);
+  bl.k = k;
+  bl.v = v;
+  bl.in_place = in_place;
+  HIPCHK(c, launch_bind(c->dt, bl, s));
   memcpy(c->h_prefix_len, lens.data(), batch * sizeof(int));
-  HIPCHK(c, hipMemcpyAsync(c->d_prefix_len, c->h_prefix_len, batch * sizeof(int), hipMemcpyHostToDevice, s));
+  HIPCHK(c, launch_set_i32(c->d_prefix_len, c->h_prefix_len, batch, s));
   if (c->batch != batch) {  // state rows were bound for another batch
     c->n_fixed = c->n_corr = 0;
     c->state_bound = false;
@@ -770,6 +819,7 @@ jpi_status ensure_table(jpi_ctx* c, int n_steps, hipStream_t s, float** out) {
 struct StepGemms {
   int M;
   int s_o, s_d;  // split-K of the O and Down projections (QKV and GateUp are not split)
+  bool small;    // five-launch layers
   bool persist;  // single-launch path
   // action-time variant: split-K of the action-time MLP's two GEMMs, and of the
   // state token's O and Down projections (M = batch rows)
@@ -793,10 +843,27 @@ bool use_persist(jpi_ctx* c, int batch) {
   return c->persist_occ >= 1;  // one workgroup per CU, grid = CU count: all co-resident
 }
 
+// Five-launch layers (jpi_small.hip) for up to SMALL_ROWS activation rows.  Per
+// call on one MI355X, pi0.5 shape, 816 tokens: 1 rollout 6.6 ms against 7.75 (single
+// launch), 3 rollouts 9.6 against 11.3 and 8 (400 rows) 11.6 against 13.1 (eight launches per layer); the tiny bf16 expert,
+// 4 rollouts, 10 steps 0.59 against 0.91 (single launch).  Past 512 rows the
+// tiles of the eight-launch layers share their operands better.
+// JPI_PERSIST=1 and a wait bound set for its test ask for the single-launch kernel, which
+// otherwise serves widths that are not a multiple of 256.
+constexpr int SMALL_ROWS = 512;
+bool use_small(const jpi_ctx* c, int batch) {
+  const char* e = getenv("JPI_PERSIST");
+  if ((e && e[0] == '1') || c->persist_spin != 0) return false;
+  return c->kvf && batch * (c->H + c->n_corr) <= SMALL_ROWS;
+}
+
 StepGemms plan_gemms(jpi_ctx* c, int batch) {
   StepGemms p;
   p.M = batch * (c->H + c->n_corr);
-  p.persist = use_persist(c, batch);
+  p.small = use_small(c, batch);
+  p.persist = !p.small && use_persist(c, batch);
+  p.s_o = p.s_d = 1;
+  if (p.small) return p;
   if (p.persist) {
     p.s_o = persist_pick_split(c->W / 32, c->nH * c->Dh, c->n_cu);
     p.s_d = persist_pick_split(c->W / 32, c->F, c->n_cu);
@@ -827,7 +894,9 @@ jpi_status ensure_scratch(jpi_ctx* c, int batch, int prefix) {
   }
   const int S = c->H + c->n_corr;
   const size_t nch = p.persist ? (size_t)persist_chunks(prefix, S) : (size_t)attn_n_chunks(c->dt, prefix, S);
-  const size_t attn = (size_t)batch * c->nH * nch * S * (c->Dh + 2);
+  size_t attn = (size_t)batch * c->nH * nch * S * (c->Dh + 2);
+  if (p.small)
+    attn = std::max(attn, (flash_scratch_bytes(batch, c->nH, S, c->Dh, flash_rows_splits(batch, c->nH, S, prefix, c->n_cu)) + 3) / 4);
   if (attn > c->attn_cap) {
     if (c->opart) (void)hipFree(c->opart);
     c->opart = nullptr;
@@ -850,7 +919,24 @@ jpi_status ensure_scratch(jpi_ctx* c, int batch, int prefix) {
     HIPCHK(c, hipDeviceSynchronize());
     changed = true;
   }
-  if (p.persist && !c->w_frag) {
+  if (p.small) {
+    const size_t rows = (size_t)batch * S + batch;  // the action-time variant's state rows follow
+    if (rows * (c->W / 16) > c->ssq_cap) {
+      if (c->ssq) (void)hipFree(c->ssq);
+      c->ssq = nullptr;
+      c->ssq_cap = 0;
+      TRY(dmalloc(c, (void**)&c->ssq, rows * (c->W / 16) * sizeof(float)));
+      c->ssq_cap = rows * (c->W / 16);
+      changed = true;
+    }
+    if (c->cfg.variant == JPI_VARIANT_ACTION_TIME && !c->w_atm_a_frag) {
+      TRY(dmalloc(c, &c->w_atm_a_frag, (size_t)c->W * c->W * c->esz));
+      TRY(dmalloc(c, &c->w_atm_out_frag, (size_t)c->W * c->W * c->esz));
+      c->frag_ready = false;
+      changed = true;
+    }
+  }
+  if ((p.persist || p.small) && !c->w_frag) {
     TRY(dmalloc(c, &c->w_frag, c->layer_elems * c->L * c->esz));
     c->frag_ready = false;
     changed = true;
@@ -873,12 +959,277 @@ jpi_status ensure_frag(jpi_ctx* c, hipStream_t s) {
     HIPCHK(c, launch_frag_order(src + c->off_gu * es, dst + c->off_gu * es, 2 * F, W, s));
     HIPCHK(c, launch_frag_order(src + c->off_d * es, dst + c->off_d * es, W, F, s));
   }
+  if (c->w_atm_a_frag && c->w_atm_out_frag) {
+    HIPCHK(c, launch_frag_order(c->w_atm_a, c->w_atm_a_frag, W, W, s));
+    HIPCHK(c, launch_frag_order(c->w_atm_out, c->w_atm_out_frag, W, W, s));
+  }
   c->frag_ready = true;
   return JPI_OK;
 }
 
+// Five-launch layers: c[n] = sum_k shift[k] W[n][k] of the QKV and the gate/up
+// product for every step time and layer (packed column order), once per
+// (weights, n_steps).  The action-time variant, whose shifts are zero, gets one
+// vector of zeros.
+jpi_status ensure_shift_table(jpi_ctx* c, const float* table, int n_steps, hipStream_t s, float** out) {
+  const bool at = c->cfg.variant == JPI_VARIANT_ACTION_TIME;
+  auto it = c->shift_tables.find(at ? 0 : n_steps);
+  if (it != c->shift_tables.end()) {
+    *out = it->second;
+    return JPI_OK;
+  }
+  const int rows = n_steps + 1, N1 = (c->nH + 2) * c->Dh, N2 = 2 * c->F;
+  const int64_t ld = (int64_t)c->L * (N1 + N2);
+  float* tab = nullptr;
+  TRY(dmalloc(c, (void**)&tab, (at ? (size_t)std::max(N1, N2) : (size_t)rows * ld) * sizeof(float)));
+  if (at) {
+    const hipError_t e0 = launch_fill_f32(tab, std::max(N1, N2), 0.f, s);
+    if (e0 != hipSuccess) {
+      (void)hipFree(tab);
+      return fail(c, JPI_ERR_HIP, std::string("shift table: ") + hipGetErrorString(e0));
+    }
+    c->shift_tables[0] = tab;
+    *out = tab;
+    return JPI_OK;
+  }
+  // the attention norms' shifts (QKV), then the MLP norms', 3 W on (gate/up)
+  const float* shifts = table + c->W;
+  hipError_t e = launch_small_shift(shifts, c->R, 6 * c->W, c->w_layers, (int64_t)c->layer_elems, tab, ld, N1 + N2, c->L,
+                                    rows, N1, c->W, s);
+  if (e == hipSuccess)
+    e = launch_small_shift(shifts + 3 * c->W, c->R, 6 * c->W, (const bf16*)c->w_layers + c->off_gu, (int64_t)c->layer_elems,
+                           tab + N1, ld, N1 + N2, c->L, rows, N2, c->W, s);
+  if (e != hipSuccess) {
+    (void)hipFree(tab);
+    return fail(c, JPI_ERR_HIP, std::string("shift table: ") + hipGetErrorString(e));
+  }
+  c->shift_tables[n_steps] = tab;
+  *out = tab;
+  return JPI_OK;
+}
+
+// Rows that go through the layers together with the five-launch kernels.
+struct SmallRows {
+  int B, S, P;                // rollouts, rows each, bound on plen
+  float *h, *ssq;
+  void* u;
+  void* skvf;                 // own keys and values; layer l's at + l * stride (elements)
+  int64_t skvf_lstride;
+  const int* plen;
+  const float2* rope;
+  int n_lead, n_t0;
+  int64_t t0_delta, c_t0;     // to the t = 0 rows of the modulation and shift tables
+};
+
+// Every layer over the rows in r.h / r.u / r.ssq, modulated by table row tk and
+// shift-table row ck.  time(kind, start, stop) hands out events.
+template <typename Timing>
+hipError_t enqueue_small_layers(jpi_ctx* c, const SmallRows& r, const float* tk, const float* ck, Timing&& time,
+                                hipStream_t s) {
+  const int W = c->W, Dh = c->Dh, nH = c->nH, F = c->F, L = c->L, M = r.B * r.S, HD = nH * Dh;
+  const int N1 = HD + 2 * Dh, N2 = 2 * F;
+  const size_t es = c->esz;
+  hipError_t e;
+  SmallGemm base{};
+  base.M = M;
+  base.ssq = base.ssq_out = r.ssq;
+  base.n_ssq = W / 16;
+  base.inv_w = 1.0f / (float)W;
+  base.eps = c->cfg.rms_eps;
+  base.c_t0 = r.c_t0;
+  base.t0_delta = r.t0_delta;
+  base.seq = r.S;
+  base.n_lead = r.n_lead;
+  base.n_t0 = r.n_t0;
+  base.h = r.h;
+  base.h_in = r.h;
+  base.h_ld = W;
+  // without shifts (action-time variant) every product reads the same zeros
+  const bool at = c->cfg.variant == JPI_VARIANT_ACTION_TIME;
+  const int64_t cl_stride = at ? 0 : N1 + N2, c_gu = at ? 0 : N1;
+  const int split = flash_rows_splits(r.B, nH, r.S, r.P, c->n_cu);
+  for (int l = 0; l < L; ++l) {
+    const bf16* lay = (const bf16*)c->w_frag + (size_t)l * c->layer_elems;
+    const float* am = tk + (size_t)(2 * l) * 3 * W;
+    const float* mm = am + 3 * W;  // after the last layer's MLP rows come the final norm's
+    const float* cl = ck + (size_t)l * cl_stride;
+    char* skvf = (char*)r.skvf + (size_t)l * r.skvf_lstride * es;
+    SmallGemm g = base;
+    g.A = (const bf16*)r.u;
+    g.W = lay;
+    g.N = N1;
+    g.KS = W / 32;
+    g.c = cl;
+    g.ep.q = c->q;
+    g.ep.skvf = skvf;
+    g.ep.rope = r.rope;
+    g.ep.n_heads = nH;
+    g.ep.head_dim = Dh;
+    g.ep.horizon = r.S;
+    time(JPI_KERNEL_QKV, &g.ev_start, &g.ev_stop);
+    if ((e = launch_small(SE_QKV, g, s)) != hipSuccess) return e;
+    AttnLaunch a{};
+    a.q = c->q;
+    a.skvf = skvf;
+    a.kvf_bstride = (int64_t)c->NBmax * kv_block_elems(Dh);
+    a.kvf = (const char*)c->kvf + (size_t)l * c->Bmax * a.kvf_bstride * es;
+    a.prefix_len = r.plen;
+    a.B = r.B;
+    a.nH = nH;
+    a.H = r.S;
+    a.P = r.P;
+    a.Dh = Dh;
+    a.opart = c->opart;
+    a.out = c->o;
+    a.out_frag = 1;
+    a.n_cu = c->n_cu;
+    time(JPI_KERNEL_ATTENTION, &a.ev_start, &a.ev_stop);
+    if ((e = launch_flash_rows(a, split, s)) != hipSuccess) return e;
+    g = base;
+    g.A = (const bf16*)c->o;
+    g.W = lay + c->off_o;
+    g.N = W;
+    g.KS = HD / 32;
+    g.gate = am + 2 * W;
+    g.scale = mm;
+    g.u = (bf16*)r.u;
+    time(JPI_KERNEL_OPROJ, &g.ev_start, &g.ev_stop);
+    if ((e = launch_small(SE_RESID, g, s)) != hipSuccess) return e;
+    g = base;
+    g.A = (const bf16*)r.u;
+    g.W = lay + c->off_gu;
+    g.N = N2;
+    g.KS = W / 32;
+    g.c = cl + c_gu;
+    g.u = (bf16*)c->z;
+    time(JPI_KERNEL_GATEUP, &g.ev_start, &g.ev_stop);
+    if ((e = launch_small(SE_GEGLU, g, s)) != hipSuccess) return e;
+    g = base;
+    g.A = (const bf16*)c->z;
+    g.W = lay + c->off_d;
+    g.N = W;
+    g.KS = F / 32;
+    g.gate = mm + 2 * W;
+    g.scale = mm + 3 * W;
+    g.u = l + 1 < L ? (bf16*)r.u : nullptr;
+    time(JPI_KERNEL_DOWN, &g.ev_start, &g.ev_stop);
+    if ((e = launch_small(SE_RESID, g, s)) != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// The whole N-step loop with the five-launch layers.
+template <typename Timing>
+hipError_t enqueue_small(jpi_ctx* c, const float* table, const float* shift, int n_steps, Timing&& time, hipStream_t s) {
+  const int batch = c->batch, H = c->H, C = c->n_corr, S = C + H, M = batch * S, W = c->W, L = c->L;
+  const bool at = c->cfg.variant == JPI_VARIANT_ACTION_TIME;
+  const int64_t CR = (int64_t)L * ((c->nH + 2) * c->Dh + 2 * c->F);
+  hipError_t e;
+#define ENQ_S(x)                                  \
+  do {                                            \
+    if ((e = (x)) != hipSuccess) return e;        \
+  } while (0)
+  SmallRows r{};
+  r.B = batch;
+  r.S = S;
+  r.P = at ? c->prefix + 1 : c->prefix;
+  r.h = c->h;
+  r.ssq = c->ssq;
+  r.u = c->y;
+  r.skvf = c->skvf;
+  r.plen = at ? c->d_plen1 : c->d_prefix_len;
+  r.rope = c->rope_tab;
+  r.n_lead = C;
+  r.n_t0 = c->committed_t0 && !at ? c->n_fixed : 0;
+  if (at) {
+    // the state token: W_s s + b_s, then every layer over it alone; each layer's key and value go
+    // into prefix slot prefix_len
+    ENQ_S(launch_plus_one(c->d_prefix_len, c->d_plen1, batch, s));
+    ENQ_S(launch_rope_table(c->d_plen1, c->rope_tab, batch, H, c->Dh, c->cfg.rope_base, s));
+    ENQ_S(launch_rope_table(c->d_prefix_len, c->rope_s, batch, 1, c->Dh, c->cfg.rope_base, s));
+    SmallRows t = r;
+    t.S = 1;
+    t.P = c->prefix;
+    t.h = c->hs;
+    t.ssq = c->ssq + (size_t)M * (W / 16);
+    t.u = c->ys;
+    t.skvf = c->skvf_state;
+    t.skvf_lstride = (int64_t)batch * kv_block_elems(c->Dh);
+    t.plen = c->d_prefix_len;
+    t.rope = c->rope_s;
+    t.n_lead = t.n_t0 = 0;
+    ENQ_S(launch_small_state(c->state, c->w_state, c->b_state, batch, W, c->cfg.state_dim, table, t.h, t.u, t.ssq, s));
+    auto untimed = [](int, hipEvent_t* a, hipEvent_t* b) { *a = *b = nullptr; };
+    ENQ_S(enqueue_small_layers(c, t, table, shift, untimed, s));
+    ENQ_S(launch_put_state_blocks(bind_launch(c, batch, c->prefix), c->skvf_state, c->d_prefix_len, s));
+  }
+  SmallHead hd{};
+  hd.M = M;
+  hd.W = W;
+  hd.A = c->A;
+  hd.seq = S;
+  hd.n_lead = C;
+  hd.n_fixed = c->n_fixed;
+  hd.n_t0 = r.n_t0;
+  hd.x = c->x;
+  hd.h = c->h;
+  hd.w_out = (const bf16*)c->w_out;
+  hd.b_out = c->b_out;
+  hd.dt = -1.0f / (float)n_steps;
+  hd.w_in = (const bf16*)c->w_in;
+  hd.b_in = c->b_in;
+  hd.corr = c->corr;
+  hd.u = (bf16*)c->y;
+  hd.ssq = c->ssq;
+  hd.eps = c->cfg.rms_eps;
+  hd.inv_w = 1.0f / (float)W;
+  const float* ctab = table + (size_t)(n_steps + 1) * c->R;  // action-time variant: W_t e(t_k) + b_i after the table
+  for (int k = 0; k <= n_steps; ++k) {
+    const float* tk = table + (size_t)k * c->R;
+    hd.do_out = k > 0;
+    hd.do_in = k < n_steps && !at;
+    hd.scale_f = tk - c->R + (size_t)6 * L * W;  // the final norm of the step that ends
+    hd.shift_f = hd.scale_f + W;
+    hd.t0_delta = (int64_t)(n_steps - (k - 1)) * c->R;
+    hd.scale = tk;
+    hd.t0_delta_in = (int64_t)(n_steps - k) * c->R;
+    if (hd.do_out || hd.do_in) ENQ_S(launch_small_head(hd, s));
+    if (k == n_steps) break;
+    if (at) {
+      // h = W_o swish(W_i [W_a x + b_a ; e(t_k)] + b_i) + b_o with the first norm's u
+      ENQ_S(launch_action_embed_frag(c->x, c->w_in, c->b_in, c->u2, M, W, c->A, s));
+      SmallGemm g{};
+      g.M = M;
+      g.N = W;
+      g.KS = W / 32;
+      g.seq = S;
+      g.A = (const bf16*)c->u2;
+      g.W = (const bf16*)c->w_atm_a_frag;
+      g.c = ctab + (size_t)k * W;
+      g.u = (bf16*)c->z;
+      ENQ_S(launch_small(SE_SWISH, g, s));
+      g.A = (const bf16*)c->z;
+      g.W = (const bf16*)c->w_atm_out_frag;
+      g.c = nullptr;
+      g.h = c->h;
+      g.h_in = c->b_atm_out;  // every row starts from the bias
+      g.h_ld = 0;
+      g.gate = tk + 2 * W;  // ones in the plain-norm table
+      g.scale = tk;
+      g.ssq_out = c->ssq;
+      g.u = (bf16*)c->y;
+      ENQ_S(launch_small(SE_RESID, g, s));
+    }
+    r.t0_delta = (int64_t)(n_steps - k) * c->R;
+    r.c_t0 = (int64_t)(n_steps - k) * CR;
+    ENQ_S(enqueue_small_layers(c, r, tk, at ? shift : shift + (size_t)k * CR, time, s));
+  }
+#undef ENQ_S
+  return hipSuccess;
+}
+
 // Enqueue the whole N-step loop on stream s (eagerly or under capture).
-hipError_t enqueue_steps(jpi_ctx* c, const float* table, int n_steps, hipStream_t s) {
+hipError_t enqueue_steps(jpi_ctx* c, const float* table, const float* shift, int n_steps, hipStream_t s) {
   const int batch = c->batch, prefix = c->prefix, H = c->H, C = c->n_corr;
   const int S = C + H;  // suffix rows per rollout: correction tokens, then action tokens
   const StepGemms p = plan_gemms(c, batch);
@@ -914,6 +1265,7 @@ hipError_t enqueue_steps(jpi_ctx* c, const float* table, int n_steps, hipStream_
     *stop = c->ev[c->ev_used + 1];
     c->ev_used += 2;
   };
+  if (p.small) return enqueue_small(c, table, shift, n_steps, timing, s);
   if (at) {
     // the state token: W_s s + b_s, then every layer over it alone (it sees the prefix
     // and itself); each layer's key and value go into prefix slot prefix_len
@@ -1252,21 +1604,24 @@ jpi_status jpi_denoise(jpi_ctx* c, const float* noise_dev, int n_steps, float* a
   TRY(ensure_table(c, n_steps, s, &table));
   // the action-time variant's action rows also see the state token's prefix slot
   TRY(ensure_scratch(c, c->batch, c->prefix + (c->cfg.variant == JPI_VARIANT_ACTION_TIME ? 1 : 0)));
-  if (use_persist(c, c->batch)) TRY(ensure_frag(c, s));
+  const StepGemms plan = plan_gemms(c, c->batch);
+  float* shift = nullptr;
+  if (plan.persist || plan.small) TRY(ensure_frag(c, s));
+  if (plan.small) TRY(ensure_shift_table(c, table, n_steps, s, &shift));
   HIPCHK(c, launch_init_x(noise_dev, c->committed, c->x, c->batch, c->H, c->A, c->n_fixed, s));
   if (c->rope_rows != c->H + c->n_corr) {  // the suffix length changed since the table was built
     HIPCHK(c, launch_rope_table(c->d_prefix_len, c->rope_tab, c->batch, c->H + c->n_corr, c->Dh, c->cfg.rope_base, s));
     c->rope_rows = c->H + c->n_corr;
   }
   if (eager_mode() || c->timed_kind >= 0) {
-    HIPCHK(c, enqueue_steps(c, table, n_steps, s));
+    HIPCHK(c, enqueue_steps(c, table, shift, n_steps, s));
   } else {
-    const GraphKey key{c->batch, c->prefix, n_steps, c->n_fixed, c->n_corr, c->committed_t0, use_persist(c, c->batch)};
+    const GraphKey key{c->batch, c->prefix, n_steps, c->n_fixed, c->n_corr, c->committed_t0, plan.small ? 2 : plan.persist ? 1 : 0};
     auto it = c->graphs.find(key);
     if (it == c->graphs.end()) {
       hipGraph_t graph = nullptr;
       HIPCHK(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-      hipError_t e = enqueue_steps(c, table, n_steps, c->cap_stream);
+      hipError_t e = enqueue_steps(c, table, shift, n_steps, c->cap_stream);
       hipError_t e2 = hipStreamEndCapture(c->cap_stream, &graph);
       if (e != hipSuccess || e2 != hipSuccess) {
         if (graph) (void)hipGraphDestroy(graph);
@@ -1498,6 +1853,9 @@ jpi_status jpi::ae_prefix_target(jpi_ctx* c, int L, int Dh, jpi_dtype dt, int ba
   t->vpt_bstride = (int64_t)Dh * c->Ppad;
   t->vpt_lstride = (int64_t)c->Bmax * t->vpt_bstride;
   t->prefix_len = c->d_prefix_len;
+  const jpi_status st = ensure_blocks(c);
+  if (st != JPI_OK) return st;
+  t->blocks = bind_launch(c, batch, prefix);
   t->rope_tab = c->rope_tab;
   t->H = c->H + c->n_corr;
   t->rope_base = c->cfg.rope_base;

@@ -70,7 +70,33 @@ __global__ void k_put_state_kv(const T* __restrict__ ks, const T* __restrict__ v
   }
 }
 
+template <int DH>
+__global__ void k_put_state_blocks(BindLaunch a, const bf16* __restrict__ skvf, const int* __restrict__ prefix_len) {
+  const int b = blockIdx.x, l = blockIdx.y, pl = prefix_len[b];
+  const size_t lb = (size_t)l * a.Bmax + b;
+  const bf16* s = skvf + ((size_t)l * a.B + b) * KvBlock<DH>::ELEMS;
+  bf16* blk = reinterpret_cast<bf16*>(a.kvf) + (lb * a.NBmax + pl / 32) * KvBlock<DH>::ELEMS;
+  for (int d = threadIdx.x; d < DH; d += blockDim.x) {
+    const bf16 k = s[KvBlock<DH>::k_at(0, d)], v = s[KvBlock<DH>::v_at(0, d)];
+    reinterpret_cast<bf16*>(a.kp)[(lb * a.Pmax + pl) * DH + d] = k;
+    reinterpret_cast<bf16*>(a.vpt)[(lb * DH + d) * a.Ppad + pl] = v;
+    blk[KvBlock<DH>::k_at(pl % 32, d)] = k;
+    blk[KvBlock<DH>::v_at(pl % 32, d)] = v;
+  }
+}
+
 }  // namespace
+
+hipError_t launch_put_state_blocks(const BindLaunch& a, const void* skvf, const int* prefix_len, hipStream_t s) {
+  const dim3 grid(a.B, a.L);
+  switch (a.Dh) {
+    case 64: hipLaunchKernelGGL(k_put_state_blocks<64>, grid, dim3(64), 0, s, a, (const bf16*)skvf, prefix_len); break;
+    case 128: hipLaunchKernelGGL(k_put_state_blocks<128>, grid, dim3(128), 0, s, a, (const bf16*)skvf, prefix_len); break;
+    case 256: hipLaunchKernelGGL(k_put_state_blocks<256>, grid, dim3(256), 0, s, a, (const bf16*)skvf, prefix_len); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
 
 hipError_t launch_const_table(float* tab, const float* norms, int rows, int L, int W, hipStream_t s) {
   hipLaunchKernelGGL(k_const_table, dim3(1024), dim3(256), 0, s, tab, norms, rows, L, W);

@@ -290,6 +290,7 @@ jpi_status jpi_vlm_prefill(jpi_vlm* v, const float* emb, int batch, int prefix, 
     VCHK(v, enqueue_block(b, s));
   }
   if (hidden_out) VCHK(v, hipMemcpyAsync(hidden_out, v->y, (size_t)M * W * 2, hipMemcpyDeviceToDevice, s));
+  if (tg.blocks.kvf) VCHK(v, launch_kv_blocks(tg.blocks, s));
   // bind: prefix_len = prefix for every rollout; the expert's own rows sit at positions prefix + i
   VCHK(v, launch_fill_i32(tg.prefix_len, batch, prefix, s));
   VCHK(v, launch_rope_table(tg.prefix_len, tg.rope_tab, batch, tg.H, Dh, tg.rope_base, s));

@@ -121,7 +121,7 @@ def main():
     if not args.child:
         if not os.path.exists(TRACE_LIB):
             sys.exit("%s is not built: run with --build first" % TRACE_LIB)
-        env = dict(os.environ, JPI_LIB=TRACE_LIB)
+        env = dict(os.environ, JPI_PERSIST="1", JPI_LIB=TRACE_LIB)
         cmd = [sys.executable, "-m", "paper_2607_12659_amd.trace_links", "--child", "--workload", args.workload,
                "--calls", str(args.calls)] + (["--json", args.json] if args.json else [])
         sys.exit(subprocess.call(cmd, env=env, cwd=ROOT))

@@ -1,0 +1,121 @@
+"""The five-launch layers (few activation rows) and the one-launch prefix
+hand-off, at the edges of their tiles, against the fp64 oracle and exact copies.
+
+Tolerance of the denoise cases: every product's inputs are rounded to bf16
+(relative 2^-9 each); over two layers and two steps with amplified gates the
+error measured on the eight-launch layers is 0.1-2e-3, so 4e-3 per rollout.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_util import Inputs, assert_bf16, device_view_i16, make_expert, run, run_env, torch_cuda
+
+pytestmark = pytest.mark.gpu
+REL, ABS = 4e-3, 4e-2
+
+SHAPES = {
+    # contraction of 8 steps (no 32-step turns), an action width that is no multiple of 8, two heads per 128 columns
+    "w256": synth.Dims(n_layers=2, width=256, n_heads=4, n_kv_heads=1, head_dim=64, mlp_dim=512, action_dim=7, horizon=10),
+    # Dh 128, contractions of 16 and 40 steps
+    "w512": synth.Dims(n_layers=2, width=512, n_heads=10, n_kv_heads=1, head_dim=128, mlp_dim=1280, action_dim=24, horizon=17),
+    "w1024": synth.Dims(n_layers=2, width=1024, n_heads=8, n_kv_heads=1, head_dim=256, mlp_dim=4096, action_dim=32, horizon=50),
+}
+LENS = [70, 0, 33, 1, 64, 31, 32, 69, 63, 65]
+
+
+def _case(shape, batch, n_fixed=0, n_corr=0, prefix=70):
+    lens = tuple(min(LENS[b % len(LENS)], prefix) for b in range(batch))
+    wl = synth.Workload("small-%s-b%d" % (shape, batch), SHAPES[shape], prefix=prefix, batch=batch, n_steps=2,
+                        n_fixed=n_fixed, dtype="bf16", prefix_len=lens, mod_gain=8.0)
+    inp = Inputs(wl)
+    corr = synth.normal_f32(wl.seed, "item", 1.0, (batch, n_corr, wl.dims.width)) if n_corr else None
+    return wl, inp, corr
+
+
+def _oracle(wl, inp, corr, t0=False):
+    return oracle.denoise(oracle.Expert(wl.dims, inp.weights), inp.noise, inp.K, inp.V, inp.prefix_len, wl.n_steps,
+                          committed=inp.committed, n_fixed=wl.n_fixed, corr=corr, committed_t0=t0)
+
+
+# rows: 10, 30, 130, 510 | 17, 34 .. 289 | 50, 100, 200, 250, 300, 500 and with correction tokens 53, 159, 424
+@pytest.mark.parametrize("shape,batch,n_fixed,n_corr,t0", [
+    ("w256", 1, 0, 0, False), ("w256", 3, 4, 0, True), ("w256", 13, 0, 3, False), ("w256", 51, 2, 0, False),
+    ("w512", 1, 0, 0, False), ("w512", 4, 3, 2, True), ("w512", 17, 0, 0, False),
+    ("w1024", 1, 0, 0, False), ("w1024", 1, 10, 3, True), ("w1024", 2, 0, 0, False), ("w1024", 3, 7, 3, False),
+    ("w1024", 4, 0, 0, False), ("w1024", 5, 7, 0, True), ("w1024", 6, 0, 0, False), ("w1024", 8, 5, 3, True),
+    ("w1024", 10, 0, 0, False)])
+def test_small_rows_match_oracle(shape, batch, n_fixed, n_corr, t0):
+    wl, inp, corr = _case(shape, batch, n_fixed, n_corr)
+    print("case", wl.name, n_fixed, n_corr, t0, flush=True)
+    ae = make_expert(wl, inp.weights, max_batch=batch + 1, max_prefix=wl.prefix + 5, max_corr=n_corr)
+    try:
+        ae.set_committed_t0(t0)
+        kw = dict(prefix_len=inp.prefix_len, committed=inp.committed, n_fixed=n_fixed, corr=corr)
+        got = run(ae, inp.K, inp.V, inp.noise, wl.n_steps, **kw)
+        assert_bf16(got, _oracle(wl, inp, corr, t0), wl.name, reg_rel=REL, reg_abs=ABS)
+        assert np.array_equal(got, run(ae, inp.K, inp.V, inp.noise, wl.n_steps, **kw))
+        if n_fixed:
+            assert np.array_equal(got[:, :n_fixed], inp.committed.astype(np.float64))
+    finally:
+        ae.close()
+
+
+def test_small_rows_after_longer_rows():
+    """Own-key blocks keep what a longer call left behind their last key; it must not show."""
+    wl, inp, corr = _case("w1024", 2, 0, 4)
+    ae = make_expert(wl, inp.weights, max_corr=4)
+    try:
+        first = run(ae, inp.K, inp.V, inp.noise, wl.n_steps, prefix_len=inp.prefix_len)
+        run(ae, inp.K, inp.V, inp.noise * np.float32(50), wl.n_steps, prefix_len=inp.prefix_len, corr=corr * np.float32(50))
+        assert np.array_equal(first, run(ae, inp.K, inp.V, inp.noise, wl.n_steps, prefix_len=inp.prefix_len))
+    finally:
+        ae.close()
+
+
+@pytest.mark.parametrize("shape,batch", [("w256", 3), ("w1024", 1)])
+def test_single_launch_kernel_still_matches(shape, batch):
+    """JPI_PERSIST=1 asks for the single-launch kernel; the two agree within the bf16 bars."""
+    wl, inp, _ = _case(shape, batch)
+    ae = make_expert(wl, inp.weights)
+    try:
+        got = run_env(ae, "1", inp.K, inp.V, inp.noise, wl.n_steps, prefix_len=inp.prefix_len)
+        assert_bf16(got, _oracle(wl, inp, None), wl.name + "-single", reg_rel=REL, reg_abs=ABS)
+    finally:
+        ae.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("Dh,B,P,Pmax", [(64, 1, 1, 40), (64, 3, 31, 31), (128, 2, 32, 45), (128, 1, 33, 33),
+                                         (256, 2, 100, 131), (256, 3, 64, 64)])
+def test_bind_prefix_copies(dtype, Dh, B, P, Pmax):
+    """K, V and transposed V of every layer and rollout, exactly; then a hand-off in place gives the same V^T."""
+    torch = torch_cuda()
+    from paper_2607_12659_amd import jpi
+    from paper_2607_12659_amd.expert import ActionExpert, to_device
+    d = synth.Dims(n_layers=2, width=256, n_heads=4, n_kv_heads=1, head_dim=Dh, mlp_dim=512, action_dim=7, horizon=10)
+    wl = synth.Workload("bind", d, prefix=P, batch=B, n_steps=1, n_fixed=0, dtype=dtype)
+    K, V = synth.make_prefix(wl)
+    ae = ActionExpert(d, dtype, B + 1, Pmax)
+    try:
+        ae.bind_prefix(to_device(K), to_device(V))
+        torch.cuda.synchronize()
+        _, kp, vp = jpi.jpi_prefix_buffers(ae.ctx)
+        _, vt, ld = jpi.jpi_debug_prefix_vt(ae.ctx)
+        w = 1 if dtype == "bf16" else 2  # 16-bit words per element
+
+        def host(ptr, *shape):
+            a = device_view_i16(ptr, shape[:-1] + (shape[-1] * w,)).cpu().numpy()
+            return a.view(np.uint16 if dtype == "bf16" else np.float32)
+        assert np.array_equal(host(kp, 2, B + 1, Pmax, Dh)[:, :B, :P], K)
+        assert np.array_equal(host(vp, 2, B + 1, Pmax, Dh)[:, :B, :P], V)
+        first = host(vt, 2, B + 1, Dh, ld)[:, :B, :, :P].copy()
+        assert np.array_equal(first, V.transpose(0, 1, 3, 2))
+        if P == Pmax:
+            assert jpi.jpi_bind_prefix(ae.ctx, kp, vp, None, B, P) == jpi.JPI_OK
+            torch.cuda.synchronize()
+            assert np.array_equal(host(vt, 2, B + 1, Dh, ld)[:, :B, :, :P], first)
+            assert np.array_equal(host(kp, 2, B + 1, Pmax, Dh)[:, :B, :P], K)
+    finally:
+        ae.close()
