@@ -91,6 +91,8 @@ __device__ __forceinline__ rsrc_t rsrc(const void* base, int64_t bytes) {
 struct FlashSrc {
   rsrc_t k_act, v_act, k_pre, v_pre;
   int nbs, H, pl;  // action blocks (they come first), action keys, prefix keys
+  int last;        // last block of the sequence
+  rsrc_t blk;      // prefix as KvBlocks (then k_pre and v_pre are not used)
 };
 
 // Direct-to-LDS loads of block jb into one ring stage.  Wave w loads
@@ -104,13 +106,26 @@ struct FlashSrc {
 // operand is not part of the buffer's range check): K rows past the last
 // valid key read as zero and nothing past the source is touched.  Returns
 // the block's valid key count (>= 1).
-template <int DH>
+template <int DH, bool BLK>
 __device__ __forceinline__ int flash_issue(lds_t* stage, const FlashSrc& src, int jb, u32 koff, u32 vaoff, u32 vpoff,
                                            int vst_ld, int vpt_ld) {
   using FS = Flash<DH>;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool act = jb < src.nbs;
   const int key0 = (act ? jb : jb - src.nbs) * FS::KB;
+  if (BLK && !act) {
+    // a KvBlock is a stage's content in order: whole KiB per load, from where they lie.  A block past the
+    // sequence is never multiplied; the last one (or block 0 of an empty prefix) is read in its place.
+    const u32 at = (u32)max(min(jb, src.last) - src.nbs, 0) * FS::STAGE;
+    const u32 lo = (threadIdx.x & 63) * 16;
+#pragma unroll
+    for (int u = 0; u < FS::LDW; ++u) {
+      const int fi = w + FS::NW * u;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(src.blk, stage + fi * 1024, 16, lo, at + fi * 1024, 0, 0);
+    }
+    const int n = src.pl - key0;
+    return n < FS::KB ? n : FS::KB;
+  }
   const rsrc_t rk = act ? src.k_act : src.k_pre;
   const rsrc_t rv = act ? src.v_act : src.v_pre;
   const u32 voff = act ? vaoff : vpoff;
@@ -259,7 +274,7 @@ __device__ __forceinline__ void flash_compute(const char* cur, int n_valid,
 // them; the grid is T rounded up to a multiple of 8 workgroups.  The hardware
 // hands workgroup i to XCD i % 8, so item (i % 8) * (grid / 8) + i / 8 puts
 // consecutive items, which share a rollout's keys and values, in one XCD's L2.
-template <int DH>
+template <int DH, bool BLK>
 __global__ __launch_bounds__(512) void k_flash(AttnLaunch a, int S, int nqt, int qrows, void* part, float2* ml) {
   using FS = Flash<DH>;
   using MF = Mfma<bf16>;
@@ -281,6 +296,9 @@ __global__ __launch_bounds__(512) void k_flash(AttnLaunch a, int S, int nqt, int
   src.H = H;
   src.pl = pl;
   const int nb = src.nbs + (pl + FS::KB - 1) / FS::KB;
+  src.last = nb - 1;
+  if constexpr (BLK)
+    src.blk = rsrc(reinterpret_cast<const bf16*>(a.kvf) + (size_t)b * a.kvf_bstride, (int64_t)a.kvf_bstride * 2);
   const int jb0 = (int)((int64_t)split * nb / S), jb1 = (int)((int64_t)(split + 1) * nb / S);
   const int nblk = jb1 - jb0;
   // this wave's first query row; tile qt holds rows [qt * qrows, (qt + 1) * qrows)
@@ -327,7 +345,7 @@ __global__ __launch_bounds__(512) void k_flash(AttnLaunch a, int S, int nqt, int
   int nval[NS];
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
-    nval[s] = flash_issue<DH>(ring + s * FS::STAGE, src, jb0 + s, koff, vaoff, vpoff, vst_ld, vpt_ld);
+    nval[s] = flash_issue<DH, BLK>(ring + s * FS::STAGE, src, jb0 + s, koff, vaoff, vpoff, vst_ld, vpt_ld);
   flash_wait<(NS - 1) * LDW, false>();
 
   // log2-domain scores: s * log2(e) / sqrt(Dh)
@@ -361,7 +379,7 @@ __global__ __launch_bounds__(512) void k_flash(AttnLaunch a, int S, int nqt, int
     __builtin_amdgcn_s_barrier();
     if (j + NS - 1 < nblk) {
       const int ns = (j + NS - 1) % NS;
-      const int nv = flash_issue<DH>(ring + ns * FS::STAGE, src, jb0 + j + NS - 1, koff, vaoff, vpoff, vst_ld, vpt_ld);
+      const int nv = flash_issue<DH, BLK>(ring + ns * FS::STAGE, src, jb0 + j + NS - 1, koff, vaoff, vpoff, vst_ld, vpt_ld);
 #pragma unroll
       for (int s = 0; s < NS; ++s) nval[s] = s == ns ? nv : nval[s];
     }
@@ -474,8 +492,12 @@ static hipError_t launch_flash_t(const AttnLaunch& a, int S, hipStream_t s) {
   void* part = a.opart;
   float2* ml = reinterpret_cast<float2*>(reinterpret_cast<char*>(a.opart) + (size_t)S * rows * DH * 2);
   const int items = a.B * nqt * S;
-  JPI_LAUNCH((k_flash<DH>), dim3((items + 7) / 8 * 8), dim3(Flash<DH>::NW * 64), 0, s, a.ev_start,
-             S == 1 ? a.ev_stop : (hipEvent_t) nullptr, a, S, nqt, qrows, part, ml);
+  if (a.kvf && a.P > 0)
+    JPI_LAUNCH((k_flash<DH, true>), dim3((items + 7) / 8 * 8), dim3(Flash<DH>::NW * 64), 0, s, a.ev_start,
+               S == 1 ? a.ev_stop : (hipEvent_t) nullptr, a, S, nqt, qrows, part, ml);
+  else
+    JPI_LAUNCH((k_flash<DH, false>), dim3((items + 7) / 8 * 8), dim3(Flash<DH>::NW * 64), 0, s, a.ev_start,
+               S == 1 ? a.ev_stop : (hipEvent_t) nullptr, a, S, nqt, qrows, part, ml);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || S == 1) return e;
   constexpr int RPB = 256 / (DH / 4);

@@ -1487,6 +1487,10 @@ hipError_t enqueue_steps(jpi_ctx* c, const float* table, const float* shift, int
       a.kp_bstride = (int64_t)c->Pmax * Dh;
       a.vpt_bstride = (int64_t)c->Ppad * Dh;
       a.vpt_dstride = c->Ppad;
+      if (c->kvf && !at) {  // (the state token's slot is written to K and V^T only here)
+        a.kvf_bstride = (int64_t)c->NBmax * kv_block_elems(Dh);
+        a.kvf = (const char*)c->kvf + (size_t)l * c->Bmax * a.kvf_bstride * es;
+      }
       a.prefix_len = plen_act;
       a.B = batch;
       a.nH = nH;
