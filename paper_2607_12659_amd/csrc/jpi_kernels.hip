@@ -625,6 +625,12 @@ hipError_t launch_gemm(jpi_dtype dt, const GemmLaunch& g, hipStream_t s) {
     if (gemm_pipe_enabled() && g.M <= 512 && tiles(128, 128) < n_cu && g.splitk == 1 && g.K % DmaSmall::BK == 0 &&
         (size_t)g.N * g.K * 2 < (1u << 31))
       return launch_dma<DmaSmall>(g, s);
+    // a K split whose 128 x 128 tiles still leave half of the units idle: 64 x 64 tiles on the pipelined kernel
+    // (with the slices' sum, against the register-staged 128 x 128 kernel: M = 150, N = 1024, K = 4096 in 4
+    // slices 19.4 -> 9.1 us, in 2 slices 31.1 -> 12.3; M = 400, K = 2048 in 4 slices 14.3 -> 10.0)
+    if (gemm_pipe_enabled() && g.M <= 512 && 2 * tiles(128, 128) <= n_cu && (g.K / g.splitk) % DmaSmall::BK == 0 &&
+        (size_t)g.N * g.K * 2 < (1u << 31))
+      return launch_dma<DmaSmall>(g, s);
     // Larger M: 256 x 256 tiles on the direct-to-LDS ring (64-deep slices, double-buffered, sixteen
     // waves) when such tiles alone cover the units (GateUp at M = 3200: 71.5 us on the register-staged
     // k_gemm_big, 68.1 us on the first, eight-wave version of this ring), else one round of 128 x 256 ring
@@ -658,8 +664,30 @@ __global__ void k_sum_slices(const float* __restrict__ P, float* __restrict__ C,
   C[i] = v;
 }
 
+// The same sum for up to four slices of a multiple of four elements: every load of a
+// thread's piece in flight at once.
+template <int S>
+__global__ void k_sum_slices4(const f32x4* __restrict__ P, f32x4* __restrict__ C, size_t n4) {
+  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+  if (i >= n4) return;
+  f32x4 t[S];
+#pragma unroll
+  for (int z = 0; z < S; ++z) t[z] = P[z * n4 + i];
+  f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int z = 0; z < S; ++z) v += t[z];
+  C[i] = v;
+}
+
 hipError_t launch_sum_slices(const float* P, float* C, int S, size_t MN, hipStream_t s) {
-  hipLaunchKernelGGL(k_sum_slices, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, s, P, C, S, MN);
+  const bool aligned = MN % 4 == 0 && ((uintptr_t)P | (uintptr_t)C) % 16 == 0;
+  const dim3 grid4((unsigned)((MN / 4 + 255) / 256));
+  if (aligned && S == 2)
+    hipLaunchKernelGGL(k_sum_slices4<2>, grid4, dim3(256), 0, s, (const f32x4*)P, (f32x4*)C, MN / 4);
+  else if (aligned && S == 4)
+    hipLaunchKernelGGL(k_sum_slices4<4>, grid4, dim3(256), 0, s, (const f32x4*)P, (f32x4*)C, MN / 4);
+  else
+    hipLaunchKernelGGL(k_sum_slices, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, s, P, C, S, MN);
   return hipGetLastError();
 }
 
