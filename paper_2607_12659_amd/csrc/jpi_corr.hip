@@ -15,6 +15,7 @@
 // Linear layers with bias run as: residual rows preset to the bias, fp32
 // split-K GEMM slices, then the residual + norm row kernel with gate 1, which
 // also gives the next block's normalised input.
+#include <algorithm>
 #include <cstring>
 #include <string>
 #include <vector>
@@ -28,6 +29,7 @@ using namespace jpi;
 namespace {
 
 constexpr int NBLK = 4;
+constexpr int XKV_SPLIT = 4;  // K slices of the VLM tokens' key and value product (d_VLM is a multiple of 256)
 const char* block_prefix[NBLK] = {"qformer.", "action_block.", "blocks.0.", "blocks.1."};
 enum { BLK_QF, BLK_ACT, BLK_J0, BLK_J1 };
 enum BKind { B_ATTN_NORM, B_Q, B_K, B_V, B_O, B_MLP_NORM, B_GATE, B_UP, B_DOWN, B_N };
@@ -95,6 +97,105 @@ __global__ __launch_bounds__(256) void k_conf(const bf16* __restrict__ y, const 
   if (threadIdx.x == 0) conf[b] = acc + bconf[0];
 }
 
+// ---- the five-launch layers' side
+__device__ __forceinline__ size_t frag_at(int m, int k, int K) {
+  return (((size_t)(m >> 4) * (K >> 5) + (k >> 5)) * 64 + ((k & 31) >> 3) * 16 + (m & 15)) * 8 + (k & 7);
+}
+
+// k_action_in with a fragment-ordered result, four columns per thread
+__global__ __launch_bounds__(256) void k_action_in_frag(const float* __restrict__ x, const bf16* __restrict__ w,
+                                                        const float* __restrict__ b, bf16* __restrict__ u, int W, int A) {
+  __shared__ float xs[256];
+  const int m = blockIdx.x;
+  for (int a = threadIdx.x; a < A; a += 256) xs[a] = x[(size_t)m * A + a];
+  __syncthreads();
+  for (int k = 4 * threadIdx.x; k < W; k += 1024) {
+    f32x4 h = *reinterpret_cast<const f32x4*>(b + k);
+    if (A % 8 == 0) {
+      for (int q = 0; q < A; q += 8)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bf16x8 wv = *reinterpret_cast<const bf16x8*>(w + (size_t)(k + e) * A + q);
+#pragma unroll
+          for (int z = 0; z < 8; ++z) h[e] = fmaf(xs[q + z], (float)wv[z], h[e]);
+        }
+    } else {
+      for (int q = 0; q < A; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = fmaf(xs[q], (float)w[(size_t)(k + e) * A + q], h[e]);
+    }
+    typedef bf16 b4 __attribute__((ext_vector_type(4)));
+    *reinterpret_cast<b4*>(u + frag_at(m, k, W)) =
+        b4{(bf16)gelu_tanh(h[0]), (bf16)gelu_tanh(h[1]), (bf16)gelu_tanh(h[2]), (bf16)gelu_tanh(h[3])};
+  }
+}
+
+// k_fuse_in with a fragment-ordered result
+__global__ __launch_bounds__(256) void k_fuse_in_frag(const float* __restrict__ c, const float* __restrict__ hact,
+                                                      bf16* __restrict__ X, int T, int n, int W) {
+  const int m = blockIdx.x, b = m / T;
+  for (int k = 4 * threadIdx.x; k < 2 * W; k += 1024) {
+    const f32x4 v = k < W ? *reinterpret_cast<const f32x4*>(c + (size_t)m * W + k)
+                          : *reinterpret_cast<const f32x4*>(hact + ((size_t)b * n + n - 1) * W + k - W);
+    typedef bf16 b4 __attribute__((ext_vector_type(4)));
+    *reinterpret_cast<b4*>(X + frag_at(m, k, 2 * W)) = b4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
+  }
+}
+
+// conf[b] = sum_k w_conf[k] mean_j y_j[k] + b_conf with y_j = h_j (1 + w_final) / sqrt(mean h_j^2 + eps)
+__global__ __launch_bounds__(256) void k_conf_rows(const float* __restrict__ h, const float* __restrict__ ssq,
+                                                   const float* __restrict__ wfinal, const bf16* __restrict__ wconf,
+                                                   const float* __restrict__ bconf, float* __restrict__ conf, int T,
+                                                   int W, float eps) {
+  __shared__ float red[4], rs[64];
+  const int b = blockIdx.x, lane = threadIdx.x & 63;
+  for (int j = threadIdx.x >> 6; j < T; j += 4) {
+    const float s = wave_sum(lane < W / 16 ? ssq[((size_t)b * T + j) * (W / 16) + lane] : 0.f);
+    if (lane == 0) rs[j] = 1.0f / sqrtf(s / (float)W + eps);
+  }
+  __syncthreads();
+  float acc = 0.f;
+  for (int k = threadIdx.x; k < W; k += 256) {
+    float ym = 0.f;
+    for (int j = 0; j < T; ++j) ym += rs[j] * h[((size_t)b * T + j) * W + k];
+    acc = fmaf((float)wconf[k] * (1.0f + wfinal[k]), ym / (float)T, acc);
+  }
+  acc = block_sum_256(acc, red);
+  if (threadIdx.x == 0) conf[b] = acc + bconf[0];
+}
+
+// Sum of S split-K slices [M][2 Dh] (k columns in RoPE pack order, then v) of a rollout's VLM tokens into
+// its KvBlocks: one workgroup per 32 tokens, rollout and 32 columns, four columns of a token per thread
+// (with every column in one workgroup 26 of them took 13 us at 816 tokens).
+template <int S>
+__global__ __launch_bounds__(256) void k_xkv_blocks(const float* __restrict__ part, int M, int n, int Dh,
+                                                    bf16* __restrict__ kvf, int64_t bstride) {
+  const int b = blockIdx.y, t0 = blockIdx.x * 32, C = 2 * Dh, half = Dh / 2;
+  bf16* blk = kvf + b * bstride + (int64_t)blockIdx.x * 64 * Dh;
+  const int key = threadIdx.x / 8, col = blockIdx.z * 32 + (threadIdx.x % 8) * 4;
+  f32x4 t[S];
+#pragma unroll
+  for (int z = 0; z < S; ++z)
+    t[z] = t0 + key < n ? *reinterpret_cast<const f32x4*>(part + ((size_t)z * M + (size_t)b * n + t0 + key) * C + col)
+                        : f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 v = t[0];
+#pragma unroll
+  for (int z = 1; z < S; ++z) v += t[z];
+  typedef bf16 b4 __attribute__((ext_vector_type(4)));
+  const b4 w = b4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
+  if (col < Dh) {
+    const int p = col & 31, d = (col >> 5) * 16 + (p & 15) + (p >= 16 ? half : 0);
+    const int at = ((((key >> 2) & 1) * (Dh >> 5) + (d >> 5)) * 64 + ((d & 31) >> 3) * 16 + 4 * (key >> 3) + (key & 3)) * 8 + (d & 7);
+    *reinterpret_cast<b4*>(blk + at) = w;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int d = col - Dh + i;
+      blk[32 * Dh + ((d >> 4) * 64 + (key >> 3) * 16 + (d & 15)) * 8 + (key & 7)] = w[i];
+    }
+  }
+}
+
 }  // namespace
 
 struct jpi_corr {
@@ -120,6 +221,15 @@ struct jpi_corr {
   float *partial = nullptr, *opart = nullptr;
   float *ones = nullptr, *zeros = nullptr;
   int *tlen = nullptr, *zero_len = nullptr;
+  // five-launch layers (where they can run): fragment-ordered weights and what depends on the weights only
+  bool small = false;
+  bf16 *f_blocks = nullptr, *f_a1 = nullptr, *f_fuse = nullptr, *f_corr = nullptr;
+  float *ssq = nullptr;                       // [rows][W / 16]
+  bf16 *skvf = nullptr, *kvf = nullptr;       // own keys' blocks; the VLM tokens' [Bmax][NBmax]
+  float *h_q = nullptr;                       // Q-Former: the learned queries, a copy per rollout,
+  bf16 *q_q = nullptr, *skvf_q = nullptr;     // and their query, key and value rows
+  float2 *rope_one = nullptr, *rope_pos = nullptr;  // [Hmax][Dh/2]: no rotation; positions 0 ..
+  int NBmax = 0;
   float2 *rope_id = nullptr, *rope_act = nullptr;
 };
 
@@ -210,6 +320,149 @@ hipError_t linear_norm(jpi_corr* m, const void* A, const void* Wt, const float* 
   return launch_resid_norm(JPI_BF16, r, false, s);
 }
 
+constexpr int SMALL_MAX_ROWS = 512;
+
+void drop_small(jpi_corr* m) {
+  for (void* p : {(void*)m->f_blocks, (void*)m->f_a1, (void*)m->f_fuse, (void*)m->f_corr, (void*)m->ssq, (void*)m->skvf,
+                  (void*)m->kvf, (void*)m->h_q, (void*)m->q_q, (void*)m->skvf_q, (void*)m->rope_one, (void*)m->rope_pos})
+    if (p) (void)hipFree(p);
+  m->f_blocks = m->f_a1 = m->f_fuse = m->f_corr = m->skvf = m->kvf = m->q_q = m->skvf_q = nullptr;
+  m->ssq = m->h_q = nullptr;
+  m->rope_one = m->rope_pos = nullptr;
+  m->small = false;
+}
+
+// A block over B rollouts of H rows on the five-launch layers, gate 1 and shift 0
+SmallLayer small_base(const jpi_corr* m, int blk, int B, int H) {
+  SmallLayer y{};
+  y.B = B;
+  y.S = H;
+  y.W = m->W;
+  y.nH = m->nH;
+  y.Dh = m->Dh;
+  y.F = m->F;
+  y.n_cu = m->n_cu;
+  y.w = m->f_blocks + (size_t)blk * m->layer_elems;
+  y.off_o = m->off_o;
+  y.off_gu = m->off_gu;
+  y.off_d = m->off_d;
+  y.h_in = y.h = m->h;
+  y.ssq = m->ssq;
+  y.u_in = y.u = (bf16*)m->y;
+  y.u_out = true;
+  y.q = m->q;
+  y.o = m->o;
+  y.z = m->z;
+  y.skvf = m->skvf;
+  y.kvf = m->kvf;  // no earlier keys (P = 0) unless the caller sets them
+  y.kvf_bstride = (int64_t)m->NBmax * kv_block_elems(m->Dh);
+  y.rope = m->rope_one;
+  y.rope_shared = 1;
+  y.c_qkv = y.c_gu = m->zeros;  // long enough for either product
+  y.gate_attn = y.gate_mlp = m->ones;
+  y.scale_mlp = m->norms + ((size_t)2 * blk + 1) * m->W;
+  y.eps = m->cfg.rms_eps;
+  y.opart = m->opart;
+  return y;
+}
+
+// h = bias + A Wt^T with the u of the next norm and the sums of squares
+hipError_t small_linear(const jpi_corr* m, const void* A, const bf16* Wt, const float* bias, int M, int K,
+                        const float* next_norm, hipStream_t s) {
+  SmallGemm g{};
+  g.M = M;
+  g.N = m->W;
+  g.KS = K / 32;
+  g.seq = M;
+  g.A = (const bf16*)A;
+  g.W = Wt;
+  g.h = m->h;
+  g.h_in = bias;
+  g.h_ld = 0;
+  g.gate = m->ones;
+  g.scale = next_norm;
+  g.ssq_out = m->ssq;
+  g.u = (bf16*)m->y;
+  return launch_small(SE_RESID, g, s);
+}
+
+// Everything of the five-launch path that depends on the weights only, and its buffers.  Where they do not
+// fit, m->small stays false and the eight-launch blocks run.
+hipError_t ready_small(jpi_corr* m, hipStream_t s) {
+  const size_t W = m->W, Dh = m->Dh, nH = m->nH, HD = nH * Dh, F = m->F, B = m->Bmax, T = m->T;
+  const size_t blk = kv_block_elems((int)Dh);
+  if (!small_supported(JPI_BF16, m->W, m->nH, m->Dh, m->F) || (int)(B * T) > SMALL_MAX_ROWS) return hipSuccess;
+  m->NBmax = (m->Tmax + 31) / 32;
+  if (!m->f_blocks) {
+    bool ok = true;
+    auto alloc = [&](auto** p, size_t bytes) {
+      if (ok && hipMalloc((void**)p, bytes) != hipSuccess) ok = false;
+    };
+    alloc(&m->f_blocks, (size_t)NBLK * m->layer_elems * 2);
+    alloc(&m->f_a1, W * W * 2);
+    alloc(&m->f_fuse, W * 2 * W * 2);
+    alloc(&m->f_corr, W * W * 2);
+    alloc(&m->ssq, (size_t)m->Mmax * (W / 16) * 4);
+    alloc(&m->skvf, B * ((m->Hmax + 31) / 32) * blk * 2);
+    alloc(&m->kvf, B * m->NBmax * blk * 2);
+    alloc(&m->h_q, B * T * W * 4);
+    alloc(&m->q_q, B * T * HD * 2);
+    alloc(&m->skvf_q, B * ((T + 31) / 32) * blk * 2);
+    alloc(&m->rope_one, (size_t)m->Hmax * (Dh / 2) * sizeof(float2));
+    alloc(&m->rope_pos, (size_t)m->Hmax * (Dh / 2) * sizeof(float2));
+    if (!ok) {
+      (void)hipGetLastError();
+      drop_small(m);
+      return hipSuccess;
+    }
+  }
+  hipError_t e = hipSuccess;
+  auto run = [&](hipError_t r) {
+    if (e == hipSuccess) e = r;
+  };
+  const bf16* wb = (const bf16*)m->w_blocks;
+  for (int b = 0; b < NBLK; ++b) {
+    const size_t o = (size_t)b * m->layer_elems;
+    run(launch_frag_order(wb + o, m->f_blocks + o, (int)((nH + 2) * Dh), (int)W, s));
+    run(launch_frag_order(wb + o + m->off_o, m->f_blocks + o + m->off_o, (int)W, (int)HD, s));
+    run(launch_frag_order(wb + o + m->off_gu, m->f_blocks + o + m->off_gu, (int)(2 * F), (int)W, s));
+    run(launch_frag_order(wb + o + m->off_d, m->f_blocks + o + m->off_d, (int)W, (int)F, s));
+  }
+  run(launch_frag_order(m->w_a1, m->f_a1, (int)W, (int)W, s));
+  run(launch_frag_order(m->w_fuse, m->f_fuse, (int)W, (int)(2 * W), s));
+  run(launch_frag_order(m->w_corr, m->f_corr, (int)W, (int)W, s));
+  run(launch_identity_rope(m->rope_one, m->Hmax * (int)(Dh / 2), s));
+  run(launch_rope_table(m->zero_len, m->rope_pos, 1, m->Hmax, (int)Dh, m->cfg.rope_base, s));
+  // the learned queries' rows do not depend on a call: residual rows and their QKV product, a copy per rollout
+  run(launch_bcast_rows(m->query, m->h_q, (int)(B * T), (int)T, (int)W, s));
+  run(launch_small_rows(m->h_q, m->norms, (int)(B * T), (int)W, m->y, m->ssq, s));
+  if (e == hipSuccess) {
+    SmallGemm g{};
+    g.A = (const bf16*)m->y;
+    g.W = m->f_blocks;
+    g.M = (int)(B * T);
+    g.N = (int)((nH + 2) * Dh);
+    g.KS = (int)W / 32;
+    g.ssq = m->ssq;
+    g.n_ssq = (int)W / 16;
+    g.inv_w = 1.0f / (float)W;
+    g.eps = m->cfg.rms_eps;
+    g.c = m->zeros;
+    g.seq = (int)T;
+    g.ep.q = m->q_q;
+    g.ep.skvf = m->skvf_q;
+    g.ep.rope = m->rope_one;
+    g.ep.rope_shared = 1;
+    g.ep.n_heads = (int)nH;
+    g.ep.head_dim = (int)Dh;
+    g.ep.horizon = (int)T;
+    run(launch_small(SE_QKV, g, s));
+  }
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  m->small = e == hipSuccess;
+  return e;
+}
+
 }  // namespace
 
 extern "C" {
@@ -223,6 +476,7 @@ jpi_status jpi_corr_destroy(jpi_corr* m) {
                   m->vst, m->xk, m->xvt, (void*)m->partial, (void*)m->opart, (void*)m->ones, (void*)m->zeros,
                   (void*)m->tlen, (void*)m->zero_len, (void*)m->rope_id, (void*)m->rope_act})
     if (p) (void)hipFree(p);
+  drop_small(m);
   delete m;
   return JPI_OK;
 }
@@ -296,20 +550,23 @@ jpi_status jpi_corr_create(const jpi_corr_config* cfg, int device, jpi_corr** ou
   alloc((void**)&m->b_corr, W * 4);
   alloc((void**)&m->b_conf, 4);
   alloc((void**)&m->h, M * W * 4);
-  alloc(&m->y, M * W * 2);
+  const size_t M16 = (M + 15) / 16 * 16;  // fragment-ordered activations fill whole 16-row groups
+  alloc(&m->y, M16 * W * 2);
   alloc(&m->q, M * nH * Dh * 2);
-  alloc(&m->o, M * nH * Dh * 2);
-  alloc(&m->z, M * F * 2);
-  alloc(&m->u, M * W * 2);
-  alloc(&m->xcat, B * m->T * 2 * W * 2);
+  alloc(&m->o, M16 * nH * Dh * 2);
+  alloc(&m->z, M16 * F * 2);
+  alloc(&m->u, M16 * W * 2);
+  alloc(&m->xcat, (B * m->T + 15) / 16 * 16 * 2 * W * 2);
   alloc(&m->ks, M * Dh * 2);
   alloc(&m->vst, B * Dh * ((m->Hmax + 7) / 8 * 8) * 2);
   alloc(&m->xk, B * m->Tmax * Dh * 2);
   alloc(&m->xvt, B * Dh * m->Tpad * 2);
-  alloc((void**)&m->partial, (size_t)16 * M * W * 4);
+  // split-K slices of a block, or of the VLM tokens' keys and values (XKV_SPLIT slices)
+  alloc((void**)&m->partial, std::max((size_t)16 * M * W, (size_t)XKV_SPLIT * B * m->Tmax * 2 * Dh) * 4);
   alloc((void**)&m->opart, attn_q > attn_b ? attn_q : attn_b);
   alloc((void**)&m->ones, W * 4);
-  alloc((void**)&m->zeros, W * 4);
+  const size_t n_zero = std::max(std::max(W, 2 * F), (nH + 2) * Dh);
+  alloc((void**)&m->zeros, n_zero * 4);
   alloc((void**)&m->tlen, B * 4);
   alloc((void**)&m->zero_len, B * 4);
   alloc((void**)&m->rope_id, rope_rows * (Dh / 2) * sizeof(float2));
@@ -319,7 +576,7 @@ jpi_status jpi_corr_create(const jpi_corr_config* cfg, int device, jpi_corr** ou
     jpi_corr_destroy(m);
     return JPI_ERR_OOM;
   }
-  if (launch_fill_f32(m->ones, (int)W, 1.0f, 0) != hipSuccess || launch_fill_f32(m->zeros, (int)W, 0.0f, 0) != hipSuccess ||
+  if (launch_fill_f32(m->ones, (int)W, 1.0f, 0) != hipSuccess || launch_fill_f32(m->zeros, (int)n_zero, 0.0f, 0) != hipSuccess ||
       launch_fill_i32(m->zero_len, (int)B, 0, 0) != hipSuccess ||
       launch_identity_rope(m->rope_id, (int)(rope_rows * (Dh / 2)), 0) != hipSuccess ||
       hipDeviceSynchronize() != hipSuccess) {
@@ -427,7 +684,6 @@ jpi_status jpi_corr_set_weight(jpi_corr* m, const char* name, const void* data, 
 }
 
 jpi_status jpi_corr_finalize_weights(jpi_corr* m, void* stream) {
-  (void)stream;
   if (!m) return JPI_ERR_ARG;
   for (int bl = 0; bl < NBLK; ++bl)
     for (int k = 0; k < B_N; ++k)
@@ -435,6 +691,9 @@ jpi_status jpi_corr_finalize_weights(jpi_corr* m, void* stream) {
         return cfail(m, JPI_ERR_STATE, std::string("missing tensor ") + block_prefix[bl] + bkind_suffix[k]);
   for (int k = 0; k < G_N; ++k)
     if (!m->have[(size_t)NBLK * B_N + k]) return cfail(m, JPI_ERR_STATE, std::string("missing tensor ") + gkind_name[k]);
+  CCHK(m, hipSetDevice(m->device));
+  m->small = false;
+  CCHK(m, ready_small(m, (hipStream_t)stream));
   m->finalized = true;
   return JPI_OK;
 }
@@ -449,6 +708,39 @@ jpi_status jpi_corr_compress(jpi_corr* m, const void* vlm_state, int batch, int 
   CCHK(m, hipSetDevice(m->device));
   hipStream_t s = (hipStream_t)stream;
   const int W = m->W, Dh = m->Dh, T = m->T;
+  if (m->small) {
+    // the VLM tokens' keys and values: split over K (816 tokens, K 2048: 52 tiles of 64 x 64 in all), summed into blocks
+    GemmLaunch g{};
+    g.A = vlm_state;
+    g.W = m->w_xkv;
+    g.M = batch * n_tokens;
+    g.N = 2 * Dh;
+    g.K = m->V;
+    g.splitk = g.M > 64 ? XKV_SPLIT : 1;
+    g.n_cu = m->n_cu;
+    g.epi = EPI_STORE_F32;
+    g.ep.out_f32 = m->partial;
+    CCHK(m, launch_gemm(JPI_BF16, g, s));
+    const int64_t bstride = (int64_t)m->NBmax * kv_block_elems(Dh);
+    const dim3 grid((n_tokens + 31) / 32, batch, 2 * Dh / 32);
+    if (g.splitk == 1)
+      hipLaunchKernelGGL(k_xkv_blocks<1>, grid, dim3(256), 0, s, m->partial, g.M, n_tokens, Dh, m->kvf, bstride);
+    else
+      hipLaunchKernelGGL(k_xkv_blocks<XKV_SPLIT>, grid, dim3(256), 0, s, m->partial, g.M, n_tokens, Dh, m->kvf, bstride);
+    CCHK(m, hipGetLastError());
+    // the learned queries' block over them; its residual rows are the result
+    SmallLayer y = small_base(m, BLK_QF, batch, T);
+    y.own_done = true;
+    y.q = m->q_q;
+    y.skvf = m->skvf_q;
+    y.h_in = m->h_q;
+    y.h = state_out;
+    y.P = n_tokens;
+    y.u_out = false;
+    y.scale_next = m->norms;
+    CCHK(m, enqueue_small_layer(y, s));
+    return JPI_OK;
+  }
   CCHK(m, launch_fill_i32(m->tlen, batch, n_tokens, s));
   // the VLM tokens' keys and values (no query heads, no rotation)
   GemmLaunch g{};
@@ -498,6 +790,44 @@ jpi_status jpi_corr_predict(jpi_corr* m, const float* state, const float* action
   hipStream_t s = (hipStream_t)stream;
   const int W = m->W, Dh = m->Dh, T = m->T, n = n_actions, Ma = batch * n, Mq = batch * T;
   const float* nrm = m->norms;
+  if (m->small && Ma <= SMALL_MAX_ROWS) {
+    hipLaunchKernelGGL(k_action_in_frag, dim3(Ma), dim3(256), 0, s, actions, (const bf16*)m->w_a0, m->b_a0,
+                       (bf16*)m->u, W, m->A);
+    CCHK(m, hipGetLastError());
+    CCHK(m, small_linear(m, m->u, m->f_a1, m->b_a1, Ma, W, nrm + (size_t)2 * BLK_ACT * W, s));
+    SmallLayer y = small_base(m, BLK_ACT, batch, n);
+    y.rope = m->rope_pos;
+    y.u_out = false;
+    y.scale_next = nrm;
+    CCHK(m, enqueue_small_layer(y, s));
+    hipLaunchKernelGGL(k_fuse_in_frag, dim3(Mq), dim3(256), 0, s, state, m->h, (bf16*)m->xcat, T, n, W);
+    CCHK(m, hipGetLastError());
+    CCHK(m, small_linear(m, m->xcat, m->f_fuse, m->b_fuse, Mq, 2 * W, nrm + (size_t)2 * BLK_J0 * W, s));
+    y = small_base(m, BLK_J0, batch, T);
+    y.scale_next = nrm + (size_t)2 * BLK_J1 * W;
+    CCHK(m, enqueue_small_layer(y, s));
+    y = small_base(m, BLK_J1, batch, T);
+    y.scale_next = m->final_norm;
+    CCHK(m, enqueue_small_layer(y, s));
+    SmallGemm g{};
+    g.A = (const bf16*)m->y;
+    g.W = m->f_corr;
+    g.M = Mq;
+    g.N = W;
+    g.KS = W / 32;
+    g.ssq = m->ssq;
+    g.n_ssq = W / 16;
+    g.inv_w = 1.0f / (float)W;
+    g.eps = m->cfg.rms_eps;
+    g.c = m->b_corr;
+    g.seq = Mq;
+    g.h = item_out;
+    CCHK(m, launch_small(SE_F32, g, s));
+    hipLaunchKernelGGL(k_conf_rows, dim3(batch), dim3(256), 0, s, m->h, m->ssq, m->final_norm, (const bf16*)m->w_conf,
+                       m->b_conf, conf_out, T, W, m->cfg.rms_eps);
+    CCHK(m, hipGetLastError());
+    return JPI_OK;
+  }
   // action branch: MLP, then the block with RoPE at positions 0 .. n-1
   CCHK(m, launch_rope_table(m->zero_len, m->rope_act, batch, n, Dh, m->cfg.rope_base, s));
   hipLaunchKernelGGL(k_action_in, dim3(Ma), dim3(256), 0, s, actions, (const bf16*)m->w_a0, m->b_a0, (bf16*)m->u, W,

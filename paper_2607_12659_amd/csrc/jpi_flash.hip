@@ -590,7 +590,7 @@ __global__ __launch_bounds__(64 * ROWS_NW, 2) void k_flash_rows(AttnLaunch a, in
   load_k(p0);
   load_v(p0);
   __builtin_amdgcn_sched_barrier(0);
-  const int pl = a.prefix_len[b];
+  const int pl = a.prefix_len ? a.prefix_len[b] : a.P;
   const int nb = nbs + (pl + KB - 1) / KB;
   const float qscale = 1.4426950408889634f / sqrtf((float)DH);
   f32x4 o[NT];

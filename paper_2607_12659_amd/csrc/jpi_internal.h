@@ -31,6 +31,7 @@ struct EpiParams {
   void* vst;             // [B][Dh][vst_ld] (v stored transposed)
   int vst_ld;            // row stride of vst in elements (>= horizon)
   void* skvf;            // five-launch layers: ks and vst as [B][ceil(H / 32)] KvBlocks instead
+  int rope_shared;       // five-launch layers: one table [H][Dh/2] for every rollout
   const float2* rope;    // [B][H][Dh/2] (cos, sin) at position prefix_len[b] + i
   int n_heads, head_dim, horizon;
   // EPI_GEGLU: packed columns in 32-wide groups [gate 16 | up 16]
@@ -86,12 +87,12 @@ hipError_t launch_inproj_norm(jpi_dtype dt, const float* x, const void* w_in, co
 hipError_t launch_resid_norm(jpi_dtype dt, const RowLaunch& r, bool final_step, hipStream_t s);
 
 // Five-launch layers for few rows (jpi_small.hip).
-enum SmallEpi { SE_QKV = 0, SE_GEGLU = 1, SE_RESID = 2, SE_SWISH = 3 };
+enum SmallEpi { SE_QKV = 0, SE_GEGLU = 1, SE_RESID = 2, SE_SWISH = 3, SE_F32 = 4 };
 struct SmallGemm {
   const bf16* A;         // fragment-ordered [M rounded up to 16][32 KS]
   const bf16* W;         // fragment-ordered [N][32 KS]
   int M, N, KS;
-  // SE_QKV, SE_GEGLU: result row scaled by 1 / sqrt(sum(ssq row) * inv_w + eps), then + c[n]
+  // SE_QKV, SE_GEGLU, SE_F32: result row scaled by 1 / sqrt(sum(ssq row) * inv_w + eps), then + c[n]
   // (SE_SWISH: + c[n] only)
   const float* ssq;      // [M][n_ssq] sums of squares of the residual row, 16 columns each
   int n_ssq;
@@ -101,7 +102,7 @@ struct SmallGemm {
   int seq, n_lead, n_t0; // rows per rollout, correction rows, leading action rows at t = 0
   EpiParams ep;          // SE_QKV destinations
   // SE_RESID: h += gate * product
-  float* h;              // [M][N] updated residual rows
+  float* h;              // [M][N] updated residual rows; SE_F32: the result
   const float* h_in;     // rows before the update at h_in + row * h_ld
   int64_t h_ld;
   const float *gate, *scale;  // [N] scale: of the norm that follows
@@ -134,6 +135,37 @@ hipError_t launch_action_embed_frag(const float* x, const void* w, const float* 
 // its state rows: h[b] = W_s state[b] + b_s with u = bf16(h (1 + scale)) and the sums of squares
 hipError_t launch_small_state(const float* state, const void* w, const float* b, int B, int W, int state_dim,
                               const float* scale, float* h, void* u, float* ssq, hipStream_t s);
+// u = bf16(h (1 + scale)), fragment-ordered, and the sums of squares of h [M][W]
+hipError_t launch_small_rows(const float* h, const float* scale, int M, int W, void* u, float* ssq, hipStream_t s);
+// One decoder layer: QKV, attention, O, gate/up, Down.
+struct SmallLayer {
+  int B, S, W, nH, Dh, F, n_cu;    // B rollouts of S rows
+  const bf16* w;                   // fragment-ordered layer
+  size_t off_o, off_gu, off_d;     // element offsets in it
+  const float* h_in;               // residual rows before the layer
+  float* h;                        // after it ([B S][W]; h_in may be h)
+  float* ssq;                      // [B S][W / 16]
+  const bf16* u_in;                // h_in's u, not needed with own_done
+  bf16* u;                         // after the layer (and between its halves)
+  bool u_out;                      // the last product writes u
+  void *q, *o, *z;                 // scratch: [B S][nH Dh] twice, [B S][F], whole 16-row groups
+  void* skvf;                      // own keys and values, [B][ceil(S / 32)] KvBlocks
+  bool own_done;                   // q and skvf hold the QKV product already
+  const void* kvf;                 // earlier keys' blocks (any valid address when P is 0)
+  int64_t kvf_bstride;
+  const int* plen;                 // null: P
+  int P;
+  const float2* rope;
+  int rope_shared;
+  const float *c_qkv, *c_gu;
+  const float *gate_attn, *scale_mlp, *gate_mlp, *scale_next;
+  int n_lead, n_t0;
+  int64_t t0_delta, c_t0;
+  float eps;
+  float* opart;
+  hipEvent_t ev[5][2];             // optional: timestamps, in the order of jpi_kernel_kind
+};
+hipError_t enqueue_small_layer(const SmallLayer& y, hipStream_t s);
 bool small_supported(jpi_dtype dt, int W, int nH, int Dh, int F);
 hipError_t launch_small(SmallEpi epi, const SmallGemm& g, hipStream_t s);
 hipError_t launch_small_head(const SmallHead& a, hipStream_t s);
@@ -179,7 +211,7 @@ struct AttnLaunch {
   const void* skvf;       // launch_flash_rows: own keys, [B][ceil(H / 32)] blocks
   const void* kvf;        // and the prefix's, rollout b at kvf + b * kvf_bstride (elements)
   int64_t kvf_bstride;
-  const int* prefix_len;  // device [B]
+  const int* prefix_len;  // device [B]; launch_flash_rows: null = P for every rollout
   int B, nH, H, P, Dh;
   float* opart;           // [B][nH][n_chunks][H][Dh]
   float* mpart;           // [B][nH][n_chunks][H]

@@ -628,8 +628,8 @@ hipError_t launch_gemm(jpi_dtype dt, const GemmLaunch& g, hipStream_t s) {
     // a K split whose 128 x 128 tiles still leave half of the units idle: 64 x 64 tiles on the pipelined kernel
     // (with the slices' sum, against the register-staged 128 x 128 kernel: M = 150, N = 1024, K = 4096 in 4
     // slices 19.4 -> 9.1 us, in 2 slices 31.1 -> 12.3; M = 400, K = 2048 in 4 slices 14.3 -> 10.0)
-    if (gemm_pipe_enabled() && g.M <= 512 && 2 * tiles(128, 128) <= n_cu && (g.K / g.splitk) % DmaSmall::BK == 0 &&
-        (size_t)g.N * g.K * 2 < (1u << 31))
+    if (gemm_pipe_enabled() && 2 * tiles(128, 128) <= n_cu && (g.K / g.splitk) % DmaSmall::BK == 0 &&
+        (size_t)g.N * g.K * 2 < (1u << 31) && (size_t)g.M * g.K * 2 < (1u << 31))
       return launch_dma<DmaSmall>(g, s);
     // Larger M: 256 x 256 tiles on the direct-to-LDS ring (64-deep slices, double-buffered, sixteen
     // waves) when such tiles alone cover the units (GateUp at M = 3200: 71.5 us on the register-staged

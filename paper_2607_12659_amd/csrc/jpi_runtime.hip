@@ -1026,94 +1026,54 @@ struct SmallRows {
 template <typename Timing>
 hipError_t enqueue_small_layers(jpi_ctx* c, const SmallRows& r, const float* tk, const float* ck, Timing&& time,
                                 hipStream_t s) {
-  const int W = c->W, Dh = c->Dh, nH = c->nH, F = c->F, L = c->L, M = r.B * r.S, HD = nH * Dh;
-  const int N1 = HD + 2 * Dh, N2 = 2 * F;
+  const int W = c->W, Dh = c->Dh, nH = c->nH, L = c->L, N1 = (nH + 2) * Dh, N2 = 2 * c->F;
   const size_t es = c->esz;
-  hipError_t e;
-  SmallGemm base{};
-  base.M = M;
-  base.ssq = base.ssq_out = r.ssq;
-  base.n_ssq = W / 16;
-  base.inv_w = 1.0f / (float)W;
-  base.eps = c->cfg.rms_eps;
-  base.c_t0 = r.c_t0;
-  base.t0_delta = r.t0_delta;
-  base.seq = r.S;
-  base.n_lead = r.n_lead;
-  base.n_t0 = r.n_t0;
-  base.h = r.h;
-  base.h_in = r.h;
-  base.h_ld = W;
   // without shifts (action-time variant) every product reads the same zeros
   const bool at = c->cfg.variant == JPI_VARIANT_ACTION_TIME;
-  const int64_t cl_stride = at ? 0 : N1 + N2, c_gu = at ? 0 : N1;
-  const int split = flash_rows_splits(r.B, nH, r.S, r.P, c->n_cu);
+  const int64_t c_lstride = at ? 0 : N1 + N2, c_gu = at ? 0 : N1;
+  SmallLayer y{};
+  y.B = r.B;
+  y.S = r.S;
+  y.W = W;
+  y.nH = nH;
+  y.Dh = Dh;
+  y.F = c->F;
+  y.n_cu = c->n_cu;
+  y.off_o = c->off_o;
+  y.off_gu = c->off_gu;
+  y.off_d = c->off_d;
+  y.h_in = y.h = r.h;
+  y.ssq = r.ssq;
+  y.u_in = y.u = (bf16*)r.u;
+  y.q = c->q;
+  y.o = c->o;
+  y.z = c->z;
+  y.kvf_bstride = (int64_t)c->NBmax * kv_block_elems(Dh);
+  y.plen = r.plen;
+  y.P = r.P;
+  y.rope = r.rope;
+  y.n_lead = r.n_lead;
+  y.n_t0 = r.n_t0;
+  y.t0_delta = r.t0_delta;
+  y.c_t0 = r.c_t0;
+  y.eps = c->cfg.rms_eps;
+  y.opart = c->opart;
   for (int l = 0; l < L; ++l) {
-    const bf16* lay = (const bf16*)c->w_frag + (size_t)l * c->layer_elems;
     const float* am = tk + (size_t)(2 * l) * 3 * W;
     const float* mm = am + 3 * W;  // after the last layer's MLP rows come the final norm's
-    const float* cl = ck + (size_t)l * cl_stride;
-    char* skvf = (char*)r.skvf + (size_t)l * r.skvf_lstride * es;
-    SmallGemm g = base;
-    g.A = (const bf16*)r.u;
-    g.W = lay;
-    g.N = N1;
-    g.KS = W / 32;
-    g.c = cl;
-    g.ep.q = c->q;
-    g.ep.skvf = skvf;
-    g.ep.rope = r.rope;
-    g.ep.n_heads = nH;
-    g.ep.head_dim = Dh;
-    g.ep.horizon = r.S;
-    time(JPI_KERNEL_QKV, &g.ev_start, &g.ev_stop);
-    if ((e = launch_small(SE_QKV, g, s)) != hipSuccess) return e;
-    AttnLaunch a{};
-    a.q = c->q;
-    a.skvf = skvf;
-    a.kvf_bstride = (int64_t)c->NBmax * kv_block_elems(Dh);
-    a.kvf = (const char*)c->kvf + (size_t)l * c->Bmax * a.kvf_bstride * es;
-    a.prefix_len = r.plen;
-    a.B = r.B;
-    a.nH = nH;
-    a.H = r.S;
-    a.P = r.P;
-    a.Dh = Dh;
-    a.opart = c->opart;
-    a.out = c->o;
-    a.out_frag = 1;
-    a.n_cu = c->n_cu;
-    time(JPI_KERNEL_ATTENTION, &a.ev_start, &a.ev_stop);
-    if ((e = launch_flash_rows(a, split, s)) != hipSuccess) return e;
-    g = base;
-    g.A = (const bf16*)c->o;
-    g.W = lay + c->off_o;
-    g.N = W;
-    g.KS = HD / 32;
-    g.gate = am + 2 * W;
-    g.scale = mm;
-    g.u = (bf16*)r.u;
-    time(JPI_KERNEL_OPROJ, &g.ev_start, &g.ev_stop);
-    if ((e = launch_small(SE_RESID, g, s)) != hipSuccess) return e;
-    g = base;
-    g.A = (const bf16*)r.u;
-    g.W = lay + c->off_gu;
-    g.N = N2;
-    g.KS = W / 32;
-    g.c = cl + c_gu;
-    g.u = (bf16*)c->z;
-    time(JPI_KERNEL_GATEUP, &g.ev_start, &g.ev_stop);
-    if ((e = launch_small(SE_GEGLU, g, s)) != hipSuccess) return e;
-    g = base;
-    g.A = (const bf16*)c->z;
-    g.W = lay + c->off_d;
-    g.N = W;
-    g.KS = F / 32;
-    g.gate = mm + 2 * W;
-    g.scale = mm + 3 * W;
-    g.u = l + 1 < L ? (bf16*)r.u : nullptr;
-    time(JPI_KERNEL_DOWN, &g.ev_start, &g.ev_stop);
-    if ((e = launch_small(SE_RESID, g, s)) != hipSuccess) return e;
+    y.w = (const bf16*)c->w_frag + (size_t)l * c->layer_elems;
+    y.u_out = l + 1 < L;  // the step's head takes h
+    y.skvf = (char*)r.skvf + (size_t)l * r.skvf_lstride * es;
+    y.kvf = (const char*)c->kvf + (size_t)l * c->Bmax * y.kvf_bstride * es;
+    y.c_qkv = ck + (size_t)l * c_lstride;
+    y.c_gu = y.c_qkv + c_gu;
+    y.gate_attn = am + 2 * W;
+    y.scale_mlp = mm;
+    y.gate_mlp = mm + 2 * W;
+    y.scale_next = mm + 3 * W;
+    for (int k = JPI_KERNEL_QKV; k <= JPI_KERNEL_DOWN; ++k) time(k, &y.ev[k][0], &y.ev[k][1]);
+    const hipError_t e = enqueue_small_layer(y, s);
+    if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }

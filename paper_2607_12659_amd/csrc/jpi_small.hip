@@ -92,7 +92,7 @@ __device__ __forceinline__ void pin_args(const SmallGemm& g) {
   asm volatile("" :: "s"(g.h), "s"(g.h_in), "s"(g.h_ld), "s"(g.gate), "s"(g.scale));
   asm volatile("" :: "s"(g.ssq_out), "s"(g.u));
   asm volatile("" :: "s"(g.ep.q), "s"(g.ep.skvf));
-  asm volatile("" :: "s"(g.ep.rope), "s"(g.ep.n_heads), "s"(g.ep.head_dim), "s"(g.ep.horizon));
+  asm volatile("" :: "s"(g.ep.rope), "s"(g.ep.n_heads), "s"(g.ep.head_dim), "s"(g.ep.horizon), "s"(g.ep.rope_shared));
 }
 
 // Tile of 16 MT x 16 NT over the whole contraction; NWV waves each take K
@@ -101,7 +101,7 @@ __device__ __forceinline__ void pin_args(const SmallGemm& g) {
 template <int MT, int NT, int NWV, int KW, SmallEpi EPI, bool T0>
 __global__ __launch_bounds__(64 * NWV) void k_small(SmallGemm g) {
   using MF = Mfma<bf16>;
-  constexpr bool FOLD = EPI == SE_QKV || EPI == SE_GEGLU;
+  constexpr bool FOLD = EPI == SE_QKV || EPI == SE_GEGLU || EPI == SE_F32;
   constexpr int PN = FOLD ? 2 : 1;             // column tiles per epilogue unit (RoPE and gate/up pairs)
   constexpr int UNITS = MT * NT / PN;
   constexpr int WPU = NWV / UNITS >= 4 ? 4 : 1;  // waves that share a unit, one row quad each, or a wave per unit
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(64 * NWV) void k_small(SmallGemm g) {
 #pragma unroll
     for (int j = 0; j < QW; ++j) {
       const int row = min(row0 + j, M - 1), b = row / H, q = row - b * H;
-      rope[j] = __builtin_amdgcn_raw_buffer_load_b64(rr, unit && !is_v ? (u32)(row * half + d) * 8 : NONE, 0, 0);
+      rope[j] = __builtin_amdgcn_raw_buffer_load_b64(rr, unit && !is_v ? (u32)((h.ep.rope_shared ? q : row) * half + d) * 8 : NONE, 0, 0);
       const int kb = (b * nbs + (q >> 5)) * 64 * Dh;  // KvBlock; key q & 31 of it
       dst[j] = is_v       ? kb + 32 * Dh + ((within >> 4) * 64 + ((q & 31) >> 3) * 16 + (within & 15)) * 8 + (q & 7)
                : hn == nH ? kb + ((((q >> 2) & 1) * (Dh >> 5) + (d >> 5)) * 64 + ((d & 31) >> 3) * 16 + 4 * ((q & 31) >> 3) + (q & 3)) * 8 + (d & 7)
@@ -300,6 +300,11 @@ __global__ __launch_bounds__(64 * NWV) void k_small(SmallGemm g) {
       const float cx = is_v ? 1.f : __builtin_bit_cast(float, rc), cy = __builtin_bit_cast(float, rsn);  // v: (0, 0) read
       base[dst[j]] = from_f32<bf16>(lo * cx - hi * cy);
       base[dst[j] + dst2] = from_f32<bf16>(lo * cy + hi * cx);
+    } else if constexpr (EPI == SE_F32) {
+      if (row >= M) continue;
+      const float r = rs[rl0 + j];
+      h.h[(size_t)row * h.N + col0] = fmaf(r, v[j][0], e0[j]);
+      h.h[(size_t)row * h.N + col0 + 16] = fmaf(r, v[j][PN - 1], e1[j]);
     } else if constexpr (EPI == SE_GEGLU) {
       const float r = rs[rl0 + j];
       out[j] = gelu_tanh(fmaf(r, v[j][0], e0[j])) * fmaf(r, v[j][PN - 1], e1[j]);
@@ -316,7 +321,7 @@ __global__ __launch_bounds__(64 * NWV) void k_small(SmallGemm g) {
       out[j] = h2 * (1.0f + e2[j]);
     }
   }
-  if constexpr (EPI != SE_QKV) {
+  if constexpr (EPI != SE_QKV && EPI != SE_F32) {
     if (EPI == SE_RESID && !h.u) return;
     const int KSd = h.N / (32 * PN), t = (n0 + un) / PN;
     if constexpr (WPU == 4) store_frag_quad(h.u, m0 + um, KSd, t, q0, stage[wave], out[0]);
@@ -380,7 +385,7 @@ __global__ __launch_bounds__(S::NT) void k_small_ring(SmallGemm g) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int row = min(m0 + (wm * S::TM + a) * 16 + 4 * (lane >> 4) + i, M - 1);
-          rope[a][b / 2][i] = __builtin_amdgcn_raw_buffer_load_b64(rr, hn <= nH ? (u32)(row * half + d) * 8 : 0x80000000u, 0, 0);
+          rope[a][b / 2][i] = __builtin_amdgcn_raw_buffer_load_b64(rr, hn <= nH ? (u32)((h.ep.rope_shared ? row % h.ep.horizon : row) * half + d) * 8 : 0x80000000u, 0, 0);
         }
     }
   }
@@ -670,6 +675,16 @@ __global__ __launch_bounds__(256) void k_action_embed_frag(const float* __restri
   }
 }
 
+__global__ __launch_bounds__(256) void k_small_rows(const float* __restrict__ h, const float* __restrict__ scale,
+                                                    bf16* __restrict__ u, float* __restrict__ ssq, int W) {
+  const int m = blockIdx.x;
+  for (int k = threadIdx.x; k < W; k += 256) {
+    const float v = h[(size_t)m * W + k], s = group16_sum(v * v);
+    u[(((size_t)(m / 16) * (W / 32) + k / 32) * 64 + ((k % 32) / 8) * 16 + m % 16) * 8 + k % 8] = from_f32<bf16>(v * (1.0f + scale[k]));
+    if (k % 16 == 0) ssq[(size_t)m * (W / 16) + k / 16] = s;
+  }
+}
+
 // h[b] = W_s state[b] + b_s in fp64, its u and sums of squares; one workgroup per 16 columns of a
 // row, 16 threads per column
 __global__ __launch_bounds__(256) void k_small_state(const float* __restrict__ state, const bf16* __restrict__ w,
@@ -709,7 +724,7 @@ hipError_t launch_ring(const SmallGemm& g, hipStream_t s) {
 template <int MT, int NT, int NWV, int KW, SmallEpi EPI>
 hipError_t launch_t(const SmallGemm& g, hipStream_t s) {
   const dim3 grid(g.N / 16 / NT, ((g.M + 15) / 16 + MT - 1) / MT);
-  if constexpr (EPI != SE_SWISH)
+  if constexpr (EPI != SE_SWISH && EPI != SE_F32)
     if (g.n_t0 > 0) {
       JPI_LAUNCH((k_small<MT, NT, NWV, KW, EPI, true>), grid, dim3(64 * NWV), 0, s, g.ev_start, g.ev_stop, g);
       return hipGetLastError();
@@ -743,8 +758,12 @@ hipError_t launch_small(SmallEpi epi, const SmallGemm& g, hipStream_t s) {
       return RG <= 4 ? launch_t<1, 2, 8, 4, SE_QKV>(g, s) : launch_t<2, 4, 8, 4, SE_QKV>(g, s);
     case SE_GEGLU:
       if (!k32) return launch_t<2, 2, 8, 1, SE_GEGLU>(g, s);
+      if (RG == 1) return launch_t<1, 2, 8, 4, SE_GEGLU>(g, s);
       if (RG <= 4) return launch_t<4, 2, 16, 2, SE_GEGLU>(g, s);
       return RG <= 16 ? launch_ring<Ring64, SE_GEGLU>(g, s) : launch_ring<Ring128, SE_GEGLU>(g, s);
+    case SE_F32:
+      if (!k32) return launch_t<2, 2, 8, 1, SE_F32>(g, s);
+      return RG <= 4 ? launch_t<1, 2, 8, 4, SE_F32>(g, s) : launch_t<2, 4, 8, 4, SE_F32>(g, s);
     case SE_SWISH:
       if (!k32) return launch_t<2, 1, 8, 1, SE_SWISH>(g, s);
       return RG <= 4 ? launch_t<1, 1, 8, 4, SE_SWISH>(g, s) : launch_t<2, 1, 8, 4, SE_SWISH>(g, s);
@@ -765,10 +784,104 @@ hipError_t launch_small(SmallEpi epi, const SmallGemm& g, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+hipError_t enqueue_small_layer(const SmallLayer& y, hipStream_t s) {
+  const int HD = y.nH * y.Dh;
+  hipError_t e;
+  SmallGemm base{};
+  base.M = y.B * y.S;
+  base.ssq = base.ssq_out = y.ssq;
+  base.n_ssq = y.W / 16;
+  base.inv_w = 1.0f / (float)y.W;
+  base.eps = y.eps;
+  base.c_t0 = y.c_t0;
+  base.t0_delta = y.t0_delta;
+  base.seq = y.S;
+  base.n_lead = y.n_lead;
+  base.n_t0 = y.n_t0;
+  base.h = y.h;
+  base.h_ld = y.W;
+  auto timed = [&](SmallGemm& g, int kind) {
+    g.ev_start = y.ev[kind][0];
+    g.ev_stop = y.ev[kind][1];
+  };
+  SmallGemm g = base;
+  if (!y.own_done) {
+    g.A = y.u_in;
+    g.W = y.w;
+    g.N = HD + 2 * y.Dh;
+    g.KS = y.W / 32;
+    g.c = y.c_qkv;
+    g.ep.q = y.q;
+    g.ep.skvf = y.skvf;
+    g.ep.rope = y.rope;
+    g.ep.rope_shared = y.rope_shared;
+    g.ep.n_heads = y.nH;
+    g.ep.head_dim = y.Dh;
+    g.ep.horizon = y.S;
+    timed(g, JPI_KERNEL_QKV);
+    if ((e = launch_small(SE_QKV, g, s)) != hipSuccess) return e;
+  }
+  AttnLaunch a{};
+  a.q = y.q;
+  a.skvf = y.skvf;
+  a.kvf = y.kvf;
+  a.kvf_bstride = y.kvf_bstride;
+  a.prefix_len = y.plen;
+  a.B = y.B;
+  a.nH = y.nH;
+  a.H = y.S;
+  a.P = y.P;
+  a.Dh = y.Dh;
+  a.opart = y.opart;
+  a.out = y.o;
+  a.out_frag = 1;
+  a.n_cu = y.n_cu;
+  a.ev_start = y.ev[JPI_KERNEL_ATTENTION][0];
+  a.ev_stop = y.ev[JPI_KERNEL_ATTENTION][1];
+  if ((e = launch_flash_rows(a, flash_rows_splits(y.B, y.nH, y.S, y.P, y.n_cu), s)) != hipSuccess) return e;
+  g = base;
+  g.A = (const bf16*)y.o;
+  g.W = y.w + y.off_o;
+  g.N = y.W;
+  g.KS = HD / 32;
+  g.h_in = y.h_in;
+  g.gate = y.gate_attn;
+  g.scale = y.scale_mlp;
+  g.u = y.u;
+  timed(g, JPI_KERNEL_OPROJ);
+  if ((e = launch_small(SE_RESID, g, s)) != hipSuccess) return e;
+  g = base;
+  g.A = y.u;
+  g.W = y.w + y.off_gu;
+  g.N = 2 * y.F;
+  g.KS = y.W / 32;
+  g.c = y.c_gu;
+  g.u = (bf16*)y.z;
+  timed(g, JPI_KERNEL_GATEUP);
+  if ((e = launch_small(SE_GEGLU, g, s)) != hipSuccess) return e;
+  g = base;
+  g.A = (const bf16*)y.z;
+  g.W = y.w + y.off_d;
+  g.N = y.W;
+  g.KS = y.F / 32;
+  g.h_in = y.h;
+  g.gate = y.gate_mlp;
+  g.scale = y.scale_next;
+  g.u = y.u_out ? y.u : nullptr;
+  timed(g, JPI_KERNEL_DOWN);
+  return launch_small(SE_RESID, g, s);
+}
+
 hipError_t launch_small_head(const SmallHead& a, hipStream_t s) {
   if (a.M < 1 || a.W > 2048 || a.W % 32 != 0 || a.A < 1 || a.A > 64 || a.seq <= a.n_lead) return hipErrorInvalidValue;
   if (a.W <= 1024) hipLaunchKernelGGL(k_small_head<1>, dim3(a.M), dim3(256), 0, s, a);
   else hipLaunchKernelGGL(k_small_head<2>, dim3(a.M), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_rows(const float* h, const float* scale, int M, int W, void* u, float* ssq, hipStream_t s) {
+  if (M < 1 || W % 256 != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_small_rows, dim3(M), dim3(256), 0, s, h, scale, (bf16*)u, ssq, W);
   return hipGetLastError();
 }
 

@@ -119,3 +119,32 @@ def test_bind_prefix_copies(dtype, Dh, B, P, Pmax):
             assert np.array_equal(host(kp, 2, B + 1, Pmax, Dh)[:, :B, :P], K)
     finally:
         ae.close()
+
+
+# action rows 1, 75, 200 and 513 (past the five-launch layers); one token, a block's edge, several blocks
+@pytest.mark.parametrize("batch,n_actions,tokens", [(1, 1, 1), (3, 25, 33), (8, 25, 64), (2, 10, 130), (27, 19, 5)])
+def test_correction_rows_match_oracle(batch, n_actions, tokens):
+    torch = torch_cuda()
+    import synth.correction as sc
+    from gpu_util import Corr
+    from paper_2607_12659_amd.expert import to_device
+    wl = sc.CORR_WORKLOADS["corr40m-p816"].with_(batch=batch, n_actions=n_actions, vlm_tokens=tokens)
+    w = sc.make_corr_weights(wl)
+    x, acts = sc.make_vlm_state(wl), sc.make_actions(wl)
+    m = Corr(wl.dims, w, batch, n_actions, tokens + 7)
+    try:
+        print("case", batch, n_actions, tokens, flush=True)
+        c = m.compress(to_device(x), batch, tokens)
+        item, conf = m.predict(c, to_device(np.ascontiguousarray(acts, np.float32)), batch, n_actions)
+        torch.cuda.synchronize()
+        c, item = c.cpu().numpy().astype(np.float64), item.cpu().numpy().astype(np.float64)
+        for b in sorted({0, batch // 2, batch - 1}):  # the oracle takes half a second a rollout
+            c_o = oracle.correction.compress(wl.dims, w, x[b])
+            i_o, f_o = oracle.correction.correct(wl.dims, w, c_o, acts[b])
+            # measured on the eight-launch blocks: 7e-4 and 3.6e-3
+            assert_bf16(c[b:b + 1], c_o[None], "state %d" % b, reg_rel=3e-3)
+            assert_bf16(item[b:b + 1], i_o[None], "item %d" % b, reg_rel=1.5e-2)
+            # each term of the confidence's dot product within the bf16 bar of the item
+            assert abs(float(conf[b]) - f_o) <= 2e-2 * np.abs(oracle.widen(w["conf_head.w"])[0]).sum()
+    finally:
+        m.close()
