@@ -163,6 +163,32 @@ __device__ __forceinline__ void epilogue_qkv_pre(const EpiParams& ep, int M, int
   }
 }
 
+// V columns (natural order, stored transposed) of four consecutive rows, a lane's share of a result pair:
+// where they are four tokens of one rollout at a place that allows it, as 8- or 4-byte stores.  A
+// 2-byte store per row touches 16 V^T rows per instruction.  False if the columns are not V's or the
+// rows do not fit: nothing is stored then.
+__device__ __forceinline__ bool epilogue_v4(const EpiParams& ep, int M, int N, int row, int col_lo, f32x4 lo, f32x4 hi) {
+  const int within = col_lo - (ep.n_heads + 1) * ep.head_dim, H = ep.horizon;
+  if (within < 0 || col_lo >= N || row + 3 >= M) return false;
+  const int b = row / H, i = row - b * H;
+  if (i + 3 >= H || ((i | ep.vst_ld) & 1)) return false;
+  typedef bf16 b4 __attribute__((ext_vector_type(4)));
+  typedef bf16 b2 __attribute__((ext_vector_type(2)));
+  bf16* p = reinterpret_cast<bf16*>(ep.vst) + ((size_t)b * ep.head_dim + within) * ep.vst_ld + i;
+  bf16* q = p + (size_t)16 * ep.vst_ld;
+  const b4 x = b4{(bf16)lo[0], (bf16)lo[1], (bf16)lo[2], (bf16)lo[3]}, y = b4{(bf16)hi[0], (bf16)hi[1], (bf16)hi[2], (bf16)hi[3]};
+  if (((i | ep.vst_ld) & 3) == 0) {
+    *reinterpret_cast<b4*>(p) = x;
+    *reinterpret_cast<b4*>(q) = y;
+  } else {
+    *reinterpret_cast<b2*>(p) = b2{x[0], x[1]};
+    *reinterpret_cast<b2*>(p + 2) = b2{x[2], x[3]};
+    *reinterpret_cast<b2*>(q) = b2{y[0], y[1]};
+    *reinterpret_cast<b2*>(q + 2) = b2{y[2], y[3]};
+  }
+  return true;
+}
+
 // s_waitcnt with vmcnt = N and the other counters not waited for
 template <int N>
 __device__ __forceinline__ void wait_vm() {

@@ -11,8 +11,7 @@
 // products of this one.  A running (max, sum) per row gives the online
 // softmax.
 // With one key range the workgroup writes the normalised output; with several
-// it writes a bf16 partial normalised by its own sum plus (max, sum), merged
-// by k_flash_merge.
+// it writes a bf16 partial normalised by its own sum plus (max, sum), merged by k_flash_merge.
 //
 // Products use v_mfma_f32_16x16x32_bf16 with the operands swapped:
 // S^T = K q^T puts one query row in each lane (lane % 16) and four keys of a
@@ -36,6 +35,7 @@ namespace jpi {
 typedef unsigned int u32;
 typedef u32 u32x4 __attribute__((ext_vector_type(4)));
 typedef u32 u32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 
 template <int DH>
 struct Flash {
@@ -427,57 +427,89 @@ __global__ __launch_bounds__(512) void k_flash(AttnLaunch a, int S, int nqt, int
   }
 }
 
-// out row (b, head, i) = sum_s 2^(m_s - m) l_s O_s / sum_s 2^(m_s - m) l_s,
-// splits in order; a split without keys (m_s = -inf) is skipped.
-// Dh / 4 threads per query row, 4 dims each.
-template <int DH, typename TO>
-__global__ __launch_bounds__(256) void k_flash_merge(AttnLaunch a, int S, const void* part, const float2* ml) {
+// address of columns col .. col + 3 (col a multiple of 4) of a row of the attention output
+__device__ __forceinline__ size_t attn_out_at(const AttnLaunch& a, int DH, int m, int col) {
+  const int C = a.nH * DH;
+  if (!a.out_frag) return (size_t)m * C + col;
+  return (((size_t)(m >> 4) * (C / 32) + (col >> 5)) * 64 + ((col & 31) >> 3) * 16 + (m & 15)) * 8 + (col & 7);
+}
+
+// out row (b, head, i) = sum_s 2^(m_s - m) l_s O_s / sum_s 2^(m_s - m) l_s, ranges in order; a
+// range without keys (m_s = -inf) is skipped.  Dh / 4 threads per query row, 4 dims each.  S is
+// known when compiling, so that the loads of a row's partials are one round trip
+// (16 predicated ones took 7 us at three rollouts whatever S was).
+template <int DH, int S, typename TO>
+__global__ __launch_bounds__(256) void k_flash_merge(AttnLaunch a, const bf16* part, const float2* ml) {
   constexpr int TPR = DH / 4, RPB = 256 / TPR;
   const int R = a.nH * a.H;
   const int t = threadIdx.x, rr = blockIdx.x * RPB + t / TPR, q4 = t % TPR;
   if (rr >= a.B * R) return;
   const int b = rr / R, r = rr - b * R;
   const int hn = r / a.H, i = r - hn * a.H;
-  float2 mv[FLASH_MAX_SPLITS];
-  u32x2 ov[FLASH_MAX_SPLITS];
+  float2 mv[S];
+  u32x2 ov[S];
   float m = -INFINITY;
 #pragma unroll
-  for (int s = 0; s < FLASH_MAX_SPLITS; ++s) {
-    if (s < S) {
-      const size_t rowi = ((size_t)s * a.B + b) * R + r;
-      mv[s] = ml[rowi];
-      ov[s] = *reinterpret_cast<const u32x2*>(reinterpret_cast<const bf16*>(part) + rowi * DH + 4 * q4);
-      m = fmaxf(m, mv[s].x);
-    }
+  for (int s = 0; s < S; ++s) {
+    const size_t rowi = ((size_t)s * a.B + b) * R + r;
+    mv[s] = ml[rowi];
+    ov[s] = *reinterpret_cast<const u32x2*>(part + rowi * DH + 4 * q4);
   }
+#pragma unroll
+  for (int s = 0; s < S; ++s) m = fmaxf(m, mv[s].x);
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
   float lsum = 0.f;
 #pragma unroll
-  for (int s = 0; s < FLASH_MAX_SPLITS; ++s) {
-    if (s < S && mv[s].x != -INFINITY) {
-      const float wl = exp2f(mv[s].x - m) * mv[s].y;
-      const f32x4 v = f32x4{__builtin_bit_cast(float, ov[s][0] << 16), __builtin_bit_cast(float, ov[s][0] & 0xffff0000u),
-                            __builtin_bit_cast(float, ov[s][1] << 16), __builtin_bit_cast(float, ov[s][1] & 0xffff0000u)};
-      acc += wl * v;
-      lsum += wl;
-    }
+  for (int s = 0; s < S; ++s) {
+    const bool some = mv[s].x != -INFINITY;
+    const float wl = some ? __builtin_amdgcn_exp2f(mv[s].x - m) * mv[s].y : 0.f;
+    const f32x4 v = f32x4{__builtin_bit_cast(float, ov[s][0] << 16), __builtin_bit_cast(float, ov[s][0] & 0xffff0000u),
+                          __builtin_bit_cast(float, ov[s][1] << 16), __builtin_bit_cast(float, ov[s][1] & 0xffff0000u)};
+    if (some) acc += wl * v;  // the partial of a range without keys is not written
+    lsum += wl;
   }
   acc *= 1.0f / lsum;
-  TO* out = reinterpret_cast<TO*>(a.out) + ((size_t)b * a.H + i) * (size_t)a.nH * DH + (size_t)hn * DH + 4 * q4;
+  TO* out = reinterpret_cast<TO*>(a.out) + attn_out_at(a, DH, b * a.H + i, hn * DH + 4 * q4);
 #pragma unroll
   for (int e = 0; e < 4; ++e) out[e] = from_f32<TO>(acc[e]);
 }
 
-// Key ranges per (rollout, 128-row tile): enough workgroups to cover the
-// chip once, at least two key blocks per range.
+template <int DH, typename TO>
+static hipError_t launch_merge(const AttnLaunch& a, int S, const bf16* part, const float2* ml, hipStream_t s) {
+  constexpr int RPB = 256 / (DH / 4);
+  const size_t rows = (size_t)a.B * a.nH * a.H;
+  const dim3 grid((unsigned)((rows + RPB - 1) / RPB));
+#define MERGE(N) \
+  case N: JPI_LAUNCH((k_flash_merge<DH, N, TO>), grid, dim3(256), 0, s, (hipEvent_t) nullptr, a.ev_stop, a, part, ml); break;
+  switch (S) {
+    MERGE(2) MERGE(3) MERGE(4) MERGE(5) MERGE(6) MERGE(7) MERGE(8) MERGE(9) MERGE(10) MERGE(11) MERGE(12) MERGE(13)
+    MERGE(14) MERGE(15) MERGE(16)
+    default: return hipErrorInvalidValue;
+  }
+#undef MERGE
+  return hipGetLastError();
+}
+
+// Key ranges per (rollout, 128-row tile), one workgroup per compute unit at a time: the count that
+// makes rounds x (fixed + blocks per range) least, where a workgroup's start, first load and stores take about
+// as long as six 32-key blocks and several ranges cost a merge (three more).  A count just past a whole round was the
+// costly case of "enough workgroups to cover the chip once": the 816-token prefill's 51 tiles at 6 ranges are 306
+// workgroups in two rounds, at 5 ranges 255 in one.
 int flash_splits(int B, int nH, int H, int P, int n_cu) {
   const int KB = 32;
   const int nqt = (nH * H + 127) / 128;
   const int nb = (H + KB - 1) / KB + (P + KB - 1) / KB;
-  int s = (n_cu + B * nqt - 1) / (B * nqt);
-  s = s < nb / 2 ? s : nb / 2;
-  s = s < FLASH_MAX_SPLITS ? s : FLASH_MAX_SPLITS;
-  return s > 1 ? s : 1;
+  int best = 1;
+  long best_cost = -1;
+  for (int s = 1; s <= FLASH_MAX_SPLITS && (s == 1 || s <= nb / 2); ++s) {
+    const long rounds = ((long)B * nqt * s + n_cu - 1) / n_cu;
+    const long cost = rounds * (6 + (nb + s - 1) / s) + (s > 1 ? 3 : 0);
+    if (best_cost < 0 || cost < best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 template <int DH>
@@ -500,13 +532,7 @@ static hipError_t launch_flash_t(const AttnLaunch& a, int S, hipStream_t s) {
                S == 1 ? a.ev_stop : (hipEvent_t) nullptr, a, S, nqt, qrows, part, ml);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || S == 1) return e;
-  constexpr int RPB = 256 / (DH / 4);
-  const dim3 grid((unsigned)((rows + RPB - 1) / RPB));
-  if (a.out_f32)
-    JPI_LAUNCH((k_flash_merge<DH, float>), grid, dim3(256), 0, s, (hipEvent_t) nullptr, a.ev_stop, a, S, part, ml);
-  else
-    JPI_LAUNCH((k_flash_merge<DH, bf16>), grid, dim3(256), 0, s, (hipEvent_t) nullptr, a.ev_stop, a, S, part, ml);
-  return hipGetLastError();
+  return a.out_f32 ? launch_merge<DH, float>(a, S, (const bf16*)part, ml, s) : launch_merge<DH, bf16>(a, S, (const bf16*)part, ml, s);
 }
 
 size_t flash_scratch_bytes(int B, int nH, int H, int Dh, int S) {
@@ -536,14 +562,6 @@ hipError_t launch_flash(const AttnLaunch& a, int S, hipStream_t s) {
 // from the XCD's L2, so this pays while B * (rows / 16) * keys stays small; from
 // there k_flash, which shares each block between 112 rows, reads less.
 // ---------------------------------------------------------------------------
-typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
-
-// address of columns col .. col + 3 (col a multiple of 4) of a row of the attention output
-__device__ __forceinline__ size_t attn_out_at(const AttnLaunch& a, int DH, int m, int col) {
-  const int C = a.nH * DH;
-  if (!a.out_frag) return (size_t)m * C + col;
-  return (((size_t)(m >> 4) * (C / 32) + (col >> 5)) * 64 + ((col & 31) >> 3) * 16 + (m & 15)) * 8 + (col & 7);
-}
 
 constexpr int ROWS_NW = 4;  // waves of k_flash_rows
 
@@ -691,45 +709,6 @@ __global__ __launch_bounds__(64 * ROWS_NW, 2) void k_flash_rows(AttnLaunch a, in
   }
 }
 
-// Merge of S key ranges, as k_flash_merge, with S known when compiling: the
-// loads of a row's partials are one round trip (16 predicated ones took 7 us
-// at three rollouts whatever S was).
-template <int DH, int S, typename TO>
-__global__ __launch_bounds__(256) void k_flash_rows_merge(AttnLaunch a, const bf16* part, const float2* ml) {
-  constexpr int TPR = DH / 4, RPB = 256 / TPR;
-  const int R = a.nH * a.H;
-  const int t = threadIdx.x, rr = blockIdx.x * RPB + t / TPR, q4 = t % TPR;
-  if (rr >= a.B * R) return;
-  const int b = rr / R, r = rr - b * R;
-  const int hn = r / a.H, i = r - hn * a.H;
-  float2 mv[S];
-  u32x2 ov[S];
-  float m = -INFINITY;
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const size_t rowi = ((size_t)s * a.B + b) * R + r;
-    mv[s] = ml[rowi];
-    ov[s] = *reinterpret_cast<const u32x2*>(part + rowi * DH + 4 * q4);
-  }
-#pragma unroll
-  for (int s = 0; s < S; ++s) m = fmaxf(m, mv[s].x);
-  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-  float lsum = 0.f;
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const bool some = mv[s].x != -INFINITY;
-    const float wl = some ? __builtin_amdgcn_exp2f(mv[s].x - m) * mv[s].y : 0.f;
-    const f32x4 v = f32x4{__builtin_bit_cast(float, ov[s][0] << 16), __builtin_bit_cast(float, ov[s][0] & 0xffff0000u),
-                          __builtin_bit_cast(float, ov[s][1] << 16), __builtin_bit_cast(float, ov[s][1] & 0xffff0000u)};
-    if (some) acc += wl * v;  // the partial of a range without keys is not written
-    lsum += wl;
-  }
-  acc *= 1.0f / lsum;
-  TO* out = reinterpret_cast<TO*>(a.out) + attn_out_at(a, DH, b * a.H + i, hn * DH + 4 * q4);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) out[e] = from_f32<TO>(acc[e]);
-}
-
 // Key ranges per 16-row tile: workgroups for the whole chip, at least one 32-key block per wave
 int flash_rows_splits(int B, int nH, int H, int P, int n_cu) {
   const int ntile = (nH * H + 15) / 16, nb = (H + 31) / 32 + (P + 31) / 32;
@@ -748,12 +727,7 @@ static hipError_t launch_flash_rows_t(const AttnLaunch& a, int S, hipStream_t s)
              S == 1 ? a.ev_stop : (hipEvent_t) nullptr, a, S, ntile, part, ml);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || S == 1) return e;
-  constexpr int RPB = 256 / (DH / 4);
-  const dim3 grid((unsigned)((rows + RPB - 1) / RPB));
-  if (S == 2) JPI_LAUNCH((k_flash_rows_merge<DH, 2, TO>), grid, dim3(256), 0, s, (hipEvent_t) nullptr, a.ev_stop, a, part, ml);
-  else if (S == 4) JPI_LAUNCH((k_flash_rows_merge<DH, 4, TO>), grid, dim3(256), 0, s, (hipEvent_t) nullptr, a.ev_stop, a, part, ml);
-  else JPI_LAUNCH((k_flash_rows_merge<DH, 8, TO>), grid, dim3(256), 0, s, (hipEvent_t) nullptr, a.ev_stop, a, part, ml);
-  return hipGetLastError();
+  return launch_merge<DH, TO>(a, S, part, ml, s);
 }
 
 hipError_t launch_flash_rows(const AttnLaunch& a, int S, hipStream_t s) {

@@ -414,6 +414,9 @@ __global__ __launch_bounds__(S::NT) void k_gemm_dma(GemmLaunch g) {
     for (int b = 0; b < S::TN; b += 2)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
+        if constexpr (EPI == EPI_QKV) {
+          if (i == 0 && epilogue_v4(g.ep, M, N, rbase + a * 16, cbase + b * 16, acc[a][b], acc[a][b + 1])) break;
+        }
         if constexpr (PRE)
           epilogue_qkv_pre<bf16>(g.ep, M, N, rbase + a * 16 + i, cbase + b * 16, acc[a][b][i], acc[a][b + 1][i],
                                  rope[a][b / 2][i]);
@@ -429,6 +432,8 @@ __global__ __launch_bounds__(S::NT) void k_gemm_dma(GemmLaunch g) {
 typedef DmaShape<128, 128, 8, 64> DmaMid;          // one slice: 32 KB; ring 128 KB; waves 2 x 4 of 64 x 32
 typedef DmaShape<64, 64, 8, 64, 4, 4> DmaSmall;    // one slice: 16 KB; ring 64 KB (two workgroups per unit);
                                                    // waves 4 x 2 of 16 x 32
+typedef DmaShape<128, 64, 8, 64, 3, 4> DmaTall;    // one slice: 24 KB; ring 72 KB (two workgroups per unit);
+                                                   // waves 4 x 2 of 32 x 32
 typedef DmaShape<128, 256, 16, 64, 3, 4> DmaWide;  // one slice: 48 KB; ring 144 KB; waves 4 x 4 of 32 x 64
                                                   // (batch 64 48.62 -> 45.89 ms against eight waves on
                                                   // four 32-deep slices)
@@ -709,24 +714,41 @@ hipError_t launch_gemm(jpi_dtype dt, const GemmLaunch& g, hipStream_t s) {
     if (gemm_pipe_enabled() && 2 * tiles(128, 128) <= n_cu && (g.K / g.splitk) % DmaSmall::BK == 0 &&
         (size_t)g.N * g.K * 2 < (1u << 31) && (size_t)g.M * g.K * 2 < (1u << 31))
       return launch_dma<DmaSmall>(g, s);
-    // Larger M: 256 x 256 tiles on the direct-to-LDS ring (64-deep slices, double-buffered, sixteen
-    // waves) when such tiles alone cover the units (GateUp at M = 3200: 71.5 us on the register-staged
-    // k_gemm_big, 68.1 us on the first, eight-wave version of this ring), else one round of 128 x 256 ring
-    // tiles (two 64-deep slices in flight, sixteen waves) when they fill at least three quarters of the
-    // units (M = 3200, first eight-wave version: QKV 39.6 -> 38.1, split-K O-proj 29.0 -> 25.6 and Down
-    // 48.6 -> 42.8 us against two register-staged 128 x 128 workgroups per unit; register-staged 128 x 256
-    // tiles were slower than both)
+    // Otherwise the ring tile with the least estimated time: turns of tiles over the units, each a start and
+    // the time of its 64-deep slices, plus what its epilogue adds.  Fitted (us) to every tile on one MI355X at M = 550 .. 3200
+    // over the expert's and the VLM's products; within 15 % of the fastest tile on all of them.  Against the
+    // rule it replaces (256 x 256 when they fill the units, one full round of 128 x 256, else register-staged
+    // 128 x 128): gate/up M = 1126 37.2 -> 26.6, M = 1689 42.6 -> 28.9; Down in 4 slices M = 550 17.7 -> 12.5, M = 1126
+    // 22.4 -> 16.6; VLM QKV M = 1689 48.4 -> 39.3, M = 816 25.2 -> 22.1.
     const bool fits = (size_t)g.N * g.K * 2 < (1u << 31) && (size_t)g.M * g.K * 2 < (1u << 31);
-    auto kfits = [&](int bk) { return (g.K / g.splitk) % bk == 0; };
-    if (fits && kfits(DmaBig::BK) && tiles(256, 256) >= n_cu) return launch_dma<DmaBig>(g, s);
+    if (gemm_pipe_enabled() && fits) {
+      struct Ring {
+        int bm, bn, per_cu;     // tile, workgroups per unit
+        float start, slice;     // us of a round, of one slice of a tile
+        float qkv;              // what a QKV epilogue adds
+        hipError_t (*launch)(const GemmLaunch&, hipStream_t);
+      };
+      static const Ring rings[] = {{256, 256, 1, 8.0f, 1.18f, 20.f, launch_dma<DmaBig>},
+                                   {128, 256, 1, 5.3f, 0.66f, 11.f, launch_dma<DmaWide>},
+                                   {128, 128, 1, 4.5f, 0.47f, 7.f, launch_dma<DmaMid>},
+                                   {128, 64, 2, 4.0f, 0.29f, 4.f, launch_dma<DmaTall>},
+                                   {64, 64, 2, 3.7f, 0.27f, 3.5f, launch_dma<DmaSmall>}};
+      const float slices = (float)(g.K / g.splitk / 64);
+      const Ring* best = nullptr;
+      float best_t = 0.f;
+      for (const Ring& r : rings) {
+        const int t = tiles(r.bm, r.bn), turns = (t + n_cu - 1) / n_cu;
+        const int rounds = (t + n_cu * r.per_cu - 1) / (n_cu * r.per_cu);
+        const float us = turns * slices * r.slice + rounds * (r.start + (g.epi == EPI_QKV ? r.qkv : 0.f));
+        if (!best || us < best_t) {
+          best = &r;
+          best_t = us;
+        }
+      }
+      return best->launch(g, s);
+    }
     if (tiles(256, 256) >= n_cu) return launch_big<Big256>(g, s);
-    if (fits && kfits(DmaWide::BK) && tiles(128, 256) <= n_cu && 4 * tiles(128, 256) >= 3 * n_cu)
-      return launch_dma<DmaWide>(g, s);
     if (tiles(128, 128) >= n_cu || g.epi == EPI_STORE_F32) return launch_gemm_t<bf16, 128, 128>(g, s);
-    // fewer 128 x 128 tiles than units, no K split, yet enough 64 x 64 tiles to fill them (VLM QKV at
-    // M = 816, N = 2560: 520 tiles): the ring at two workgroups per unit (prefill 5.52 -> 5.38 ms)
-    if (gemm_pipe_enabled() && fits && g.splitk == 1 && kfits(DmaSmall::BK) && tiles(64, 64) >= n_cu)
-      return launch_dma<DmaSmall>(g, s);
     if (tiles(128, 64) >= n_cu) return launch_gemm_t<bf16, 128, 64>(g, s);
     return launch_gemm_t<bf16, 64, 64>(g, s);
   }
