@@ -130,63 +130,77 @@ __device__ __forceinline__ float gelu_tanh(float z) {
 __device__ __forceinline__ float2 qkv_rope_factor(const EpiParams& ep, int M, int N, int row, int col_lo) {
   const int Dh = ep.head_dim, qcols = ep.n_heads * Dh;
   if (row >= M || col_lo >= N || col_lo >= qcols + Dh) return float2{1.f, 0.f};
-  const int hn = col_lo < qcols ? col_lo / Dh : -1;
-  const int within = col_lo < qcols ? col_lo - hn * Dh : col_lo - qcols;
+  const int within = col_lo & (Dh - 1);  // Dh is a power of two
   const int d = (within >> 5) * 16 + (within & 15);
   return ep.rope[(size_t)row * (Dh >> 1) + d];  // row = b * H + i
 }
 
-// EPI_QKV epilogue with the rotation factors already in hand
-template <typename T>
-__device__ __forceinline__ void epilogue_qkv_pre(const EpiParams& ep, int M, int N, int row, int col_lo, float lo,
-                                                 float hi, float2 cs) {
-  if (row >= M || col_lo >= N) return;
-  const int Dh = ep.head_dim, half = Dh >> 1, H = ep.horizon;
-  const int b = row / H, i = row - b * H;
-  const int qcols = ep.n_heads * Dh;
-  if (col_lo < qcols + Dh) {
-    const int hn = col_lo < qcols ? col_lo / Dh : -1;
-    const int within = col_lo < qcols ? col_lo - hn * Dh : col_lo - qcols;
-    const int d = (within >> 5) * 16 + (within & 15);
-    const float r_lo = lo * cs.x - hi * cs.y;
-    const float r_hi = lo * cs.y + hi * cs.x;
-    const size_t kbs = ep.ks_bstride ? (size_t)ep.ks_bstride : (size_t)H * Dh;
-    T* dst = hn >= 0 ? reinterpret_cast<T*>(ep.q) + (((size_t)b * ep.n_heads + hn) * H + i) * Dh
-                     : reinterpret_cast<T*>(ep.ks) + b * kbs + (size_t)i * Dh;
-    dst[d] = from_f32<T>(r_lo);
-    dst[d + half] = from_f32<T>(r_hi);
-  } else {
-    const int within = col_lo - qcols - Dh;
-    T* dst = reinterpret_cast<T*>(ep.vst) + (size_t)b * Dh * ep.vst_ld + i;
-    dst[(size_t)within * ep.vst_ld] = from_f32<T>(lo);
-    dst[(size_t)(within + 16) * ep.vst_ld] = from_f32<T>(hi);
+// Rollouts and rows in them of a lane's four result rows row0 .. row0 + 3, taken once per row tile: with the
+// divisions by the horizon and the head size taken per element, the epilogue cost more than the product
+// (QKV at M = 3200, N = 2560, K = 1024: 31.3 us with it, 17 without; 25.4 as it is).
+struct QkvRows {
+  unsigned b[4], i[4];
+};
+__device__ __forceinline__ QkvRows qkv_rows(const EpiParams& ep, int row0) {
+  QkvRows r;
+  const unsigned H = ep.horizon;
+  unsigned b = (unsigned)row0 / H, i = (unsigned)row0 - b * H;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    r.b[e] = b;
+    r.i[e] = i++;
+    if (i == H) i = 0, ++b;
   }
+  return r;
 }
 
-// V columns (natural order, stored transposed) of four consecutive rows, a lane's share of a result pair:
-// where they are four tokens of one rollout at a place that allows it, as 8- or 4-byte stores.  A
-// 2-byte store per row touches 16 V^T rows per instruction.  False if the columns are not V's or the
-// rows do not fit: nothing is stored then.
-__device__ __forceinline__ bool epilogue_v4(const EpiParams& ep, int M, int N, int row, int col_lo, f32x4 lo, f32x4 hi) {
-  const int within = col_lo - (ep.n_heads + 1) * ep.head_dim, H = ep.horizon;
-  if (within < 0 || col_lo >= N || row + 3 >= M) return false;
-  const int b = row / H, i = row - b * H;
-  if (i + 3 >= H || ((i | ep.vst_ld) & 1)) return false;
+// EPI_QKV epilogue of a result pair tile (columns col_lo and col_lo + 16 of rows row0 ..) with the rotation
+// factors in hand.  A 16-column tile lies in one q head, in k or in v.  V is stored transposed: four
+// consecutive tokens of a rollout leave as 8- or 4-byte stores where their place allows it.
+__device__ __forceinline__ void epilogue_qkv_tile(const EpiParams& ep, const QkvRows& r, int M, int N, int row0, int col_lo,
+                                                  f32x4 lo, f32x4 hi, const float2 (&cs)[4]) {
+  if (col_lo >= N) return;
+  const int Dh = ep.head_dim, half = Dh >> 1, H = ep.horizon;
+  const int hn = __builtin_amdgcn_readfirstlane(col_lo >> (31 - __builtin_clz(Dh))), within = col_lo & (Dh - 1);
+  if (hn <= ep.n_heads) {
+    const int d = (within >> 5) * 16 + (within & 15);
+    const bool is_k = hn == ep.n_heads;
+    bf16* base = is_k ? reinterpret_cast<bf16*>(ep.ks) + d
+                      : reinterpret_cast<bf16*>(ep.q) + (size_t)hn * (size_t)(H * Dh) + d;
+    const size_t bs = is_k && ep.ks_bstride ? (size_t)ep.ks_bstride : (size_t)(is_k ? 1 : ep.n_heads) * (size_t)(H * Dh);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (row0 + e >= M) continue;
+      bf16* p = base + r.b[e] * bs + r.i[e] * (size_t)Dh;
+      p[0] = from_f32<bf16>(lo[e] * cs[e].x - hi[e] * cs[e].y);
+      p[half] = from_f32<bf16>(lo[e] * cs[e].y + hi[e] * cs[e].x);
+    }
+    return;
+  }
   typedef bf16 b4 __attribute__((ext_vector_type(4)));
   typedef bf16 b2 __attribute__((ext_vector_type(2)));
-  bf16* p = reinterpret_cast<bf16*>(ep.vst) + ((size_t)b * ep.head_dim + within) * ep.vst_ld + i;
-  bf16* q = p + (size_t)16 * ep.vst_ld;
   const b4 x = b4{(bf16)lo[0], (bf16)lo[1], (bf16)lo[2], (bf16)lo[3]}, y = b4{(bf16)hi[0], (bf16)hi[1], (bf16)hi[2], (bf16)hi[3]};
-  if (((i | ep.vst_ld) & 3) == 0) {
-    *reinterpret_cast<b4*>(p) = x;
-    *reinterpret_cast<b4*>(q) = y;
-  } else {
-    *reinterpret_cast<b2*>(p) = b2{x[0], x[1]};
-    *reinterpret_cast<b2*>(p + 2) = b2{x[2], x[3]};
-    *reinterpret_cast<b2*>(q) = b2{y[0], y[1]};
-    *reinterpret_cast<b2*>(q + 2) = b2{y[2], y[3]};
+  bf16* p = reinterpret_cast<bf16*>(ep.vst) + ((size_t)r.b[0] * Dh + within) * ep.vst_ld + r.i[0];
+  bf16* q = p + (size_t)16 * ep.vst_ld;
+  if (row0 + 3 < M && r.i[0] + 3 < (unsigned)H && ((r.i[0] | ep.vst_ld) & 1) == 0) {
+    if (((r.i[0] | ep.vst_ld) & 3) == 0) {
+      *reinterpret_cast<b4*>(p) = x;
+      *reinterpret_cast<b4*>(q) = y;
+    } else {
+      *reinterpret_cast<b2*>(p) = b2{x[0], x[1]};
+      *reinterpret_cast<b2*>(p + 2) = b2{x[2], x[3]};
+      *reinterpret_cast<b2*>(q) = b2{y[0], y[1]};
+      *reinterpret_cast<b2*>(q + 2) = b2{y[2], y[3]};
+    }
+    return;
   }
-  return true;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (row0 + e >= M) continue;
+    bf16* v = reinterpret_cast<bf16*>(ep.vst) + ((size_t)r.b[e] * Dh + within) * ep.vst_ld + r.i[e];
+    v[0] = x[e];
+    v[(size_t)16 * ep.vst_ld] = y[e];
+  }
 }
 
 // s_waitcnt with vmcnt = N and the other counters not waited for

@@ -409,21 +409,26 @@ __global__ __launch_bounds__(S::NT) void k_gemm_dma(GemmLaunch g) {
 
   float* out = g.ep.out_f32 ? g.ep.out_f32 + (size_t)blockIdx.z * M * N : nullptr;
 #pragma unroll
-  for (int a = 0; a < S::TM; ++a)
+  for (int a = 0; a < S::TM; ++a) {
+    const int row0 = rbase + a * 16;
+    if constexpr (EPI == EPI_QKV) {
+      const QkvRows rows = qkv_rows(g.ep, row0);
 #pragma unroll
-    for (int b = 0; b < S::TN; b += 2)
+      for (int b = 0; b < S::TN; b += 2) {
+        if constexpr (!PRE) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if constexpr (EPI == EPI_QKV) {
-          if (i == 0 && epilogue_v4(g.ep, M, N, rbase + a * 16, cbase + b * 16, acc[a][b], acc[a][b + 1])) break;
+          for (int i = 0; i < 4; ++i) rope[0][0][i] = qkv_rope_factor(g.ep, M, N, row0 + i, cbase + b * 16);
         }
-        if constexpr (PRE)
-          epilogue_qkv_pre<bf16>(g.ep, M, N, rbase + a * 16 + i, cbase + b * 16, acc[a][b][i], acc[a][b + 1][i],
-                                 rope[a][b / 2][i]);
-        else
-          epilogue_pair<bf16, EPI>(g.ep, out, M, N, rbase + a * 16 + i, cbase + b * 16, acc[a][b][i],
-                                   acc[a][b + 1][i]);
+        epilogue_qkv_tile(g.ep, rows, M, N, row0, cbase + b * 16, acc[a][b], acc[a][b + 1], rope[PRE ? a : 0][PRE ? b / 2 : 0]);
       }
+    } else {
+#pragma unroll
+      for (int b = 0; b < S::TN; b += 2)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          epilogue_pair<bf16, EPI>(g.ep, out, M, N, row0 + i, cbase + b * 16, acc[a][b][i], acc[a][b + 1][i]);
+    }
+  }
 }
 
 // Every ring runs at least two waves per SIMD: with one, a wave's LDS reads and its MFMAs take turns
@@ -719,7 +724,7 @@ hipError_t launch_gemm(jpi_dtype dt, const GemmLaunch& g, hipStream_t s) {
     // over the expert's and the VLM's products; within 15 % of the fastest tile on all of them.  Against the
     // rule it replaces (256 x 256 when they fill the units, one full round of 128 x 256, else register-staged
     // 128 x 128): gate/up M = 1126 37.2 -> 26.6, M = 1689 42.6 -> 28.9; Down in 4 slices M = 550 17.7 -> 12.5, M = 1126
-    // 22.4 -> 16.6; VLM QKV M = 1689 48.4 -> 39.3, M = 816 25.2 -> 22.1.
+    // 22.4 -> 16.6; VLM QKV M = 1689 48.4 -> 32.0, M = 816 25.2 -> 21.0 (with the row-tile epilogue).
     const bool fits = (size_t)g.N * g.K * 2 < (1u << 31) && (size_t)g.M * g.K * 2 < (1u << 31);
     if (gemm_pipe_enabled() && fits) {
       struct Ring {
@@ -728,11 +733,11 @@ hipError_t launch_gemm(jpi_dtype dt, const GemmLaunch& g, hipStream_t s) {
         float qkv;              // what a QKV epilogue adds
         hipError_t (*launch)(const GemmLaunch&, hipStream_t);
       };
-      static const Ring rings[] = {{256, 256, 1, 8.0f, 1.18f, 20.f, launch_dma<DmaBig>},
-                                   {128, 256, 1, 5.3f, 0.66f, 11.f, launch_dma<DmaWide>},
-                                   {128, 128, 1, 4.5f, 0.47f, 7.f, launch_dma<DmaMid>},
-                                   {128, 64, 2, 4.0f, 0.29f, 4.f, launch_dma<DmaTall>},
-                                   {64, 64, 2, 3.7f, 0.27f, 3.5f, launch_dma<DmaSmall>}};
+      static const Ring rings[] = {{256, 256, 1, 8.0f, 1.18f, 8.f, launch_dma<DmaBig>},
+                                   {128, 256, 1, 5.3f, 0.66f, 5.f, launch_dma<DmaWide>},
+                                   {128, 128, 1, 4.5f, 0.47f, 4.f, launch_dma<DmaMid>},
+                                   {128, 64, 2, 4.0f, 0.29f, 0.f, launch_dma<DmaTall>},
+                                   {64, 64, 2, 3.7f, 0.27f, 0.5f, launch_dma<DmaSmall>}};
       const float slices = (float)(g.K / g.splitk / 64);
       const Ring* best = nullptr;
       float best_t = 0.f;
