@@ -709,12 +709,26 @@ __global__ __launch_bounds__(64 * ROWS_NW, 2) void k_flash_rows(AttnLaunch a, in
   }
 }
 
-// Key ranges per 16-row tile: workgroups for the whole chip, at least one 32-key block per wave
-int flash_rows_splits(int B, int nH, int H, int P, int n_cu) {
+// Key ranges per 16-row tile: the least estimated time (0.1 us; rounds of one workgroup per unit, each a start and the
+// turns of its waves over 32-key blocks - a memory round trip and the block's bytes - and the merge with its launch).  A
+// second workgroup on a unit costs almost a whole round, so ranges pay only while they fit one.  Measured with the merge
+// (Dh 256, 8 heads of 50 rows, 816 tokens; 1, 2, 4, 8 ranges): one rollout 13.5, 12.3, 10.6, 10.2 us; two 13.2,
+// 12.4, 10.7, 13.6; five 13.7, 13.6, 17.1; eight 13.4, 18.7.  With "enough for the chip" (three rollouts four
+// ranges, eight two) batch 8 took 11.65 ms instead of 11.13 and batch 3 9.74 instead of 9.54.  Eight waves a
+// workgroup and 32 rows a workgroup were slower throughout.
+int flash_rows_splits(int B, int nH, int H, int P, int Dh, int n_cu) {
   const int ntile = (nH * H + 15) / 16, nb = (H + 31) / 32 + (P + 31) / 32;
-  int s = 1;
-  while (s < 8 && B * ntile * s < n_cu && ROWS_NW * s < nb) s *= 2;
-  return s;
+  int best = 1;
+  long best_cost = -1;
+  for (int s = 1; s <= 8 && (s == 1 || 2 * s < nb); s *= 2) {
+    const long rounds = ((long)B * ntile * s + n_cu - 1) / n_cu;
+    const long cost = rounds * (52 + (6 + 6 * Dh / 256) * ((nb + ROWS_NW * s - 1) / (ROWS_NW * s))) + (s > 1 ? 35 : 0);
+    if (best_cost < 0 || cost < best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 template <int DH, typename TO>

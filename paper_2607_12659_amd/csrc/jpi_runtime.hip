@@ -896,7 +896,7 @@ jpi_status ensure_scratch(jpi_ctx* c, int batch, int prefix) {
   const size_t nch = p.persist ? (size_t)persist_chunks(prefix, S) : (size_t)attn_n_chunks(c->dt, prefix, S);
   size_t attn = (size_t)batch * c->nH * nch * S * (c->Dh + 2);
   if (p.small)
-    attn = std::max(attn, (flash_scratch_bytes(batch, c->nH, S, c->Dh, flash_rows_splits(batch, c->nH, S, prefix, c->n_cu)) + 3) / 4);
+    attn = std::max(attn, (flash_scratch_bytes(batch, c->nH, S, c->Dh, flash_rows_splits(batch, c->nH, S, prefix, c->Dh, c->n_cu)) + 3) / 4);
   if (attn > c->attn_cap) {
     if (c->opart) (void)hipFree(c->opart);
     c->opart = nullptr;

@@ -838,7 +838,7 @@ hipError_t enqueue_small_layer(const SmallLayer& y, hipStream_t s) {
   a.n_cu = y.n_cu;
   a.ev_start = y.ev[JPI_KERNEL_ATTENTION][0];
   a.ev_stop = y.ev[JPI_KERNEL_ATTENTION][1];
-  if ((e = launch_flash_rows(a, flash_rows_splits(y.B, y.nH, y.S, y.P, y.n_cu), s)) != hipSuccess) return e;
+  if ((e = launch_flash_rows(a, flash_rows_splits(y.B, y.nH, y.S, y.P, y.Dh, y.n_cu), s)) != hipSuccess) return e;
   g = base;
   g.A = (const bf16*)y.o;
   g.W = y.w + y.off_o;

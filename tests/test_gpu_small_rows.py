@@ -62,6 +62,22 @@ def test_small_rows_match_oracle(shape, batch, n_fixed, n_corr, t0):
         ae.close()
 
 
+# 1, 2, 4 and 8 key ranges, some without keys
+@pytest.mark.parametrize("shape,batch,lens", [("w1024", 4, [300, 0, 33, 299]), ("w1024", 3, [1100, 0, 545]),
+                                              ("w1024", 2, [700, 130]), ("w1024", 1, [700]), ("w512", 1, [1500])])
+def test_small_rows_key_ranges(shape, batch, lens):
+    wl = synth.Workload("ranges-%s-b%d" % (shape, batch), SHAPES[shape], prefix=lens[0], batch=batch, n_steps=2, n_fixed=0,
+                        dtype="bf16", prefix_len=tuple(lens), mod_gain=8.0)
+    inp = Inputs(wl)
+    print("case", wl.name, lens, flush=True)
+    ae = make_expert(wl, inp.weights)
+    try:
+        got = run(ae, inp.K, inp.V, inp.noise, wl.n_steps, prefix_len=inp.prefix_len)
+        assert_bf16(got, _oracle(wl, inp, None), wl.name, reg_rel=REL, reg_abs=ABS)
+    finally:
+        ae.close()
+
+
 def test_small_rows_after_longer_rows():
     """Own-key blocks keep what a longer call left behind their last key; it must not show."""
     wl, inp, corr = _case("w1024", 2, 0, 4)
