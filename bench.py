@@ -9,9 +9,9 @@ in HBM.  Prints one JSON line:
   roofline   the dominant kernel's algorithmic bytes per launch / its average
              launch duration (start/stop HIP events tied to every dispatch of
              that kernel on the stream it runs on, in a timing pass right after
-             the timed region), against MI355X's 8 TB/s HBM peak.  With
-             batch * horizon <= 64 the whole call is one persistent kernel;
-             otherwise the largest GEMM kind.  "kernels" lists every kind that
+             the timed region), against MI355X's 8 TB/s HBM peak.  The GateUp
+             product is the largest kind; where the single-launch kernel
+             runs instead (JPI_PERSIST=1) the whole call is that kernel.  "kernels" lists every kind that
              ran.  "traffic" is the HBM bytes per launch measured with the
              FETCH_SIZE / WRITE_SIZE counters (scaled by a plain copy of known
              size, see --calibrate-copy) when the counters were taken on the
@@ -670,7 +670,7 @@ def bench_loop(args):
                           "expert_with_item": round(mean["act"], 4)},
         "synchronous_reaction_ms": round(sync_ms, 4),
         "reaction_reduction": round(sync_ms / stats.reaction_ms, 3),
-        "roofline": {"bound": "hbm", "kernel": "k_persist (the expert call inside the loop)", "achieved": round(gbs, 1),
+        "roofline": {"bound": "hbm", "kernel": "the expert call inside the loop", "achieved": round(gbs, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": None},
         "cpu_baseline": None, "outputs_finite": finite,
         "note": "forced confidence trace (synthetic weights); iteration times include host synchronisation per hook",
