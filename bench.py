@@ -9,9 +9,9 @@ in HBM.  Prints one JSON line:
   roofline   the dominant kernel's algorithmic bytes per launch / its average
              launch duration (start/stop HIP events tied to every dispatch of
              that kernel on the stream it runs on, in a timing pass right after
-             the timed region), against MI355X's 8 TB/s HBM peak.  The GateUp
-             product is the largest kind; where the single-launch kernel
-             runs instead (JPI_PERSIST=1) the whole call is that kernel.  "kernels" lists every kind that
+             the timed region), against MI355X's 8 TB/s HBM peak.  It is the
+             GateUp product, half of the weight bytes; where the single-launch
+             kernel runs instead (JPI_PERSIST=1) the whole call is that kernel.  "kernels" lists every kind that
              ran.  "traffic" is the HBM bytes per launch measured with the
              FETCH_SIZE / WRITE_SIZE counters (scaled by a plain copy of known
              size, see --calibrate-copy) when the counters were taken on the
