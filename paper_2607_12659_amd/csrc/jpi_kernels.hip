@@ -702,9 +702,8 @@ hipError_t launch_gemm(jpi_dtype dt, const GemmLaunch& g, hipStream_t s) {
     auto tiles = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.splitk; };
     // the direct-to-LDS pipeline (one 128 KB ring per compute unit) wins where one
     // round of 128 x 128 tiles covers the chip and no more (measured: M = 400
-    // GateUp 25.1 -> 19.6 us, Down 16.2 -> 13.4 us); with more tiles the
-    // register-staged kernel's two workgroups per unit win, with fewer the
-    // smaller tiles below
+    // GateUp 25.1 -> 19.6 us, Down 16.2 -> 13.4 us, against the register-staged
+    // kernel); other counts take a tile by the rules below
     if (gemm_pipe_enabled() && g.M <= 512 && tiles(128, 128) >= n_cu && tiles(128, 128) <= n_cu + n_cu / 4 &&
         (g.K / g.splitk) % DmaMid::BK == 0 && (size_t)g.N * g.K * 2 < (1u << 31))
       return launch_dma<DmaMid>(g, s);
@@ -752,6 +751,7 @@ hipError_t launch_gemm(jpi_dtype dt, const GemmLaunch& g, hipStream_t s) {
       }
       return best->launch(g, s);
     }
+    // operands of 2 GiB or more (the rings' buffer offsets are 32 bit) and JPI_GEMM_PIPE=0: register-staged tiles
     if (tiles(256, 256) >= n_cu) return launch_big<Big256>(g, s);
     if (tiles(128, 128) >= n_cu || g.epi == EPI_STORE_F32) return launch_gemm_t<bf16, 128, 128>(g, s);
     if (tiles(128, 64) >= n_cu) return launch_gemm_t<bf16, 128, 64>(g, s);

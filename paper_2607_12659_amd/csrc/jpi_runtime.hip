@@ -845,7 +845,7 @@ bool use_persist(jpi_ctx* c, int batch) {
 
 // Five-launch layers (jpi_small.hip) for up to SMALL_ROWS activation rows.  Per
 // call on one MI355X, pi0.5 shape, 816 tokens: 1 rollout 6.6 ms against 7.75 (single
-// launch), 3 rollouts 9.6 against 11.3 and 8 (400 rows) 11.6 against 13.1 (eight launches per layer); the tiny bf16 expert,
+// launch), 3 rollouts 9.5 against 11.3 and 8 (400 rows) 11.1 against 13.1 (eight launches per layer); the tiny bf16 expert,
 // 4 rollouts, 10 steps 0.59 against 0.91 (single launch).  Past 512 rows the
 // tiles of the eight-launch layers share their operands better.
 // JPI_PERSIST=1 and a wait bound set for its test ask for the single-launch kernel, which
