@@ -58,7 +58,7 @@ int gemm_pick_splitk(jpi_dtype dt, int M, int N, int K, int n_cu);
 hipError_t launch_sum_slices(const float* P, float* C, int S, size_t MN, hipStream_t s);
 int gemm_k_quantum(jpi_dtype dt, int M);  // K of every split must be a multiple of this
 
-// Per-row residual update + next adaRMSNorm (see k_resid_norm).
+// Per-row residual update + next adaRMSNorm (see k_resid_norm_row).
 struct RowLaunch {
   const float* part;     // [S][M][W] split-K slices of the sublayer output
   int S, M, W;

@@ -804,8 +804,8 @@ hipError_t launch_sum_slices(const float* P, float* C, int S, size_t MN, hipStre
 // given tokens of the expert's width and produce no velocity.
 // k_inproj_norm:  h = x W_in^T + b_in (action rows) or the correction token;
 //                 y = adaRMSNorm(h; scale, shift)
-// k_resid_norm:   h += gate * sum_z P[z][m];  y = adaRMSNorm(h; scale, shift)
-//   FINAL variant (action rows only): v = adaRMSNorm(h; s_f, b_f) W_out^T + b_out
+// k_resid_norm_*: h += gate * sum_z P[z][m];  y = adaRMSNorm(h; scale, shift)
+// k_resid_head    (last layer, action rows only): the same h, v = adaRMSNorm(h; s_f, b_f) W_out^T + b_out
 //                  and x[b][i] += dt * v for action rows i >= n_fixed
 // adaRMSNorm(h) = h / sqrt(mean(h^2) + eps) * (1 + scale) + shift.
 // ===========================================================================
@@ -877,78 +877,76 @@ __device__ __forceinline__ void load4(const bf16* p, float (&w)[4]) {
   w[3] = __uint_as_float(v.y & 0xffff0000u);
 }
 
-template <typename T, bool FINAL>
-__global__ __launch_bounds__(256) void k_resid_norm(RowLaunch r) {
-  __shared__ float hs[ROW_MAX_W];
+// The step's last row kernel, one workgroup per action row: thread t owns columns 4t + 1024 j .. + 3, which stay in its
+// registers from the slices to the dot products.  NJ 1024-column passes and up to MAXS slices, known when compiling, and
+// the first eight rows of W_out (the next eight, while eight are multiplied) requested before the row
+// reduction: with 16 predicated slices, the row in LDS and W_out behind the
+// reduction a launch over ten rows of 256 columns (fp32, 8 slices) took 7.4 us against 4.3, one over 3200 rows of 1024 (bf16, 2 slices)
+// 56.7 against 43.1.
+template <typename T, int NJ, int MAXS>
+__global__ __launch_bounds__(256) void k_resid_head(RowLaunch r) {
   __shared__ float red[4];
   __shared__ float dots[4][ROW_MAX_A];
   const int m = blockIdx.x, W = r.W, S = r.S;
   const size_t MW = (size_t)r.M * W;
+  const int seq = r.n_lead + r.horizon, b = m / seq, i = m - b * seq - r.n_lead;
   // the last layer's correction rows feed nothing (the next step restarts them)
-  if constexpr (FINAL) {
-    if (m % (r.n_lead + r.horizon) < r.n_lead) return;
-  }
+  if (i < 0) return;
   // committed rows at t = 0 take the gate, scale and shift of the t = 0 table row
-  const float *gate = r.gate, *scale = r.scale, *shift = r.shift;
-  if (r.n_t0 > 0) {
-    const int ia = m % (r.n_lead + r.horizon) - r.n_lead;
-    if (ia >= 0 && ia < r.n_t0) {
-      gate += r.t0_delta;
-      scale += r.t0_delta;
-      shift += r.t0_delta;
-    }
-  }
+  const int64_t t0 = i < r.n_t0 ? r.t0_delta : 0;
+  const float *gate = r.gate + t0, *scale = r.scale + t0, *shift = r.shift + t0;
   float* hr = r.h + (size_t)m * W;
   const float* pr = r.part + (size_t)m * W;
-  // four columns per thread per pass; all split-K slices loaded before summing
-  for (int k0 = threadIdx.x; k0 < W; k0 += 1024) {
-    float v[4][ROW_MAX_S], hv[4], gv[4];
+  const T* wo = reinterpret_cast<const T*>(r.w_out);
+  constexpr int PRE = NJ == 1 ? 8 : 0;  // W_out rows requested ahead
+  float wq[PRE > 0 ? PRE : 1][4];
+  auto request = [&](int a0) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int k = k0 + 256 * j;
+    for (int u = 0; u < PRE; ++u)
+      if (a0 + u < r.A && 4 * (int)threadIdx.x < W) load4(wo + (size_t)(a0 + u) * W + 4 * threadIdx.x, wq[u]);
+  };
+  f32x4 hv[NJ], sc[NJ], sh[NJ];
+  float ss = 0.f;
 #pragma unroll
-      for (int z = 0; z < ROW_MAX_S; ++z) v[j][z] = (z < S && k < W) ? pr[z * MW + k] : 0.f;
-      hv[j] = k < W ? hr[k] : 0.f;
-      gv[j] = k < W ? gate[k] : 0.f;
-    }
+  for (int j = 0; j < NJ; ++j) {
+    const int k = 4 * threadIdx.x + 1024 * j;
+    hv[j] = sc[j] = sh[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (k >= W) continue;
+    f32x4 v[MAXS];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int k = k0 + 256 * j;
-      float sum = 0.f;
+    for (int z = 0; z < MAXS; ++z)
+      v[z] = z < S ? *reinterpret_cast<const f32x4*>(pr + z * MW + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+    const f32x4 h = *reinterpret_cast<const f32x4*>(hr + k), g4 = *reinterpret_cast<const f32x4*>(gate + k);
+    sc[j] = *reinterpret_cast<const f32x4*>(scale + k);
+    sh[j] = *reinterpret_cast<const f32x4*>(shift + k);
+    if (j == 0) request(0);
+    f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int z = 0; z < ROW_MAX_S; ++z)
-        if (z < S) sum += v[j][z];
-      if (k < W) {
-        const float h2 = hv[j] + gv[j] * sum;
-        hr[k] = h2;
-        hs[k] = h2;
-      }
-    }
+    for (int z = 0; z < MAXS; ++z)
+      if (z < S) sum += v[z];
+    hv[j] = h + g4 * sum;
+    *reinterpret_cast<f32x4*>(hr + k) = hv[j];
+    ss += hv[j][0] * hv[j][0] + hv[j][1] * hv[j][1] + hv[j][2] * hv[j][2] + hv[j][3] * hv[j][3];
   }
-  __syncthreads();
-  const float rs = row_rstd(hs, W, r.eps, red);
-  if constexpr (!FINAL) {
-    T* yr = reinterpret_cast<T*>(r.y) + (size_t)m * W;
-    for (int k = threadIdx.x; k < W; k += 256) yr[k] = from_f32<T>(hs[k] * rs * (1.0f + scale[k]) + shift[k]);
-  } else {
-    // v[a] = sum_k y[k] W_out[a][k] + b_out[a]; thread t owns columns 4t + 1024 j .. + 3,
-    // so each row of W_out is read with one 4-element load per thread, all independent
-    constexpr int NJ = ROW_MAX_W / 1024;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const T* wo = reinterpret_cast<const T*>(r.w_out);
-    float yk[NJ][4];
+  const float rs = 1.0f / sqrtf(block_sum_256(ss, red) / (float)W + r.eps);
+  // v[a] = sum_k y[k] W_out[a][k] + b_out[a]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  f32x4 y[NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int k = 4 * threadIdx.x + 1024 * j;
+  for (int j = 0; j < NJ; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        yk[j][e] = k < W ? hs[k + e] * rs * (1.0f + scale[k + e]) + shift[k + e] : 0.f;
-    }
-    for (int a0 = 0; a0 < r.A; a0 += 8) {
-      float p[8];
+    for (int e = 0; e < 4; ++e) y[j][e] = hv[j][e] * rs * (1.0f + sc[j][e]) + sh[j][e];  // zero past W
+  for (int a0 = 0; a0 < r.A; a0 += 8) {
+    float p[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        p[u] = 0.f;
+    for (int u = 0; u < 8; ++u) {
+      p[u] = 0.f;
+      if constexpr (PRE > 0) {
+        if (a0 + u < r.A && 4 * (int)threadIdx.x < W) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) p[u] = fmaf(y[0][e], wq[u][e], p[u]);
+        }
+      } else {
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
           const int k = 4 * threadIdx.x + 1024 * j;
@@ -956,23 +954,23 @@ __global__ __launch_bounds__(256) void k_resid_norm(RowLaunch r) {
             float w4[4];
             load4(wo + (size_t)(a0 + u) * W + k, w4);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) p[u] = fmaf(yk[j][e], w4[e], p[u]);
+            for (int e = 0; e < 4; ++e) p[u] = fmaf(y[j][e], w4[e], p[u]);
           }
         }
       }
+    }
+    if constexpr (PRE > 0) request(a0 + 8);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float t = wave_sum(p[u]);
-        if (lane == 0 && a0 + u < r.A) dots[wave][a0 + u] = t;
-      }
+    for (int u = 0; u < 8; ++u) {
+      const float t = wave_sum(p[u]);
+      if (lane == 0 && a0 + u < r.A) dots[wave][a0 + u] = t;
     }
-    __syncthreads();
-    const int seq = r.n_lead + r.horizon, b = m / seq, i = m % seq - r.n_lead;
-    if (threadIdx.x < r.A && i >= r.n_fixed) {
-      const int a = threadIdx.x;
-      const float v = ((dots[0][a] + dots[1][a]) + dots[2][a]) + dots[3][a] + r.b_out[a];
-      r.x[((size_t)b * r.horizon + i) * r.A + a] += r.dt * v;
-    }
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < r.A && i >= r.n_fixed) {
+    const int a = threadIdx.x;
+    const float v = ((dots[0][a] + dots[1][a]) + dots[2][a]) + dots[3][a] + r.b_out[a];
+    r.x[((size_t)b * r.horizon + i) * r.A + a] += r.dt * v;
   }
 }
 
@@ -1032,7 +1030,7 @@ __global__ __launch_bounds__(256) void k_resid_norm_row(RowLaunch r) {
 
 // Non-final residual + norm with one wave per row (four rows per workgroup):
 // the row's sum of squares is a wave reduction, so no workgroup barrier.
-// Same per-element arithmetic as k_resid_norm (slices summed in order).
+// Same per-element arithmetic as k_resid_norm_row (slices summed in order).
 template <typename T, int NJ>
 __global__ __launch_bounds__(256) void k_resid_norm_wave(RowLaunch r) {
   // A wave per row, W <= 256 NJ.  Every load of the row (up to RW_SLICES
@@ -1136,23 +1134,39 @@ static void launch_norm_row(const RowLaunch& r, hipStream_t s) {
 #undef NORM_ROW
 }
 
+template <typename T>
+static void launch_head_row(const RowLaunch& r, hipStream_t s) {
+#define HEAD_ROW(NJ, MAXS) hipLaunchKernelGGL((k_resid_head<T, NJ, MAXS>), dim3(r.M), dim3(256), 0, s, r)
+  if (r.W <= 1024) {
+    if (r.S <= 4) HEAD_ROW(1, 4);
+    else HEAD_ROW(1, ROW_MAX_S);
+  } else if (r.W <= 2048) {
+    if (r.S <= 4) HEAD_ROW(2, 4);
+    else HEAD_ROW(2, ROW_MAX_S);
+  } else {
+    if (r.S <= 4) HEAD_ROW(4, 4);
+    else HEAD_ROW(4, ROW_MAX_S);
+  }
+#undef HEAD_ROW
+}
+
 hipError_t launch_resid_norm(jpi_dtype dt, const RowLaunch& r, bool final_step, hipStream_t s) {
   if (r.W > ROW_MAX_W || r.S > ROW_MAX_S || r.S < 1) return hipErrorInvalidValue;
   if (final_step && (r.A > ROW_MAX_A || r.horizon < 1 || r.n_lead < 0 || r.M % (r.n_lead + r.horizon)))
     return hipErrorInvalidValue;
   // a wave per row pays off only with many rows (batch 64: 23 -> 12 us); with
   // fewer rows a workgroup per row keeps more loads in flight
-  if (!final_step && r.W % 4 != 0) return hipErrorInvalidValue;
+  if (r.W % 4 != 0) return hipErrorInvalidValue;
   const bool wave_rows = !final_step && r.M >= 2048;
   const dim3 wave_grid((r.M + 3) / 4);
   if (dt == JPI_BF16) {
-    if (final_step) hipLaunchKernelGGL((k_resid_norm<bf16, true>), dim3(r.M), dim3(256), 0, s, r);
+    if (final_step) launch_head_row<bf16>(r, s);
     else if (wave_rows && r.W <= 1024) hipLaunchKernelGGL((k_resid_norm_wave<bf16, 4>), wave_grid, dim3(256), 0, s, r);
     else if (wave_rows && r.W <= 2048) hipLaunchKernelGGL((k_resid_norm_wave<bf16, 8>), wave_grid, dim3(256), 0, s, r);
     else if (wave_rows) hipLaunchKernelGGL((k_resid_norm_wave<bf16, 16>), wave_grid, dim3(256), 0, s, r);
     else launch_norm_row<bf16>(r, s);
   } else {
-    if (final_step) hipLaunchKernelGGL((k_resid_norm<float, true>), dim3(r.M), dim3(256), 0, s, r);
+    if (final_step) launch_head_row<float>(r, s);
     else if (wave_rows && r.W <= 1024) hipLaunchKernelGGL((k_resid_norm_wave<float, 4>), wave_grid, dim3(256), 0, s, r);
     else if (wave_rows && r.W <= 2048) hipLaunchKernelGGL((k_resid_norm_wave<float, 8>), wave_grid, dim3(256), 0, s, r);
     else if (wave_rows) hipLaunchKernelGGL((k_resid_norm_wave<float, 16>), wave_grid, dim3(256), 0, s, r);
