@@ -60,6 +60,30 @@ def test_denoise_past_512_rows(width, heads, Dh, horizon, batch, n_corr):
         ae.close()
 
 
+# the last row kernel's passes over 1024 columns: one, two and four, the last one ragged; action widths around its groups of eight
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("width,A", [(192, 8), (1024, 1), (1088, 9), (2112, 17)])
+def test_last_row_kernel_widths(dtype, width, A):
+    d = synth.Dims(n_layers=1, width=width, n_heads=1, n_kv_heads=1, head_dim=64, mlp_dim=64, action_dim=A, horizon=3)
+    B = 2 if dtype == "f32" else 171  # 513 rows: past the five-launch layers
+    lens = tuple([5, 0][b % 2] for b in range(B))
+    wl = synth.Workload("head", d, prefix=5, batch=B, n_steps=2, n_fixed=1, dtype=dtype, prefix_len=lens)
+    inp = Inputs(wl)
+    print("case", dtype, width, A, flush=True)
+    ae = make_expert(wl, inp.weights)
+    try:
+        got = run(ae, inp.K, inp.V, inp.noise, 2, prefix_len=lens, committed=inp.committed, n_fixed=1)
+        pick = [0, 1, B - 1]  # rollouts are independent
+        ref = oracle.denoise(oracle.Expert(d, inp.weights), inp.noise[pick], inp.K[:, pick], inp.V[:, pick],
+                             [lens[b] for b in pick], 2, committed=inp.committed[pick], n_fixed=1)
+        # fp32 sums of at most 2112 terms per product; bf16: every product's inputs rounded (2^-9 each)
+        bar = 1e-5 if dtype == "f32" else 4e-3
+        assert np.linalg.norm(got[pick] - ref) <= bar * np.linalg.norm(ref)
+        assert np.array_equal(got[:, :1], inp.committed.astype(np.float64))
+    finally:
+        ae.close()
+
+
 # several rollouts whose rows start at every place mod 4 in a row tile (QKV tiles cross rollouts)
 @pytest.mark.parametrize("prefix", [44, 45, 46, 47])
 def test_prefill_rows_cross_rollouts(prefix):
