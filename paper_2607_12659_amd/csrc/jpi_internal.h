@@ -9,6 +9,7 @@
 #include <hip/hip_ext.h>
 
 #include "../../include/jpi.h"
+#include "jpi_bounds.h"
 
 namespace jpi {
 

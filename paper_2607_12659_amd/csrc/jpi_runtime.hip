@@ -434,7 +434,7 @@ jpi_status jpi_create(const jpi_config* cfg, int device, jpi_ctx** out) {
   ALLOC(c->ks, M * Dh * es);
   ALLOC(c->vst, (size_t)c->Bmax * Dh * ((seq_max + 7) / 8 * 8) * es);  // rows padded to 8 elements
   ALLOC(c->o, M16 * nH * Dh * es);
-  ALLOC(c->z, M16 * F * es);
+  ALLOC(c->z, M16 * z_columns(W, F, g.variant == JPI_VARIANT_ACTION_TIME) * es);
   ALLOC(c->pflags, (size_t)persist_flag_words() * sizeof(unsigned));
   ALLOC(c->perr, 256);
   if (persist_trace_build()) {  // room for 64 Euler steps of every layer's 8 phases, 3 stamps each

@@ -1,0 +1,33 @@
+"""The host arithmetic that buffer sizes and kernel index bounds rest on
+(csrc/jpi_bounds.h), over every shape class the library accepts: a small C++
+program is compiled from the header and run, no GPU needed."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2607_12659_amd", "csrc")
+
+PROGRAMS = {
+    # z holds the GeGLU output of every row and, in the action-time variant, the action-time MLP's W columns
+    "z_columns": """
+  for (size_t W = 64; W <= 4096; W += 64)
+    for (size_t F = 64; F <= 4096; F += 64)
+      for (int at = 0; at < 2; ++at) {
+        const size_t z = jpi::z_columns(W, F, at);
+        CHECK(z >= F && (!at || z >= W));
+        CHECK(z == F || (at && z == W));
+      }
+""",
+}
+
+
+@pytest.mark.parametrize("name", sorted(PROGRAMS))
+def test_bounds(name, tmp_path):
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text('#include <cstdio>\n#include "jpi_bounds.h"\n'
+                   '#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\\n", __LINE__, #x); return 1; } } while (0)\n'
+                   "int main() {" + PROGRAMS[name] + "  return 0;\n}\n")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True)
+    assert r.returncode == 0, r.stdout

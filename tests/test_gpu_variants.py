@@ -221,3 +221,25 @@ def test_pi0_shape_action_time_variant():
         rel = rel_l2_per_rollout(out, ref)
         print("%s: rel-L2 %.3e max-abs %.3e" % (label, rel, np.abs(out - ref).max()), flush=True)
         assert_bf16(out, ref, label, reg_rel=1e-2, reg_abs=5e-2)
+
+
+# an MLP narrower than the expert: the action-time MLP's rows (width columns) share a buffer with the GeGLU
+# output (mlp_dim columns); every rollout the context was made for, rows 48 and 50
+@pytest.mark.parametrize("width,mlp,horizon,batch", [(512, 256, 16, 3), (1024, 256, 50, 1), (1024, 512, 25, 2)])
+def test_action_time_mlp_narrower_than_the_expert(width, mlp, horizon, batch):
+    torch_cuda()
+    d = synth.Dims(n_layers=2, width=width, n_heads=8, n_kv_heads=1, head_dim=64, mlp_dim=mlp, action_dim=7, horizon=horizon)
+    lens = [40, 7, 33][:batch]
+    wl = synth.Workload("pi0-narrow", d, prefix=40, batch=batch, n_steps=3, n_fixed=0, dtype="bf16", prefix_len=tuple(lens))
+    print("case pi0-narrow", width, mlp, horizon, batch, flush=True)
+    w = spi0.make_pi0_weights(wl)
+    K, V = synth.make_prefix(wl)
+    noise, st = synth.make_noise(wl), spi0.make_state(wl)
+    ae = _pi0_expert(wl, w, batch, wl.prefix + 1)
+    try:
+        got = _pi0_run(ae, K, V, noise, wl.n_steps, lens, st)
+        again = _pi0_run(ae, K, V, noise, wl.n_steps, lens, st)
+    finally:
+        ae.close()
+    assert_bf16(got, opi0.denoise(wl.dims, w, noise, K, V, lens, wl.n_steps, st), "narrow MLP")
+    assert np.array_equal(got, again)
