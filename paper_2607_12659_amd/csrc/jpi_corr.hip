@@ -392,7 +392,7 @@ hipError_t ready_small(jpi_corr* m, hipStream_t s) {
   const size_t W = m->W, Dh = m->Dh, nH = m->nH, HD = nH * Dh, F = m->F, B = m->Bmax, T = m->T;
   const size_t blk = kv_block_elems((int)Dh);
   if (!small_supported(JPI_BF16, m->W, m->nH, m->Dh, m->F) || (int)(B * T) > SMALL_MAX_ROWS) return hipSuccess;
-  m->NBmax = (m->Tmax + 31) / 32;
+  m->NBmax = kv_blocks(m->Tmax);
   if (!m->f_blocks) {
     bool ok = true;
     auto alloc = [&](auto** p, size_t bytes) {

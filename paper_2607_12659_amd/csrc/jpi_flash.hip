@@ -598,7 +598,8 @@ __global__ __launch_bounds__(64 * ROWS_NW, 2) void k_flash_rows(AttnLaunch a, in
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) vf[nt] = *reinterpret_cast<const u32x4*>(p + (2 * NST + nt) * 512);
   };
-  // the first block does not wait for prefix_len: any block below the bound P may be read
+  // the first block does not wait for prefix_len: any block below the bound P may be read (a rollout has
+  // kv_blocks(P) of them, checked before the launch)
   const int jb0 = split * NW + w;
   MF::frag qf[NST];
   const bf16* qb = reinterpret_cast<const bf16*>(a.q) + ((size_t)b * R + min(row0 + fr, R - 1)) * DH + 8 * g;
@@ -746,6 +747,7 @@ static hipError_t launch_flash_rows_t(const AttnLaunch& a, int S, hipStream_t s)
 
 hipError_t launch_flash_rows(const AttnLaunch& a, int S, hipStream_t s) {
   if ((S != 1 && S != 2 && S != 4 && S != 8) || a.H < 1 || a.B < 1) return hipErrorInvalidValue;
+  if (a.P < 0 || (int64_t)(kv_blocks(a.P) * kv_block_elems(a.Dh)) > a.kvf_bstride) return hipErrorInvalidValue;
   switch (a.Dh) {
     case 64: return a.out_f32 ? launch_flash_rows_t<64, float>(a, S, s) : launch_flash_rows_t<64, bf16>(a, S, s);
     case 128: return a.out_f32 ? launch_flash_rows_t<128, float>(a, S, s) : launch_flash_rows_t<128, bf16>(a, S, s);

@@ -661,7 +661,7 @@ jpi_status ensure_blocks(jpi_ctx* c) {
     return JPI_OK;
   }
   const size_t blk = kv_block_elems(c->Dh) * c->esz, S = c->H + c->Cmax;
-  c->NBmax = (c->Pmax + 31) / 32;
+  c->NBmax = kv_blocks(c->Pmax);
   const size_t own = (size_t)c->Bmax * ((S + 31) / 32) * blk;
   const size_t state = c->cfg.variant == JPI_VARIANT_ACTION_TIME ? (size_t)c->L * c->Bmax * blk : 0;
   if (hipMalloc(&c->kvf, (size_t)c->L * c->Bmax * c->NBmax * blk) != hipSuccess) {
@@ -879,6 +879,11 @@ StepGemms plan_gemms(jpi_ctx* c, int batch) {
   return p;
 }
 
+// Keys that a rollout's rows may see in the prefix slots (a bound on prefix_len, and on the state token's slot).
+int prefix_keys(const jpi_ctx* c) {
+  return key_bound(c->prefix, c->Pmax, c->cfg.variant == JPI_VARIANT_ACTION_TIME);
+}
+
 jpi_status ensure_scratch(jpi_ctx* c, int batch, int prefix) {
   const StepGemms p = plan_gemms(c, batch);
   const size_t need = std::max((size_t)std::max(std::max(p.s_o, p.s_d), p.s_a) * p.M * c->W,
@@ -1092,7 +1097,7 @@ hipError_t enqueue_small(jpi_ctx* c, const float* table, const float* shift, int
   SmallRows r{};
   r.B = batch;
   r.S = S;
-  r.P = at ? c->prefix + 1 : c->prefix;
+  r.P = prefix_keys(c);
   r.h = c->h;
   r.ssq = c->ssq;
   r.u = c->y;
@@ -1199,7 +1204,7 @@ hipError_t enqueue_steps(jpi_ctx* c, const float* table, const float* shift, int
   // action rows see prefix_len + 1 keys there and start at position prefix_len + 1
   const bool at = c->cfg.variant == JPI_VARIANT_ACTION_TIME;
   const int* plen_act = at ? c->d_plen1 : c->d_prefix_len;
-  const int P_act = at ? prefix + 1 : prefix;
+  const int P_act = prefix_keys(c);
   const int nch = attn_n_chunks(c->dt, P_act, S);
   const float eps = c->cfg.rms_eps;
   const float dt_step = -1.0f / (float)n_steps;
@@ -1566,8 +1571,7 @@ jpi_status jpi_denoise(jpi_ctx* c, const float* noise_dev, int n_steps, float* a
   hipStream_t s = (hipStream_t)stream;
   float* table = nullptr;
   TRY(ensure_table(c, n_steps, s, &table));
-  // the action-time variant's action rows also see the state token's prefix slot
-  TRY(ensure_scratch(c, c->batch, c->prefix + (c->cfg.variant == JPI_VARIANT_ACTION_TIME ? 1 : 0)));
+  TRY(ensure_scratch(c, c->batch, prefix_keys(c)));
   const StepGemms plan = plan_gemms(c, c->batch);
   float* shift = nullptr;
   if (plan.persist || plan.small) TRY(ensure_frag(c, s));

@@ -9,6 +9,21 @@ import pytest
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2607_12659_amd", "csrc")
 
 PROGRAMS = {
+    # every prefix length that a binding accepts (action-time variant: below max_prefix) fits the bound, and the first
+    # block that a wave of the few-row attention reads without knowing the length lies in the rollout's blocks
+    "key_bound": """
+  for (int pmax = 1; pmax <= 1100; ++pmax)
+    for (int prefix = pmax > 70 ? pmax - 70 : 0; prefix <= pmax; ++prefix)
+      for (int at = 0; at < 2; ++at) {
+        const int bound = jpi::key_bound(prefix, pmax, at), longest = at ? (prefix < pmax ? prefix : pmax - 1) + 1 : prefix;
+        CHECK(bound >= longest && bound <= pmax);
+        for (int own = 1; own <= 2; ++own)
+          for (int jb0 = 0; jb0 < 32; ++jb0) {
+            const int last = own + jpi::kv_blocks(bound) - 1, first = jb0 < last ? jb0 : last;
+            CHECK(first - own < jpi::kv_blocks(pmax));
+          }
+      }
+""",
     # z holds the GeGLU output of every row and, in the action-time variant, the action-time MLP's W columns
     "z_columns": """
   for (size_t W = 64; W <= 4096; W += 64)

@@ -243,3 +243,26 @@ def test_action_time_mlp_narrower_than_the_expert(width, mlp, horizon, batch):
         ae.close()
     assert_bf16(got, opi0.denoise(wl.dims, w, noise, K, V, lens, wl.n_steps, st), "narrow MLP")
     assert np.array_equal(got, again)
+
+
+# every prefix slot bound (a hand-off in place has to), whole 32-key blocks, the longest length that leaves the state
+# token's slot free: the action rows see max_prefix keys and no block past them
+@pytest.mark.parametrize("width,heads,Dh,horizon,max_prefix,lens", [
+    (256, 4, 64, 10, 32, [31]), (256, 4, 64, 10, 64, [63, 5]), (1024, 8, 256, 50, 32, [31]), (1024, 8, 256, 50, 320, [319]),
+    (1024, 8, 256, 50, 320, [0, 319]), (1024, 8, 256, 50, 928, [927])])
+def test_action_time_full_prefix_of_whole_blocks(width, heads, Dh, horizon, max_prefix, lens):
+    torch_cuda()
+    d = synth.Dims(n_layers=2, width=width, n_heads=heads, n_kv_heads=1, head_dim=Dh, mlp_dim=2 * width, action_dim=7,
+                   horizon=horizon)
+    B = len(lens)
+    wl = synth.Workload("pi0-full", d, prefix=max_prefix, batch=B, n_steps=2, n_fixed=0, dtype="bf16", prefix_len=tuple(lens))
+    print("case pi0-full", width, max_prefix, lens, flush=True)
+    w = spi0.make_pi0_weights(wl)
+    K, V = synth.make_prefix(wl)
+    noise, st = synth.make_noise(wl), spi0.make_state(wl)
+    ae = _pi0_expert(wl, w, B, max_prefix)
+    try:
+        got = _pi0_run(ae, K, V, noise, wl.n_steps, lens, st)
+    finally:
+        ae.close()
+    assert_bf16(got, opi0.denoise(wl.dims, w, noise, K, V, lens, wl.n_steps, st), "full prefix")
