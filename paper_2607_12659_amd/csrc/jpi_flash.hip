@@ -422,7 +422,7 @@ __global__ __launch_bounds__(512) void k_flash(AttnLaunch a, int S, int nqt, int
         *reinterpret_cast<bf16x4*>(out + nt * 16) = bf16x4{static_cast<bf16>(v[0]), static_cast<bf16>(v[1]),
                                                            static_cast<bf16>(v[2]), static_cast<bf16>(v[3])};
       }
-      if (g == 0) ml[rowi] = float2{m_ref[rt], l};
+      if (g == 0) ml[rowi] = float2{m_ref[rt], m_ref[rt] == -INFINITY ? 0.f : l};
     }
   }
 }
@@ -435,7 +435,7 @@ __device__ __forceinline__ size_t attn_out_at(const AttnLaunch& a, int DH, int m
 }
 
 // out row (b, head, i) = sum_s 2^(m_s - m) l_s O_s / sum_s 2^(m_s - m) l_s, ranges in order; a
-// range without keys (m_s = -inf) is skipped.  Dh / 4 threads per query row, 4 dims each.  S is
+// range with m_s = -inf (no keys, or no weight: l_s = 0) is skipped unless l_s is NaN.  Dh / 4 threads per query row, 4 dims each.  S is
 // known when compiling, so that the loads of a row's partials are one round trip
 // (16 predicated ones took 7 us at three rollouts whatever S was).
 template <int DH, int S, typename TO>
@@ -462,7 +462,7 @@ __global__ __launch_bounds__(256) void k_flash_merge(AttnLaunch a, const bf16* p
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const bool some = mv[s].x != -INFINITY;
-    const float wl = some ? __builtin_amdgcn_exp2f(mv[s].x - m) * mv[s].y : 0.f;
+    const float wl = some ? __builtin_amdgcn_exp2f(mv[s].x - m) * mv[s].y : mv[s].y;
     const f32x4 v = f32x4{__builtin_bit_cast(float, ov[s][0] << 16), __builtin_bit_cast(float, ov[s][0] & 0xffff0000u),
                           __builtin_bit_cast(float, ov[s][1] << 16), __builtin_bit_cast(float, ov[s][1] & 0xffff0000u)};
     if (some) acc += wl * v;  // the partial of a range without keys is not written
@@ -644,8 +644,8 @@ __global__ __launch_bounds__(64 * ROWS_NW, 2) void k_flash_rows(AttnLaunch a, in
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
       for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sc[kt][e]);
-    mx = row4_max(mx) * qscale;  // finite: the block holds a valid key
-    const bool over = mx > m_ref + FLASH_LIMIT;  // always on the first block
+    mx = row4_max(mx) * qscale;  // -inf where every score is -inf or NaN (fmaxf drops a NaN)
+    const bool over = mx > m_ref + FLASH_LIMIT;  // always on the first block with another score
     if (__any(over)) {
       const float f = over ? __builtin_amdgcn_exp2f(m_ref - mx) : 1.f;
       l *= f;
@@ -655,10 +655,12 @@ __global__ __launch_bounds__(64 * ROWS_NW, 2) void k_flash_rows(AttnLaunch a, in
     }
     MF::frag pb;
     float sum = 0.f;
+    // a row without a reference yet: scores of -inf give 0 and NaN stays NaN, in the sum and in the output
+    const float ref = m_ref == -INFINITY ? 0.f : m_ref;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const bf16 lo = static_cast<bf16>(__builtin_amdgcn_exp2f(fmaf(sc[0][e], qscale, -m_ref)));
-      const bf16 hi = static_cast<bf16>(__builtin_amdgcn_exp2f(fmaf(sc[1][e], qscale, -m_ref)));
+      const bf16 lo = static_cast<bf16>(__builtin_amdgcn_exp2f(fmaf(sc[0][e], qscale, -ref)));
+      const bf16 hi = static_cast<bf16>(__builtin_amdgcn_exp2f(fmaf(sc[1][e], qscale, -ref)));
       pb[e] = lo;
       pb[4 + e] = hi;
       sum += static_cast<float>(lo) + static_cast<float>(hi);
@@ -670,7 +672,13 @@ __global__ __launch_bounds__(64 * ROWS_NW, 2) void k_flash_rows(AttnLaunch a, in
     load_v(next);
   }
 
-  // the waves' outputs against one reference per row: the largest
+  const int r = row0 + fr;
+  if (split * NW >= nb) {  // a range without keys (S > 1), the same for every row: skipped by the merge
+    if (w == 0 && g == 0 && r < R) ml[((size_t)split * a.B + b) * R + r] = float2{-INFINITY, 0.f};
+    return;
+  }
+  // the waves' outputs against one reference per row: the largest.  Where there is none (every score of the
+  // range -inf or NaN) the sum is 0 or NaN: with one range the quotient below is NaN, with several the merge decides.
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
   if (g == 0) mls[w][fr] = float2{m_ref, l};
@@ -681,11 +689,9 @@ __global__ __launch_bounds__(64 * ROWS_NW, 2) void k_flash_rows(AttnLaunch a, in
 #pragma unroll
   for (int v = 0; v < NW; ++v) {
     const float2 t = mls[v][fr];
-    lsum += t.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(t.x - m) * t.y;
+    lsum += t.x == -INFINITY ? t.y : __builtin_amdgcn_exp2f(t.x - m) * t.y;
   }
-  const int r = row0 + fr;
   if (S > 1 && w == 0 && g == 0 && r < R) ml[((size_t)split * a.B + b) * R + r] = float2{m, lsum};
-  if (m == -INFINITY) return;  // a range without keys (the same for every row): skipped by the merge
   const float f = (m_ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref - m)) / lsum;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) red[w][nt][lane] = o[nt] * f;

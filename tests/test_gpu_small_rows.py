@@ -164,3 +164,94 @@ def test_correction_rows_match_oracle(batch, n_actions, tokens):
             assert abs(float(conf[b]) - f_o) <= 2e-2 * np.abs(oracle.widen(w["conf_head.w"])[0]).sum()
     finally:
         m.close()
+
+
+def _wide(B, lens, nH=1, Dh=256, horizon=20):
+    """One layer, one step: a row's attention output reaches that row's action only."""
+    d = synth.Dims(n_layers=1, width=512, n_heads=nH, n_kv_heads=1, head_dim=Dh, mlp_dim=512, action_dim=7, horizon=horizon)
+    return synth.Workload("special", d, prefix=max(lens), batch=B, n_steps=1, n_fixed=0, dtype="bf16", prefix_len=tuple(lens),
+                          mod_gain=8.0)
+
+
+# key ranges of a 16-row tile by the rule: eight, four, two and one (short prefix, and many rollouts)
+RANGES = [(1, [900]), (1, [500]), (1, [150]), (1, [20]), (25, [300])]
+
+
+@pytest.mark.parametrize("B,lens", RANGES)
+@pytest.mark.parametrize("what", ["query", "scale", "keys"])
+def test_small_rows_keep_nan(B, lens, what):
+    """A NaN in the query weights, in a modulation or in every prefix key makes every action of the rollout NaN
+    (fmaxf drops a NaN score, so a row with nothing else has no maximum)."""
+    wl = _wide(B, lens * B)
+    inp = Inputs(wl)
+    print("case NaN", what, B, lens, flush=True)
+    ae = make_expert(wl, inp.weights)
+    try:
+        clean = run(ae, inp.K, inp.V, inp.noise, 1, prefix_len=inp.prefix_len)
+        assert np.isfinite(clean).all()
+        K = inp.K.copy()
+        if what == "keys":
+            K[:, 0] = 0x7fc0  # rollout 0
+        else:
+            name = "layers.0.q.w" if what == "query" else "layers.0.attn_mod.w"
+            bad = inp.weights[name].copy()
+            bad[0, 0] = 0x7fc0
+            ae.load_weights({**inp.weights, name: bad})
+        got = run(ae, K, inp.V, inp.noise, 1, prefix_len=inp.prefix_len)
+    finally:
+        ae.close()
+    assert np.isnan(got[0]).all()
+    if what == "keys":
+        assert np.array_equal(got[1:], clean[1:])
+    else:
+        assert np.isnan(got).all()
+
+
+@pytest.mark.parametrize("B,lens", RANGES)
+@pytest.mark.parametrize("first,step", [(0, 1), (3, 1), (0, 2)])
+def test_small_rows_infinite_scores(B, lens, first, step):
+    """Prefix keys of infinite magnitude in one dimension (all, all but three, every other one): a row whose query is
+    positive there gives them no weight, a negative one has no answer (NaN)."""
+    wl = _wide(B, lens * B)
+    inp = Inputs(wl)
+    K = inp.K.copy()
+    K[0, 0, first::step, 5] = 0xff80  # -inf, rollout 0
+    print("case infinite scores", B, lens, first, step, flush=True)
+    ae = make_expert(wl, inp.weights)
+    try:
+        got = run(ae, K, inp.V, inp.noise, 1, prefix_len=inp.prefix_len)
+    finally:
+        ae.close()
+    with np.errstate(invalid="ignore"):
+        ref = oracle.denoise(oracle.Expert(wl.dims, inp.weights), inp.noise, K, inp.V, inp.prefix_len, 1)
+    bad = np.isnan(ref).any(axis=2)
+    assert bad[0].any() and not bad[0].all() and not bad[1:].any()
+    assert np.array_equal(np.isnan(got).all(axis=2), bad) and np.array_equal(np.isnan(got).any(axis=2), bad)
+    ok = ~bad
+    err = np.linalg.norm(got[ok] - ref[ok]) / np.linalg.norm(ref[ok])
+    assert err <= REL, err
+
+
+@pytest.mark.parametrize("B,lens", RANGES)
+def test_small_rows_without_any_finite_score(B, lens):
+    """Every score of every row overflows to -inf, its own keys' included: no answer, and none left from the call before."""
+    wl = _wide(B, lens * B)
+    inp = Inputs(wl)
+    W, up, down = wl.dims.width, synth.f32_to_bf16_bits(np.float32([1e20]))[0], synth.f32_to_bf16_bits(np.float32([-1e20]))[0]
+    w = {k: v.copy() for k, v in inp.weights.items()}
+    # y = 1 in every column (scale -1, shift 1); q is 1e20 and k -1e20 in the dimension that rotates least
+    w["layers.0.attn_mod.w"][:] = 0
+    w["layers.0.attn_mod.b"][:] = np.repeat(np.float32([-1, 1, 1]), W)
+    K = inp.K.copy()
+    K[:], K[..., 127] = 0, down
+    for name, v in (("q.w", up), ("k.w", down)):
+        w["layers.0." + name][:] = 0
+        w["layers.0." + name][127, 0] = v
+    print("case no finite score", B, lens, flush=True)
+    ae = make_expert(wl, inp.weights)
+    try:
+        assert np.isfinite(run(ae, inp.K, inp.V, inp.noise, 1, prefix_len=inp.prefix_len)).all()
+        ae.load_weights(w)
+        assert np.isnan(run(ae, K, inp.V, inp.noise, 1, prefix_len=inp.prefix_len)).all()
+    finally:
+        ae.close()
