@@ -848,12 +848,13 @@ bool use_persist(jpi_ctx* c, int batch) {
 // launch), 3 rollouts 9.5 against 11.3 and 8 (400 rows) 11.1 against 13.1 (eight launches per layer); the tiny bf16 expert,
 // 4 rollouts, 10 steps 0.59 against 0.91 (single launch).  Past 512 rows the
 // tiles of the eight-launch layers share their operands better.
-// JPI_PERSIST=1 and a wait bound set for its test ask for the single-launch kernel, which
-// otherwise serves widths that are not a multiple of 256.
+// JPI_PERSIST=1 and a wait bound set for its test ask for the single-launch kernel, JPI_PERSIST=0 for the
+// eight-launch layers.  The single-launch kernel also serves the shapes of at most 64 rows that it supports
+// and these layers do not.
 constexpr int SMALL_ROWS = 512;
 bool use_small(const jpi_ctx* c, int batch) {
   const char* e = getenv("JPI_PERSIST");
-  if ((e && e[0] == '1') || c->persist_spin != 0) return false;
+  if ((e && (e[0] == '0' || e[0] == '1')) || c->persist_spin != 0) return false;
   return c->kvf && batch * (c->H + c->n_corr) <= SMALL_ROWS;
 }
 

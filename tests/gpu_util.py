@@ -1,6 +1,7 @@
 """Helpers shared by the GPU tests: run a workload through the C ABI."""
 from __future__ import annotations
 
+import contextlib
 import json
 import os
 
@@ -53,20 +54,39 @@ def run(ae, K, V, noise, n_steps, prefix_len=None, committed=None, n_fixed=0, co
     return out.cpu().numpy().astype(np.float64)
 
 
-def run_env(ae, env, *args, **kw):
-    """run() with JPI_PERSIST set to env ("0" forces the multi-kernel path, None the default choice)."""
-    old = os.environ.get("JPI_PERSIST")
-    if env is None:
-        os.environ.pop("JPI_PERSIST", None)
-    else:
+@contextlib.contextmanager
+def path_env(env):
+    """JPI_PERSIST set to env: "1" the single-launch kernel, "0" the eight-launch layers, None the default choice (bf16
+    with at most 512 rows and widths of whole 256 columns up to 1024: the five-launch layers)."""
+    old = os.environ.pop("JPI_PERSIST", None)
+    if env is not None:
         os.environ["JPI_PERSIST"] = env
     try:
-        return run(ae, *args, **kw)
+        yield
     finally:
-        if old is None:
-            os.environ.pop("JPI_PERSIST", None)
-        else:
+        os.environ.pop("JPI_PERSIST", None)
+        if old is not None:
             os.environ["JPI_PERSIST"] = old
+
+
+def run_env(ae, env, *args, **kw):
+    """run() on the path that env chooses (path_env)."""
+    with path_env(env):
+        return run(ae, *args, **kw)
+
+
+def single_launches(ae, noise, n_steps):
+    """Launches of the single-launch kernel in one denoise of the bound state."""
+    torch = torch_cuda()
+    from paper_2607_12659_amd import jpi
+    assert jpi.jpi_debug_time_kernel(ae.ctx, jpi.JPI_KERNEL_PERSISTENT) == jpi.JPI_OK
+    ae.denoise(noise, n_steps)
+    ae.sync()
+    torch.cuda.synchronize()
+    st, _, n = jpi.jpi_debug_kernel_time(ae.ctx)
+    assert st == jpi.JPI_OK
+    assert jpi.jpi_debug_time_kernel(ae.ctx, jpi.JPI_KERNEL_NONE) == jpi.JPI_OK
+    return n
 
 
 def load_golden(name):

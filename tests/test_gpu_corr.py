@@ -84,9 +84,10 @@ def test_tiny_expert_rejects_too_many_correction_tokens():
 
 def test_pi05_committed10_with_correction_item():
     """The pi0.5 expert at full size with the 4-token correction item and the
-    10 committed rows of one scheduler iteration (54 suffix rows: the
-    single-launch kernel), against the stored oracle output and the
-    multi-kernel path; the call without the item is unchanged after."""
+    10 committed rows of one scheduler iteration (54 suffix rows), on the
+    default path, in the single-launch kernel and on the eight-launch layers,
+    against the stored oracle output; the call without the item is unchanged
+    after."""
     torch_cuda()
     wl = synth.WORKLOADS["pi05-b1-committed10"]
     print("case pi05-b1-committed10-corr4", flush=True)
@@ -99,12 +100,14 @@ def test_pi05_committed10_with_correction_item():
     try:
         before = run(ae, K, V, noise, wl.n_steps, committed=com, n_fixed=10)
         got = run(ae, K, V, noise, wl.n_steps, committed=com, n_fixed=10, corr=corr)
+        single = run_env(ae, "1", K, V, noise, wl.n_steps, committed=com, n_fixed=10, corr=corr)
         multi = run_env(ae, "0", K, V, noise, wl.n_steps, committed=com, n_fixed=10, corr=corr)
+        assert not np.array_equal(single, multi) and not np.array_equal(single, got) and not np.array_equal(multi, got)
         ref, meta = load_golden("pi05-b1-committed10-corr4")
         assert meta["n_corr"] == 4
         plain, _ = load_golden("pi05-b1-committed10")
         effect = rel_l2_per_rollout(plain, ref)
-        for label, out in (("single-launch", got), ("multi-kernel", multi)):
+        for label, out in (("default", got), ("single-launch", single), ("multi-kernel", multi)):
             rel = rel_l2_per_rollout(out, ref)
             print("%s: rel-L2 %.3e max-abs %.3e; the item moves the actions by %.3e"
                   % (label, rel, np.abs(out - ref).max(), effect), flush=True)
@@ -132,9 +135,9 @@ def test_persistent_tiny_bf16_correction_rows_batched():
     ae = make_expert(wl, w, max_batch=2, max_prefix=wl.prefix, max_corr=4)
     try:
         kw = dict(prefix_len=lens, committed=com, n_fixed=2, corr=corr)
-        got = run_env(ae, None, K, V, noise, wl.n_steps, **kw)
+        got = run_env(ae, "1", K, V, noise, wl.n_steps, **kw)
         multi = run_env(ae, "0", K, V, noise, wl.n_steps, **kw)
-        again = run_env(ae, None, K, V, noise, wl.n_steps, **kw)
+        again = run_env(ae, "1", K, V, noise, wl.n_steps, **kw)
     finally:
         ae.close()
     ref = oracle.denoise(oracle.Expert(wl.dims, w), noise, K, V, lens, wl.n_steps, committed=com, n_fixed=2,
@@ -142,7 +145,8 @@ def test_persistent_tiny_bf16_correction_rows_batched():
     rel = rel_l2_per_rollout(got, ref)
     print("single-launch rel-L2 %.3e, vs multi-kernel %.3e" % (rel, rel_l2_per_rollout(got, multi)), flush=True)
     assert_bf16(got, ref, "single-launch")
-    assert rel_l2_per_rollout(got, multi) <= 5e-3
+    assert_bf16(multi, ref, "multi-kernel")
+    assert rel_l2_per_rollout(got, multi) <= 5e-3 and not np.array_equal(got, multi)
     assert np.array_equal(got, again)
     assert np.array_equal(got[:, :2].astype(np.float32), com)
 
@@ -275,10 +279,11 @@ def test_correction_item_into_the_expert():
         m.close()
 
 
-def test_tiny_bf16_batch8_correction_rows_multikernel():
-    """Eight rollouts of 4 correction + 10 action rows (112 rows: the
-    multi-kernel path with several query tiles per rollout group), ragged
-    prefixes including an empty one, committed rows, against the oracle."""
+@pytest.mark.parametrize("path", ["0", None], ids=["eight-launch", "five-launch"])
+def test_tiny_bf16_batch8_correction_rows_multikernel(path):
+    """Eight rollouts of 4 correction + 10 action rows (112 rows, several
+    query tiles per rollout), ragged prefixes including an empty one,
+    committed rows, against the oracle."""
     torch_cuda()
     wl = synth.WORKLOADS["tiny-fp32"].with_(dtype="bf16", batch=8, n_fixed=1, name="tiny-bf16-corr-b8")
     lens = [64, 0, 17, 64, 1, 33, 63, 8]
@@ -287,7 +292,7 @@ def test_tiny_bf16_batch8_correction_rows_multikernel():
     com = synth.make_committed(wl)
     ae = make_expert(wl, w, max_batch=8, max_prefix=wl.prefix, max_corr=4)
     try:
-        got = run(ae, K, V, noise, wl.n_steps, prefix_len=lens, committed=com, n_fixed=1, corr=corr)
+        got = run_env(ae, path, K, V, noise, wl.n_steps, prefix_len=lens, committed=com, n_fixed=1, corr=corr)
     finally:
         ae.close()
     ref = oracle.denoise(oracle.Expert(wl.dims, w), noise, K, V, lens, wl.n_steps, committed=com, n_fixed=1,

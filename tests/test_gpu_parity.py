@@ -17,8 +17,8 @@ import pytest
 
 import oracle
 import synth
-from gpu_util import (Inputs, assert_bf16, load_golden, make_expert, rel_l2_per_rollout, run, run_env,
-                      torch_cuda)
+from gpu_util import (Inputs, assert_bf16, load_golden, make_expert, path_env, rel_l2_per_rollout, run, run_env,
+                      single_launches, torch_cuda)
 
 pytestmark = pytest.mark.gpu
 
@@ -159,7 +159,7 @@ def test_pi05_b1(pi05):
     assert np.array_equal(got, run(ae, K, V, noise, wl.n_steps))
 
 
-@pytest.mark.parametrize("path", [None, "0"], ids=["single-launch", "multi-kernel"])
+@pytest.mark.parametrize("path", [None, "1", "0"], ids=["five-launch", "single-launch", "eight-launch"])
 def test_pi05_b1_amplified_gates(path):
     """The pi0.5 shape with every layer's modulation tensors x 8 (gates near
     0.5): each sublayer, attention included, now moves the actions by far more
@@ -170,7 +170,7 @@ def test_pi05_b1_amplified_gates(path):
     torch_cuda()
     ref, meta = load_golden("pi05-b1-amp8")
     wl = synth.WORKLOADS["pi05-b1"].with_(mod_gain=8.0, name="pi05-b1-amp8")
-    print("case pi05-b1-amp8 path %s" % ("default" if path is None else "multi-kernel"), flush=True)
+    print("case pi05-b1-amp8 JPI_PERSIST %s" % path, flush=True)
     inp = Inputs(wl)
     ae = make_expert(wl, inp.weights)
     try:
@@ -256,7 +256,8 @@ def test_pi05_fp32_shape_at_1e4():
 
 
 # ---------------------------------------------------------------------------
-# single-launch (persistent) path: batch * horizon <= 64 with bf16 weights
+# the three bf16 paths of few rows: the single-launch (persistent) kernel
+# (JPI_PERSIST=1), the eight-launch layers (JPI_PERSIST=0) and the default
 # ---------------------------------------------------------------------------
 def test_persistent_tiny_bf16_batched_ragged_committed():
     torch_cuda()
@@ -265,17 +266,20 @@ def test_persistent_tiny_bf16_batched_ragged_committed():
     inp = Inputs(wl)
     ae = make_expert(wl, inp.weights)
     try:
-        got = run_env(ae, None, inp.K, inp.V, inp.noise, wl.n_steps, prefix_len=inp.prefix_len,
-                       committed=inp.committed, n_fixed=2)
-        multi = run_env(ae, "0", inp.K, inp.V, inp.noise, wl.n_steps, prefix_len=inp.prefix_len,
-                         committed=inp.committed, n_fixed=2)
+        kw = dict(prefix_len=inp.prefix_len, committed=inp.committed, n_fixed=2)
+        got = run_env(ae, "1", inp.K, inp.V, inp.noise, wl.n_steps, **kw)
+        multi = run_env(ae, "0", inp.K, inp.V, inp.noise, wl.n_steps, **kw)
+        default = run_env(ae, None, inp.K, inp.V, inp.noise, wl.n_steps, **kw)
     finally:
         ae.close()
     ref = _oracle(wl, inp, committed=inp.committed, n_fixed=2)
     print("tiny-bf16-b3 persistent vs multi-kernel path %.3e" % rel_l2_per_rollout(got, multi))
     assert_bf16(got, ref, "tiny-bf16-b3 persistent", reg_rel=2e-3)
     assert_bf16(multi, ref, "tiny-bf16-b3 multi-kernel", reg_rel=2e-3)
+    assert_bf16(default, ref, "tiny-bf16-b3 five-launch", reg_rel=2e-3)
     assert rel_l2_per_rollout(got, multi) <= 5e-3
+    # three paths that round in different places
+    assert not np.array_equal(got, multi) and not np.array_equal(got, default) and not np.array_equal(multi, default)
     assert np.array_equal(got[:, :2].astype(np.float32), inp.committed.astype(np.float32))
 
 
@@ -284,15 +288,59 @@ def test_persistent_matches_multikernel_pi05(pi05):
     wl = synth.WORKLOADS["pi05-b1"]
     K, V = synth.make_prefix(wl)
     noise = synth.make_noise(wl)
-    a = run_env(ae, None, K, V, noise, 2)
+    a = run_env(ae, "1", K, V, noise, 2)
     b = run_env(ae, "0", K, V, noise, 2)
-    print("pi05 2-step: persistent vs multi-kernel rel-L2 %.3e" % rel_l2_per_rollout(a, b))
-    assert rel_l2_per_rollout(a, b) <= 5e-3
+    c = run_env(ae, None, K, V, noise, 2)
+    print("pi05 2-step: persistent vs multi-kernel rel-L2 %.3e, five-launch vs multi-kernel %.3e"
+          % (rel_l2_per_rollout(a, b), rel_l2_per_rollout(c, b)))
+    assert rel_l2_per_rollout(a, b) <= 5e-3 and rel_l2_per_rollout(c, b) <= 5e-3
+    assert not np.array_equal(a, b) and not np.array_equal(a, c) and not np.array_equal(b, c)
     # graph replay determinism of the single-launch kernel
-    assert np.array_equal(a, run_env(ae, None, K, V, noise, 2))
+    assert np.array_equal(a, run_env(ae, "1", K, V, noise, 2))
 
 
-def test_persistent_repeated_calls_bitwise(pi05):
+@pytest.mark.parametrize("env,kernels", [("1", 1), ("0", 0), (None, 0)])
+def test_which_path_runs_the_single_launch_kernel(env, kernels):
+    from paper_2607_12659_amd.expert import to_device
+    torch_cuda()
+    wl = synth.WORKLOADS["tiny-fp32"].with_(dtype="bf16", name="tiny-bf16")
+    inp = Inputs(wl)
+    ae = make_expert(wl, inp.weights)
+    try:
+        run(ae, inp.K, inp.V, inp.noise, wl.n_steps)
+        with path_env(env):
+            assert single_launches(ae, to_device(np.ascontiguousarray(inp.noise, np.float32)), wl.n_steps) == kernels
+    finally:
+        ae.close()
+
+
+@pytest.mark.parametrize("width,heads,mlp", [(1280, 4, 256), (2048, 4, 512), (256, 2, 128)])
+def test_shapes_that_take_the_single_launch_kernel_by_default(width, heads, mlp):
+    """Few rows, multiples of 128, but a width past 1024 or an MLP or head part that is no multiple of 256."""
+    from paper_2607_12659_amd.expert import to_device
+    torch_cuda()
+    d = synth.Dims(n_layers=2, width=width, n_heads=heads, n_kv_heads=1, head_dim=64, mlp_dim=mlp, action_dim=7, horizon=10)
+    wl = synth.Workload("wide", d, prefix=33, batch=3, n_steps=2, n_fixed=2, dtype="bf16", prefix_len=(33, 0, 7))
+    inp = Inputs(wl)
+    print("case single-launch by default", width, heads, mlp, flush=True)
+    ae = make_expert(wl, inp.weights)
+    try:
+        kw = dict(prefix_len=inp.prefix_len, committed=inp.committed, n_fixed=2)
+        got = run_env(ae, None, inp.K, inp.V, inp.noise, wl.n_steps, **kw)
+        # (the eight-launch layers' products of few rows take contractions of whole 256 columns)
+        multi = run_env(ae, "0", inp.K, inp.V, inp.noise, wl.n_steps, **kw) if mlp % 256 == 0 else None
+        with path_env(None):
+            assert single_launches(ae, to_device(np.ascontiguousarray(inp.noise, np.float32)), wl.n_steps) == 1
+    finally:
+        ae.close()
+    ref = _oracle(wl, inp, committed=inp.committed, n_fixed=2)
+    assert_bf16(got, ref, "single-launch", reg_rel=4e-3)
+    if multi is not None:
+        assert_bf16(multi, ref, "eight-launch", reg_rel=4e-3)
+
+
+@pytest.mark.parametrize("path", ["1", None], ids=["single-launch", "five-launch"])
+def test_persistent_repeated_calls_bitwise(pi05, path):
     """The single-launch kernel orders its phases with per-workgroup completion
     flags (each consumer waits only for its producers).  A missing dependency
     would show as run-to-run variation, so repeated calls on two alternating
@@ -304,21 +352,23 @@ def test_persistent_repeated_calls_bitwise(pi05):
     K, V = synth.make_prefix(wl)
     n1 = synth.make_noise(wl)
     n2 = np.ascontiguousarray(-n1[:, ::-1])
-    ref1 = run(ae, K, V, n1, wl.n_steps)
-    ref2 = run(ae, K, V, n2, wl.n_steps)
+    ref1 = run_env(ae, path, K, V, n1, wl.n_steps)
+    ref2 = run_env(ae, path, K, V, n2, wl.n_steps)
     assert not np.array_equal(ref1, ref2)
     d1 = to_device(np.ascontiguousarray(n1, np.float32))
     d2 = to_device(np.ascontiguousarray(n2, np.float32))
     print("case pi05-b1 x 24 alternating calls", flush=True)
     for i in range(12):
         for d, ref in ((d1, ref1), (d2, ref2)):
-            out = ae.denoise(d, wl.n_steps)
+            with path_env(path):
+                out = ae.denoise(d, wl.n_steps)
             ae.sync()
             torch.cuda.synchronize()
             assert np.array_equal(out.cpu().numpy().astype(np.float64), ref), "call %d differs" % i
 
 
-def test_persistent_tiny_bf16_repeated_calls_bitwise():
+@pytest.mark.parametrize("path", ["1", None], ids=["single-launch", "five-launch"])
+def test_persistent_tiny_bf16_repeated_calls_bitwise(path):
     """Ragged batch of three with committed rows: many short calls in a row."""
     torch = torch_cuda()
     wl = synth.WORKLOADS["tiny-fp32"].with_(dtype="bf16", batch=3, n_fixed=2, prefix_len=(64, 5, 41),
@@ -326,13 +376,14 @@ def test_persistent_tiny_bf16_repeated_calls_bitwise():
     inp = Inputs(wl)
     ae = make_expert(wl, inp.weights)
     try:
-        ref = run(ae, inp.K, inp.V, inp.noise, wl.n_steps, prefix_len=inp.prefix_len,
-                  committed=inp.committed, n_fixed=2)
+        ref = run_env(ae, path, inp.K, inp.V, inp.noise, wl.n_steps, prefix_len=inp.prefix_len,
+                      committed=inp.committed, n_fixed=2)
         from paper_2607_12659_amd.expert import to_device
         d = to_device(np.ascontiguousarray(inp.noise, np.float32))
         print("case tiny-bf16-b3 x 40 calls", flush=True)
         for i in range(40):
-            out = ae.denoise(d, wl.n_steps)
+            with path_env(path):
+                out = ae.denoise(d, wl.n_steps)
             ae.sync()
             torch.cuda.synchronize()
             assert np.array_equal(out.cpu().numpy().astype(np.float64), ref), "call %d differs" % i
@@ -353,8 +404,8 @@ def test_persistent_wait_timeout_is_reported_and_recovers():
     inp = Inputs(wl)
     ae = make_expert(wl, inp.weights)
     try:
-        ref = run(ae, inp.K, inp.V, inp.noise, wl.n_steps, prefix_len=inp.prefix_len,
-                  committed=inp.committed, n_fixed=2)
+        ref = run_env(ae, "1", inp.K, inp.V, inp.noise, wl.n_steps, prefix_len=inp.prefix_len,
+                      committed=inp.committed, n_fixed=2)
         d = to_device(np.ascontiguousarray(inp.noise, np.float32))
         print("case tiny-bf16-b3 with a one-poll wait bound", flush=True)
         assert jpi.jpi_debug_set_spin_limit(ae.ctx, 1) == jpi.JPI_OK
@@ -363,7 +414,8 @@ def test_persistent_wait_timeout_is_reported_and_recovers():
             ae.sync()
         torch.cuda.synchronize()
         assert jpi.jpi_debug_set_spin_limit(ae.ctx, 0) == jpi.JPI_OK
-        out = ae.denoise(d, wl.n_steps)
+        with path_env("1"):
+            out = ae.denoise(d, wl.n_steps)
         ae.sync()
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy().astype(np.float64), ref)

@@ -92,7 +92,7 @@ def test_small_rows_after_longer_rows():
 
 @pytest.mark.parametrize("shape,batch", [("w256", 3), ("w1024", 1)])
 def test_single_launch_kernel_still_matches(shape, batch):
-    """JPI_PERSIST=1 asks for the single-launch kernel; the two agree within the bf16 bars."""
+    """JPI_PERSIST=1 asks for the single-launch kernel, held to the same bars."""
     wl, inp, _ = _case(shape, batch)
     ae = make_expert(wl, inp.weights)
     try:

@@ -1,11 +1,11 @@
 """The committed-rows-at-t=0 variant (jpi_set_committed_t0) against the fp64
-oracle, on both denoise paths.  Same bars as the denoise parity."""
+oracle, on every denoise path.  Same bars as the denoise parity."""
 import numpy as np
 import pytest
 
 import oracle
 import synth
-from gpu_util import Inputs, assert_bf16, load_golden, make_expert, rel_l2_per_rollout, run_env, torch_cuda
+from gpu_util import Inputs, assert_bf16, load_golden, make_expert, path_env, rel_l2_per_rollout, run_env, torch_cuda
 from synth import correction as sc
 
 pytestmark = pytest.mark.gpu
@@ -34,6 +34,7 @@ def test_tiny_committed_rows_at_t0(dtype, n_corr):
         base = run_env(ae, None, inp.K, inp.V, inp.noise, wl.n_steps, **kw)
         ae.set_committed_t0(True)
         got = run_env(ae, None, inp.K, inp.V, inp.noise, wl.n_steps, **kw)
+        single = run_env(ae, "1", inp.K, inp.V, inp.noise, wl.n_steps, **kw)
         multi = run_env(ae, "0", inp.K, inp.V, inp.noise, wl.n_steps, **kw)
         ae.set_committed_t0(False)
         back = run_env(ae, None, inp.K, inp.V, inp.noise, wl.n_steps, **kw)
@@ -50,9 +51,11 @@ def test_tiny_committed_rows_at_t0(dtype, n_corr):
     if dtype == "f32":
         assert err <= F32_TOL
     else:
-        assert_bf16(got, ref, "single-launch")
+        assert_bf16(got, ref, "five-launch")
+        assert_bf16(single, ref, "single-launch")
         assert_bf16(multi, ref, "multi-kernel")
-        assert rel_l2_per_rollout(got, multi) <= 5e-3
+        assert rel_l2_per_rollout(got, multi) <= 5e-3 and rel_l2_per_rollout(single, multi) <= 5e-3
+        assert not np.array_equal(single, multi) and not np.array_equal(got, multi) and not np.array_equal(got, single)
     assert np.abs(ref - ref0).max() > 20 * max(err, 1e-6)  # the variant is far outside the error
     assert np.array_equal(got[:, :3].astype(np.float32), inp.committed.astype(np.float32))
     assert np.array_equal(base, back)
@@ -60,7 +63,7 @@ def test_tiny_committed_rows_at_t0(dtype, n_corr):
 
 def test_pi05_committed10_at_t0():
     """pi0.5, one rollout, 10 committed rows at t = 0, against the stored
-    oracle output on the single-launch and the multi-kernel path.  (With the
+    oracle output on the default, the single-launch and the eight-launch path.  (With the
     N(0, 0.02) time MLP the variant moves these actions by only ~6e-4, so the
     tiny tests carry the discrimination.)"""
     torch_cuda()
@@ -74,21 +77,24 @@ def test_pi05_committed10_at_t0():
     try:
         ae.set_committed_t0(True)
         got = run_env(ae, None, K, V, noise, wl.n_steps, committed=com, n_fixed=10)
+        single = run_env(ae, "1", K, V, noise, wl.n_steps, committed=com, n_fixed=10)
         multi = run_env(ae, "0", K, V, noise, wl.n_steps, committed=com, n_fixed=10)
         again = run_env(ae, None, K, V, noise, wl.n_steps, committed=com, n_fixed=10)
+        again1 = run_env(ae, "1", K, V, noise, wl.n_steps, committed=com, n_fixed=10)
     finally:
         ae.close()
     ref, meta = load_golden("pi05-b1-committed10-t0")
     assert meta["committed_t0"] is True
     plain, _ = load_golden("pi05-b1-committed10")
     effect = rel_l2_per_rollout(plain, ref)
-    for label, out in (("single-launch", got), ("multi-kernel", multi)):
+    for label, out in (("five-launch", got), ("single-launch", single), ("multi-kernel", multi)):
         rel = rel_l2_per_rollout(out, ref)
         print("%s: rel-L2 %.3e max-abs %.3e; the variant moves the actions by %.3e"
               % (label, rel, np.abs(out - ref).max(), effect), flush=True)
         assert_bf16(out, ref, label, reg_rel=2e-3, reg_abs=1e-2)
         assert np.array_equal(out[:, :10].astype(np.float32), com)
-    assert np.array_equal(got, again)
+    assert np.array_equal(got, again) and np.array_equal(single, again1)
+    assert not np.array_equal(single, multi) and not np.array_equal(got, multi) and not np.array_equal(got, single)
 
 
 # ---------------------------------------------------------------------------
@@ -108,19 +114,10 @@ def _pi0_expert(wl, w, max_batch, max_prefix, state_dim=spi0.STATE_DIM):
 
 
 def _pi0_run(ae, K, V, noise, n_steps, lens, state, committed=None, n_fixed=0, persist=None):
-    """persist: None (default path choice) or "0" (force the multi-kernel path)."""
-    import os
+    """persist: None (the default path), "1" (a single launch per step) or "0" (the eight-launch layers)."""
     from paper_2607_12659_amd.expert import to_device
-    torch = torch_cuda()
-    old = os.environ.pop("JPI_PERSIST", None)
-    if persist is not None:
-        os.environ["JPI_PERSIST"] = persist
-    try:
-        return _pi0_run_now(ae, K, V, noise, n_steps, lens, state, committed, n_fixed, to_device, torch)
-    finally:
-        os.environ.pop("JPI_PERSIST", None)
-        if old is not None:
-            os.environ["JPI_PERSIST"] = old
+    with path_env(persist):
+        return _pi0_run_now(ae, K, V, noise, n_steps, lens, state, committed, n_fixed, to_device, torch_cuda())
 
 
 def _pi0_run_now(ae, K, V, noise, n_steps, lens, state, committed, n_fixed, to_device, torch):
@@ -150,6 +147,7 @@ def test_tiny_action_time_variant(dtype):
         got = _pi0_run(ae, K, V, noise, wl.n_steps, lens, st, com, 2)
         again = _pi0_run(ae, K, V, noise, wl.n_steps, lens, st, com, 2)
         moved = _pi0_run(ae, K, V, noise, wl.n_steps, lens, st * 3.0, com, 2)
+        single = _pi0_run(ae, K, V, noise, wl.n_steps, lens, st, com, 2, persist="1")
         multi = _pi0_run(ae, K, V, noise, wl.n_steps, lens, st, com, 2, persist="0")
     finally:
         ae.close()
@@ -163,15 +161,16 @@ def test_tiny_action_time_variant(dtype):
         assert err <= F32_TOL
         assert np.abs(moved - ref3).max() <= F32_TOL
     else:
-        # bf16 with 2 x 10 rows runs the single-launch kernel once per step
-        assert_bf16(got, ref, "single-launch steps")
-        assert_bf16(moved, ref3, "single-launch steps, state x 3")
+        assert_bf16(got, ref, "five-launch")
+        assert_bf16(moved, ref3, "five-launch, state x 3")
         # with these N(0, 0.1) weights each path is ~6e-3 from the oracle in bf16, so the
-        # two paths are held to the same bar against each other as against the oracle
+        # paths are held to the same bar against each other as against the oracle
         print("single-launch steps vs multi-kernel rel-L2 %.3e; multi-kernel vs oracle %.3e"
-              % (rel_l2_per_rollout(got, multi), rel_l2_per_rollout(multi, ref)), flush=True)
+              % (rel_l2_per_rollout(single, multi), rel_l2_per_rollout(multi, ref)), flush=True)
+        assert_bf16(single, ref, "single-launch steps")
         assert_bf16(multi, ref, "multi-kernel")
-        assert rel_l2_per_rollout(got, multi) <= BF16_TOL
+        assert rel_l2_per_rollout(got, multi) <= BF16_TOL and rel_l2_per_rollout(single, multi) <= BF16_TOL
+        assert not np.array_equal(single, multi) and not np.array_equal(got, multi) and not np.array_equal(got, single)
     assert effect > 20 * max(err, 1e-6)
     assert np.array_equal(got, again)
     assert np.array_equal(got[:, :2].astype(np.float32), com.astype(np.float32))
@@ -213,11 +212,14 @@ def test_pi0_shape_action_time_variant():
     ae = _pi0_expert(wl, w, 1, 816)
     try:
         got = _pi0_run(ae, K, V, noise, wl.n_steps, [815], spi0.make_state(wl), synth.make_committed(wl), 10)
+        single = _pi0_run(ae, K, V, noise, wl.n_steps, [815], spi0.make_state(wl), synth.make_committed(wl), 10,
+                          persist="1")
         multi = _pi0_run(ae, K, V, noise, wl.n_steps, [815], spi0.make_state(wl), synth.make_committed(wl), 10,
                          persist="0")
     finally:
         ae.close()
-    for label, out in (("single-launch steps", got), ("multi-kernel", multi)):
+    assert not np.array_equal(single, multi) and not np.array_equal(got, multi) and not np.array_equal(got, single)
+    for label, out in (("five-launch", got), ("single-launch steps", single), ("multi-kernel", multi)):
         rel = rel_l2_per_rollout(out, ref)
         print("%s: rel-L2 %.3e max-abs %.3e" % (label, rel, np.abs(out - ref).max()), flush=True)
         assert_bf16(out, ref, label, reg_rel=1e-2, reg_abs=5e-2)
