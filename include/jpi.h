@@ -219,8 +219,17 @@ jpi_status jpi_set_committed_t0(jpi_ctx* ctx, int enable);
  * HIP graph; later calls replay it.  Errors: JPI_ERR_STATE (weights not
  * finalized or no prefix bound), JPI_ERR_ARG (NULL, n_steps < 1).
  *
- * Co-residency: on the single-launch path (bf16, batch * (n_corr + H) <= 64,
- * widths that are not a multiple of 256, or JPI_PERSIST=1 in the environment)
+ * Paths, all captured once and replayed: the five-launch layers (bf16,
+ * batch * (n_corr + H) <= 512, max_prefix >= 1, width, mlp_dim and
+ * n_heads * head_dim multiples of 256, width <= 1024, memory for the prefix's
+ * blocks); where they do not apply, the single-launch kernel for at most 64
+ * bf16 rows of the shapes it supports (n_heads even; width, mlp_dim and
+ * n_heads * head_dim multiples of 128, width <= 2048: so also by default for
+ * widths 1280 .. 2048); the eight-launch layers otherwise.  JPI_PERSIST in
+ * the environment, read at every call: "1" asks for the single-launch kernel
+ * wherever it is supported, "0" for the eight-launch layers.
+ *
+ * Co-residency: on the single-launch path
  * the whole loop is one kernel of one workgroup per compute unit whose
  * workgroups wait for each other through memory.  That needs every
  * workgroup resident at once: do not let other device work (another stream,
@@ -322,7 +331,7 @@ typedef enum {
   JPI_KERNEL_OPROJ = 2,      /* attention output x W_o, gated residual */
   JPI_KERNEL_GATEUP = 3,     /* activations x [gate|up], GeGLU epilogue */
   JPI_KERNEL_DOWN = 4,       /* GeGLU output x W_down, gated residual */
-  JPI_KERNEL_PERSISTENT = 5  /* the single-launch denoise kernel, where it runs */
+  JPI_KERNEL_PERSISTENT = 5  /* the single-launch denoise kernel, where it runs (see jpi_denoise) */
 } jpi_kernel_kind;
 
 /* Ask jpi_denoise to record a pair of HIP events around every launch of
