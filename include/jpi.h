@@ -323,6 +323,14 @@ jpi_status jpi_debug_persist_trace(jpi_ctx* ctx, uint64_t* host_out, int64_t cap
  * Errors: JPI_ERR_ARG (NULL ctx), JPI_ERR_HIP. */
 jpi_status jpi_debug_set_spin_limit(jpi_ctx* ctx, uint32_t polls);
 
+/* Test hook for the out-of-memory paths: from now on device allocations of
+ * this context larger than `bytes` fail as if memory had run out (0: no
+ * limit).  The five-launch layers' buffers (prefix blocks, fragment-ordered
+ * weights, shift table) are optional: without them jpi_denoise runs the other
+ * layers, and the next jpi_bind_prefix tries again.  Errors: JPI_ERR_ARG
+ * (NULL ctx). */
+jpi_status jpi_debug_set_alloc_limit(jpi_ctx* ctx, size_t bytes);
+
 /* Kernel kinds of one denoise step, in launch order per layer. */
 typedef enum {
   JPI_KERNEL_NONE = -1,

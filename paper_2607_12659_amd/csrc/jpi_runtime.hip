@@ -103,7 +103,8 @@ struct jpi_ctx {
   void *kp = nullptr, *vp = nullptr;  // [L][Bmax][Pmax][Dh] as bound
   void *kvf = nullptr, *skvf = nullptr, *skvf_state = nullptr;  // KvBlocks: prefix [L][Bmax][NBmax], own rows, state rows
   int NBmax = 0;
-  bool no_blocks = false;
+  bool no_small = false;  // no memory for the five-launch layers' buffers (until the next prefix is bound)
+  size_t alloc_limit = 0;  // test hook: larger device allocations fail (0: no limit)
   void* vpt = nullptr;                 // [L][Bmax][Dh][Ppad] prefix V transposed at bind time
   int Ppad = 0;                        // Pmax + horizon rounded up to a multiple of 8
   int* d_prefix_len = nullptr;
@@ -180,7 +181,7 @@ jpi_status fail(jpi_ctx* c, jpi_status st, const std::string& msg) {
 jpi_status dmalloc(jpi_ctx* c, void** p, size_t bytes) {
   *p = nullptr;
   if (bytes == 0) bytes = 256;
-  hipError_t e = hipMalloc(p, bytes);
+  hipError_t e = c->alloc_limit && bytes > c->alloc_limit ? hipErrorOutOfMemory : hipMalloc(p, bytes);
   if (e != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();
@@ -653,26 +654,19 @@ jpi_status jpi_debug_prefix_vt(jpi_ctx* c, void** vt_out, int* ld_out) {
 namespace {
 
 // The prefix's fragment-ordered blocks, kept where the five-launch layers can
-// run.  Where they do not fit in memory the kernels that read the row-major buffers run.
+// run.  Where they do not fit in memory the kernels that read the row-major buffers run
+// (the next binding tries again).
 jpi_status ensure_blocks(jpi_ctx* c) {
-  if (c->kvf || c->no_blocks || c->Pmax < 1) return JPI_OK;
-  if (!small_supported(c->dt, c->W, c->nH, c->Dh, c->F)) {
-    c->no_blocks = true;
-    return JPI_OK;
-  }
+  c->no_small = false;
+  if (c->kvf || c->Pmax < 1 || !small_supported(c->dt, c->W, c->nH, c->Dh, c->F)) return JPI_OK;
   const size_t blk = kv_block_elems(c->Dh) * c->esz, S = c->H + c->Cmax;
   c->NBmax = kv_blocks(c->Pmax);
   const size_t own = (size_t)c->Bmax * ((S + 31) / 32) * blk;
   const size_t state = c->cfg.variant == JPI_VARIANT_ACTION_TIME ? (size_t)c->L * c->Bmax * blk : 0;
-  if (hipMalloc(&c->kvf, (size_t)c->L * c->Bmax * c->NBmax * blk) != hipSuccess) {
-    c->kvf = nullptr;
-  } else if (hipMalloc(&c->skvf, own + state) != hipSuccess) {
+  if (dmalloc(c, &c->kvf, (size_t)c->L * c->Bmax * c->NBmax * blk) != JPI_OK) return JPI_OK;
+  if (dmalloc(c, &c->skvf, own + state) != JPI_OK) {
     (void)hipFree(c->kvf);
-    c->kvf = c->skvf = nullptr;
-  }
-  if (!c->kvf) {
-    (void)hipGetLastError();
-    c->no_blocks = true;
+    c->kvf = nullptr;
     return JPI_OK;
   }
   c->skvf_state = state ? (char*)c->skvf + own : nullptr;
@@ -854,7 +848,7 @@ bool use_persist(jpi_ctx* c, int batch) {
 constexpr int SMALL_ROWS = 512;
 bool use_small(const jpi_ctx* c, int batch) {
   const char* e = getenv("JPI_PERSIST");
-  if ((e && (e[0] == '0' || e[0] == '1')) || c->persist_spin != 0) return false;
+  if ((e && (e[0] == '0' || e[0] == '1')) || c->persist_spin != 0 || c->no_small) return false;
   return c->kvf && batch * (c->H + c->n_corr) <= SMALL_ROWS;
 }
 
@@ -885,11 +879,39 @@ int prefix_keys(const jpi_ctx* c) {
   return key_bound(c->prefix, c->Pmax, c->cfg.variant == JPI_VARIANT_ACTION_TIME);
 }
 
+// Buffers that only the five-launch layers need (sets *changed where a captured graph may hold the old one).
+jpi_status ensure_small(jpi_ctx* c, int batch, bool* changed) {
+  const size_t rows = (size_t)batch * (c->H + c->n_corr) + batch;  // the action-time variant's state rows follow
+  if (rows * (c->W / 16) > c->ssq_cap) {
+    if (c->ssq) (void)hipFree(c->ssq);
+    c->ssq = nullptr;
+    c->ssq_cap = 0;
+    *changed = true;
+    TRY(dmalloc(c, (void**)&c->ssq, rows * (c->W / 16) * sizeof(float)));
+    c->ssq_cap = rows * (c->W / 16);
+  }
+  auto copy = [&](void** p, size_t elems) {  // a fragment-ordered copy of weights
+    if (*p) return JPI_OK;
+    c->frag_ready = false;
+    return dmalloc(c, p, elems * c->esz);
+  };
+  if (c->cfg.variant == JPI_VARIANT_ACTION_TIME) {
+    TRY(copy(&c->w_atm_a_frag, (size_t)c->W * c->W));
+    TRY(copy(&c->w_atm_out_frag, (size_t)c->W * c->W));
+  }
+  return copy(&c->w_frag, c->layer_elems * c->L);
+}
+
 jpi_status ensure_scratch(jpi_ctx* c, int batch, int prefix) {
+  bool changed = false;
+  if (use_small(c, batch)) {
+    const jpi_status st = ensure_small(c, batch, &changed);
+    if (st == JPI_ERR_OOM) c->no_small = true;  // the other layers run without those buffers
+    else if (st != JPI_OK) return st;
+  }
   const StepGemms p = plan_gemms(c, batch);
   const size_t need = std::max((size_t)std::max(std::max(p.s_o, p.s_d), p.s_a) * p.M * c->W,
                                (size_t)std::max(p.s_so, p.s_sd) * batch * c->W);
-  bool changed = false;
   if (need > c->partial_cap) {
     if (c->partial) (void)hipFree(c->partial);
     c->partial = nullptr;
@@ -911,12 +933,12 @@ jpi_status ensure_scratch(jpi_ctx* c, int batch, int prefix) {
     c->attn_cap = attn;
     changed = true;
   }
-  if (p.persist && !c->ysw) {
+  if (p.persist && !c->qsw) {
     // fragment-ordered activations, 64 padded rows (the padding stays zero)
     const size_t es = c->esz, bq = std::max(1, 64 / c->H);
-    TRY(dmalloc(c, &c->ysw, (size_t)64 * c->W * es));
-    TRY(dmalloc(c, &c->osw, (size_t)64 * c->nH * c->Dh * es));
-    TRY(dmalloc(c, &c->zsw, (size_t)64 * c->F * es));
+    if (!c->ysw) TRY(dmalloc(c, &c->ysw, (size_t)64 * c->W * es));
+    if (!c->osw) TRY(dmalloc(c, &c->osw, (size_t)64 * c->nH * c->Dh * es));
+    if (!c->zsw) TRY(dmalloc(c, &c->zsw, (size_t)64 * c->F * es));
     TRY(dmalloc(c, &c->qsw, bq * c->nH * 64 * c->Dh * es));
     HIPCHK(c, hipMemset(c->ysw, 0, (size_t)64 * c->W * es));
     HIPCHK(c, hipMemset(c->osw, 0, (size_t)64 * c->nH * c->Dh * es));
@@ -925,24 +947,7 @@ jpi_status ensure_scratch(jpi_ctx* c, int batch, int prefix) {
     HIPCHK(c, hipDeviceSynchronize());
     changed = true;
   }
-  if (p.small) {
-    const size_t rows = (size_t)batch * S + batch;  // the action-time variant's state rows follow
-    if (rows * (c->W / 16) > c->ssq_cap) {
-      if (c->ssq) (void)hipFree(c->ssq);
-      c->ssq = nullptr;
-      c->ssq_cap = 0;
-      TRY(dmalloc(c, (void**)&c->ssq, rows * (c->W / 16) * sizeof(float)));
-      c->ssq_cap = rows * (c->W / 16);
-      changed = true;
-    }
-    if (c->cfg.variant == JPI_VARIANT_ACTION_TIME && !c->w_atm_a_frag) {
-      TRY(dmalloc(c, &c->w_atm_a_frag, (size_t)c->W * c->W * c->esz));
-      TRY(dmalloc(c, &c->w_atm_out_frag, (size_t)c->W * c->W * c->esz));
-      c->frag_ready = false;
-      changed = true;
-    }
-  }
-  if ((p.persist || p.small) && !c->w_frag) {
+  if (p.persist && !c->w_frag) {
     TRY(dmalloc(c, &c->w_frag, c->layer_elems * c->L * c->esz));
     c->frag_ready = false;
     changed = true;
@@ -1573,10 +1578,19 @@ jpi_status jpi_denoise(jpi_ctx* c, const float* noise_dev, int n_steps, float* a
   float* table = nullptr;
   TRY(ensure_table(c, n_steps, s, &table));
   TRY(ensure_scratch(c, c->batch, prefix_keys(c)));
-  const StepGemms plan = plan_gemms(c, c->batch);
+  StepGemms plan = plan_gemms(c, c->batch);
   float* shift = nullptr;
+  if (plan.small) {
+    const jpi_status st = ensure_shift_table(c, table, n_steps, s, &shift);
+    if (st == JPI_ERR_OOM) {  // a table for very many steps: the other layers need none
+      c->no_small = true;
+      TRY(ensure_scratch(c, c->batch, prefix_keys(c)));
+      plan = plan_gemms(c, c->batch);
+    } else if (st != JPI_OK) {
+      return st;
+    }
+  }
   if (plan.persist || plan.small) TRY(ensure_frag(c, s));
-  if (plan.small) TRY(ensure_shift_table(c, table, n_steps, s, &shift));
   HIPCHK(c, launch_init_x(noise_dev, c->committed, c->x, c->batch, c->H, c->A, c->n_fixed, s));
   if (c->rope_rows != c->H + c->n_corr) {  // the suffix length changed since the table was built
     HIPCHK(c, launch_rope_table(c->d_prefix_len, c->rope_tab, c->batch, c->H + c->n_corr, c->Dh, c->cfg.rope_base, s));
@@ -1649,6 +1663,12 @@ jpi_status jpi_debug_set_spin_limit(jpi_ctx* c, uint32_t polls) {
   HIPCHK(c, hipDeviceSynchronize());
   c->persist_spin = polls;
   drop_graphs(c);  // the bound is an argument of the captured launch
+  return JPI_OK;
+}
+
+jpi_status jpi_debug_set_alloc_limit(jpi_ctx* c, size_t bytes) {
+  if (!c) return fail(nullptr, JPI_ERR_ARG, "jpi_debug_set_alloc_limit: ctx is NULL");
+  c->alloc_limit = bytes;
   return JPI_OK;
 }
 

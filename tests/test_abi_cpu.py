@@ -79,6 +79,7 @@ def test_null_arguments():
     assert j.jpi_sync(None) == j.JPI_ERR_ARG
     assert j.jpi_set_committed_t0(None, 1) == j.JPI_ERR_ARG
     assert j.jpi_bind_robot_state(None, 1) == j.JPI_ERR_ARG
+    assert j.jpi_debug_set_alloc_limit(None, 1) == j.JPI_ERR_ARG
     assert j.jpi_corr_destroy(None) == j.JPI_OK
     assert j.jpi_corr_set_weight(None, "fuse.w", 1, 1, j.JPI_BF16, 0) == j.JPI_ERR_ARG
     assert j.jpi_corr_finalize_weights(None) == j.JPI_ERR_ARG

@@ -10,7 +10,7 @@ import pytest
 
 import oracle
 import synth
-from gpu_util import Inputs, assert_bf16, device_view_i16, make_expert, run, run_env, torch_cuda
+from gpu_util import Inputs, assert_bf16, device_view_i16, make_expert, path_env, run, run_env, torch_cuda
 
 pytestmark = pytest.mark.gpu
 REL, ABS = 4e-3, 4e-2
@@ -253,5 +253,47 @@ def test_small_rows_without_any_finite_score(B, lens):
         assert np.isfinite(run(ae, inp.K, inp.V, inp.noise, 1, prefix_len=inp.prefix_len)).all()
         ae.load_weights(w)
         assert np.isnan(run(ae, K, inp.V, inp.noise, 1, prefix_len=inp.prefix_len)).all()
+    finally:
+        ae.close()
+
+
+# what does not fit: the prefix's blocks (0.8 MB, allocated by the binding), the fragment-ordered weights (69 MB; the
+# eight-launch layers' slices take 6.6 MB), the shift table of 100 steps (8.7 MB; their modulation table takes 6.2 MB)
+@pytest.mark.parametrize("what,limit,steps", [("blocks", 1 << 19, 2), ("weights", 16 << 20, 2), ("shift table", 7 << 20, 100)])
+def test_small_rows_without_memory(what, limit, steps):
+    """The eight-launch layers run, with their results, where a buffer of the five-launch layers does not fit."""
+    torch_cuda()
+    from paper_2607_12659_amd import jpi
+    from paper_2607_12659_amd.expert import to_device
+    wl, inp, _ = _case("w1024", 4)
+    K, V, noise = to_device(inp.K), to_device(inp.V), to_device(np.ascontiguousarray(inp.noise, np.float32))
+
+    def denoise():
+        out = ae.denoise(noise, steps)
+        ae.sync()
+        return out.cpu().numpy().astype(np.float64)
+
+    print("case no memory for the", what, flush=True)
+    ae = make_expert(wl, inp.weights, max_prefix=wl.prefix + 5)
+    try:
+        if what == "shift table":
+            for env in ("0", None):  # every other buffer of either path is there
+                run_env(ae, env, inp.K, inp.V, inp.noise, 2, prefix_len=inp.prefix_len)
+        assert jpi.jpi_debug_set_alloc_limit(ae.ctx, limit) == jpi.JPI_OK
+        ae.bind_prefix(K, V, inp.prefix_len)
+        if what == "blocks":
+            assert jpi.jpi_debug_set_alloc_limit(ae.ctx, 0) == jpi.JPI_OK
+        got = denoise()
+        assert np.array_equal(got, denoise())
+        assert jpi.jpi_debug_set_alloc_limit(ae.ctx, 0) == jpi.JPI_OK
+        with path_env("0"):
+            eight = denoise()
+        assert np.array_equal(got, eight)
+        ae.bind_prefix(K, V, inp.prefix_len)  # the next binding has memory
+        five = denoise()
+        assert not np.array_equal(five, eight)
+        if steps == 2:
+            for out in (five, eight):
+                assert_bf16(out, _oracle(wl, inp, None), wl.name, reg_rel=REL, reg_abs=ABS)
     finally:
         ae.close()
