@@ -133,9 +133,10 @@ __global__ __launch_bounds__(256) void k_action_in_frag(const float* __restrict_
 // k_fuse_in with a fragment-ordered result
 __global__ __launch_bounds__(256) void k_fuse_in_frag(const float* __restrict__ c, const float* __restrict__ hact,
                                                       bf16* __restrict__ X, int T, int n, int W) {
+  typedef f32x4 __attribute__((aligned(4))) piece;  // the caller's state may start at any float
   const int m = blockIdx.x, b = m / T;
   for (int k = 4 * threadIdx.x; k < 2 * W; k += 1024) {
-    const f32x4 v = k < W ? *reinterpret_cast<const f32x4*>(c + (size_t)m * W + k)
+    const f32x4 v = k < W ? *reinterpret_cast<const piece*>(c + (size_t)m * W + k)
                           : *reinterpret_cast<const f32x4*>(hact + ((size_t)b * n + n - 1) * W + k - W);
     typedef bf16 b4 __attribute__((ext_vector_type(4)));
     *reinterpret_cast<b4*>(X + frag_at(m, k, 2 * W)) = b4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};

@@ -776,6 +776,8 @@ __global__ __launch_bounds__(256) void k_bind(BindLaunch a) {
   const int key0 = blockIdx.x * 32, b = blockIdx.y, l = blockIdx.z, tid = threadIdx.x;
   const size_t src = ((size_t)l * a.B + b) * a.P, dst = ((size_t)l * a.Bmax + b) * a.Pmax;
   const bool in_place = a.in_place;
+  // the caller's K and V may start at any element
+  typedef u32x4 __attribute__((aligned(2))) piece;
   const T* k = reinterpret_cast<const T*>(a.k) + (in_place ? dst : src) * DH;
   const T* v = reinterpret_cast<const T*>(a.v) + (in_place ? dst : src) * DH;
   T* kp = reinterpret_cast<T*>(a.kp) + dst * DH;
@@ -790,8 +792,8 @@ __global__ __launch_bounds__(256) void k_bind(BindLaunch a) {
     const int kt = f / (CPR / 4), c = (f % (CPR / 4)) * 4 + (ln >> 4), row = ln & 15;
     const int kk = 8 * (row >> 2) + 4 * kt + (row & 3), key = key0 + kk;
     const bool ok = key < a.P;
-    const u32x4 x = ok ? *reinterpret_cast<const u32x4*>(k + (size_t)key * DH + c * VEC) : zero;
-    const u32x4 y = ok ? *reinterpret_cast<const u32x4*>(v + (size_t)key * DH + c * VEC) : zero;
+    const u32x4 x = ok ? *reinterpret_cast<const piece*>(k + (size_t)key * DH + c * VEC) : zero;
+    const u32x4 y = ok ? *reinterpret_cast<const piece*>(v + (size_t)key * DH + c * VEC) : zero;
     if (ok && !in_place) {
       *reinterpret_cast<u32x4*>(kp + (size_t)key * DH + c * VEC) = x;
       *reinterpret_cast<u32x4*>(vp + (size_t)key * DH + c * VEC) = y;

@@ -700,22 +700,25 @@ hipError_t launch_gemm(jpi_dtype dt, const GemmLaunch& g, hipStream_t s) {
     // unless that leaves the grid short and the epilogue cannot be split over K
     const int n_cu = g.n_cu > 0 ? g.n_cu : 256;
     auto tiles = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.splitk; };
+    // the rings load 16-byte pieces straight into LDS, which takes 16-byte-aligned operands; the register-staged
+    // kernels' loads take any
+    const bool rings_on = gemm_pipe_enabled() && ((uintptr_t)g.A | (uintptr_t)g.W) % 16 == 0;
     // the direct-to-LDS pipeline (one 128 KB ring per compute unit) wins where one
     // round of 128 x 128 tiles covers the chip and no more (measured: M = 400
     // GateUp 25.1 -> 19.6 us, Down 16.2 -> 13.4 us, against the register-staged
     // kernel); other counts take a tile by the rules below
-    if (gemm_pipe_enabled() && g.M <= 512 && tiles(128, 128) >= n_cu && tiles(128, 128) <= n_cu + n_cu / 4 &&
+    if (rings_on && g.M <= 512 && tiles(128, 128) >= n_cu && tiles(128, 128) <= n_cu + n_cu / 4 &&
         (g.K / g.splitk) % DmaMid::BK == 0 && (size_t)g.N * g.K * 2 < (1u << 31))
       return launch_dma<DmaMid>(g, s);
     // fewer 128 x 128 tiles than units and no K split (QKV at M = 400: 80 tiles): 64 x 64 tiles on the
     // pipelined kernel, two workgroups per unit (measured 20.0 -> 12.7 us; on split-K shapes no gain)
-    if (gemm_pipe_enabled() && g.M <= 512 && tiles(128, 128) < n_cu && g.splitk == 1 && g.K % DmaSmall::BK == 0 &&
+    if (rings_on && g.M <= 512 && tiles(128, 128) < n_cu && g.splitk == 1 && g.K % DmaSmall::BK == 0 &&
         (size_t)g.N * g.K * 2 < (1u << 31))
       return launch_dma<DmaSmall>(g, s);
     // a K split whose 128 x 128 tiles still leave half of the units idle: 64 x 64 tiles on the pipelined kernel
     // (with the slices' sum, against the register-staged 128 x 128 kernel: M = 150, N = 1024, K = 4096 in 4
     // slices 19.4 -> 9.1 us, in 2 slices 31.1 -> 12.3; M = 400, K = 2048 in 4 slices 14.3 -> 10.0)
-    if (gemm_pipe_enabled() && 2 * tiles(128, 128) <= n_cu && (g.K / g.splitk) % DmaSmall::BK == 0 &&
+    if (rings_on && 2 * tiles(128, 128) <= n_cu && (g.K / g.splitk) % DmaSmall::BK == 0 &&
         (size_t)g.N * g.K * 2 < (1u << 31) && (size_t)g.M * g.K * 2 < (1u << 31))
       return launch_dma<DmaSmall>(g, s);
     // Otherwise the ring tile with the least estimated time: turns of tiles over the units, each a start and
@@ -725,7 +728,7 @@ hipError_t launch_gemm(jpi_dtype dt, const GemmLaunch& g, hipStream_t s) {
     // 128 x 128): gate/up M = 1126 37.2 -> 26.6, M = 1689 42.6 -> 28.9; Down in 4 slices M = 550 17.7 -> 12.5, M = 1126
     // 22.4 -> 16.6; VLM QKV M = 1689 48.4 -> 32.0, M = 816 25.2 -> 21.0 (with the row-tile epilogue).
     const bool fits = (size_t)g.N * g.K * 2 < (1u << 31) && (size_t)g.M * g.K * 2 < (1u << 31);
-    if (gemm_pipe_enabled() && fits) {
+    if (rings_on && fits) {
       struct Ring {
         int bm, bn, per_cu;     // tile, workgroups per unit
         float start, slice;     // us of a round, of one slice of a tile
@@ -751,7 +754,7 @@ hipError_t launch_gemm(jpi_dtype dt, const GemmLaunch& g, hipStream_t s) {
       }
       return best->launch(g, s);
     }
-    // operands of 2 GiB or more (the rings' buffer offsets are 32 bit) and JPI_GEMM_PIPE=0: register-staged tiles
+    // operands of 2 GiB or more (the rings' buffer offsets are 32 bit), unaligned ones and JPI_GEMM_PIPE=0: register-staged tiles
     if (tiles(256, 256) >= n_cu) return launch_big<Big256>(g, s);
     if (tiles(128, 128) >= n_cu || g.epi == EPI_STORE_F32) return launch_gemm_t<bf16, 128, 128>(g, s);
     if (tiles(128, 64) >= n_cu) return launch_gemm_t<bf16, 128, 64>(g, s);

@@ -27,6 +27,30 @@ def test_gemm_ring_tiles(M, N, K, splitk):
     assert np.all(np.abs(got - a @ w.T) <= 1e-5 * (np.abs(a) @ np.abs(w).T) + 1e-6)
 
 
+# operands that start one element past a 16-byte boundary, at sizes that take each ring tile when aligned
+@pytest.mark.parametrize("M,N,K,splitk", [(150, 1024, 4096, 4), (400, 2560, 1024, 1), (400, 8192, 1024, 1), (816, 2560, 2048, 1),
+                                          (1126, 8192, 1024, 1)])
+@pytest.mark.parametrize("a_off,w_off", [(1, 0), (0, 1), (3, 5)])
+def test_gemm_unaligned_operands(M, N, K, splitk, a_off, w_off):
+    torch = torch_cuda()
+    from paper_2607_12659_amd import jpi
+    from paper_2607_12659_amd.expert import to_device
+    rng = np.random.default_rng(M + N + a_off + w_off)
+    A, W = _bf16(rng.normal(size=(M, K))), _bf16(rng.normal(size=(N, K)) * 0.02)
+
+    def at(x, off):
+        buf = torch.zeros(x.size + 8, dtype=torch.int16, device="cuda")
+        buf[off:off + x.size] = to_device(x).reshape(-1)
+        return buf[off:off + x.size]
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    print("case unaligned", M, N, K, splitk, a_off, w_off, flush=True)
+    st = jpi.jpi_debug_gemm(at(A, a_off), at(W, w_off), C, M, N, K, jpi.JPI_BF16, splitk)
+    assert st == jpi.JPI_OK, jpi.jpi_last_error(None)
+    torch.cuda.synchronize()
+    a, w = oracle.widen(A), oracle.widen(W)
+    assert np.all(np.abs(C.cpu().numpy().astype(np.float64) - a @ w.T) <= 1e-5 * (np.abs(a) @ np.abs(w).T) + 1e-6)
+
+
 # merges of 3, 5, 6, 7, 9, 12 and 14 key ranges; a rollout with fewer keys leaves ranges empty
 @pytest.mark.parametrize("B,P,Dh", [(2, 100, 64), (3, 333, 128), (2, 300, 256), (7, 816, 64), (2, 500, 128), (2, 700, 64),
                                     (2, 816, 256)])

@@ -137,6 +137,59 @@ def test_bind_prefix_copies(dtype, Dh, B, P, Pmax):
         ae.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_bind_prefix_from_any_element(dtype):
+    """K and V that start one element past a 16-byte boundary give the same actions."""
+    torch = torch_cuda()
+    from paper_2607_12659_amd.expert import to_device
+    d = synth.Dims(n_layers=2, width=256, n_heads=4, n_kv_heads=1, head_dim=64, mlp_dim=512, action_dim=7, horizon=10)
+    wl = synth.Workload("bind", d, prefix=45, batch=2, n_steps=2, n_fixed=0, dtype=dtype)
+    inp = Inputs(wl)
+    ae = make_expert(wl, inp.weights)
+
+    def moved(x):
+        t = to_device(x)
+        buf = torch.zeros(t.numel() + 1, dtype=t.dtype, device="cuda")
+        buf[1:] = t.reshape(-1)
+        return buf[1:].view(t.shape)
+    try:
+        want = run(ae, inp.K, inp.V, inp.noise, 2)
+        ae.bind_prefix(moved(inp.K), moved(inp.V))
+        out = ae.denoise(to_device(np.ascontiguousarray(inp.noise, np.float32)), 2)
+        ae.sync()
+        assert np.array_equal(out.cpu().numpy().astype(np.float64), want)
+    finally:
+        ae.close()
+
+
+def test_correction_inputs_from_any_element():
+    """VLM state, compressed state and outputs that start off a 16-byte boundary."""
+    torch = torch_cuda()
+    import synth.correction as sc
+    from gpu_util import Corr
+    from paper_2607_12659_amd.expert import to_device
+    wl = sc.CORR_WORKLOADS["corr40m-p816"].with_(batch=2, n_actions=5, vlm_tokens=130)
+    x, acts = to_device(sc.make_vlm_state(wl)), to_device(np.ascontiguousarray(sc.make_actions(wl), np.float32))
+    m = Corr(wl.dims, sc.make_corr_weights(wl), 2, 5, 130)
+
+    def moved(t, copy=True):
+        buf = torch.zeros(t.numel() + 1, dtype=t.dtype, device="cuda")
+        if copy:
+            buf[1:] = t.reshape(-1)
+        return buf[1:].view(t.shape)
+    try:
+        c = m.compress(x, 2, 130)
+        item, conf = m.predict(c, acts, 2, 5)
+        c2 = m.compress(x, 2, 130, out=moved(c, copy=False))
+        item2, conf2 = m.predict(c2, moved(acts), 2, 5, item=moved(item, copy=False), conf=moved(conf, copy=False))
+        assert torch.equal(c, c2) and torch.equal(item, item2) and torch.equal(conf, conf2)
+        # an unaligned VLM state takes another product kernel: the same sums in another order
+        c3 = m.compress(moved(x), 2, 130)
+        assert float((c3 - c).norm() / c.norm()) <= 1e-3
+    finally:
+        m.close()
+
+
 # action rows 1, 75, 200 and 513 (past the five-launch layers); one token, a block's edge, several blocks
 @pytest.mark.parametrize("batch,n_actions,tokens", [(1, 1, 1), (3, 25, 33), (8, 25, 64), (2, 10, 130), (27, 19, 5)])
 def test_correction_rows_match_oracle(batch, n_actions, tokens):
