@@ -1842,6 +1842,11 @@ jpi_status jpi::ae_prefix_target(jpi_ctx* c, int L, int Dh, jpi_dtype dt, int ba
   t->vpt_bstride = (int64_t)Dh * c->Ppad;
   t->vpt_lstride = (int64_t)c->Bmax * t->vpt_bstride;
   t->prefix_len = c->d_prefix_len;
+  if (hipSetDevice(c->device) != hipSuccess) {  // the blocks are the expert's, whatever device the thread is on
+    (void)hipGetLastError();
+    *why = "hipSetDevice of the action expert's device failed";
+    return JPI_ERR_HIP;
+  }
   const jpi_status st = ensure_blocks(c);
   if (st != JPI_OK) return st;
   t->blocks = bind_launch(c, batch, prefix);
