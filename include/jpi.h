@@ -165,7 +165,9 @@ jpi_status jpi_prefix_buffers(jpi_ctx* ctx, void** k_out, void** v_out);
  * they are those buffers.  prefix_len_host: host array [batch] of valid
  * lengths in [0, prefix] (NULL = all `prefix`); slots j >= prefix_len are
  * never read.  Errors: JPI_ERR_ARG (NULL), JPI_ERR_SHAPE (batch outside
- * [1, max_batch], prefix outside [0, max_prefix], prefix_len out of range). */
+ * [1, max_batch], prefix outside [0, max_prefix], prefix_len out of range),
+ * JPI_ERR_STATE (`stream` is being captured: a replay would not renew the
+ * batch and lengths that the context notes on the host). */
 jpi_status jpi_bind_prefix(jpi_ctx* ctx, const void* k, const void* v, const int32_t* prefix_len_host,
                            int batch, int prefix, void* stream);
 

@@ -722,6 +722,11 @@ jpi_status jpi_bind_prefix(jpi_ctx* c, const void* k, const void* v, const int32
   const bool in_place = (k == c->kp && v == c->vp);
   if (in_place && prefix != c->Pmax)
     return fail(c, JPI_ERR_SHAPE, "jpi_bind_prefix: the resident buffers must be bound with prefix == max_prefix");
+  // A captured binding would replay its device work without what the context notes beside it (batch, lengths)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIPCHK(c, hipStreamIsCapturing(s, &cap));
+  if (cap != hipStreamCaptureStatusNone)
+    return fail(c, JPI_ERR_STATE, "jpi_bind_prefix: the stream is being captured");
   TRY(ensure_blocks(c));
   BindLaunch bl = bind_launch(c, batch, prefix);
   bl.k = k;

@@ -137,6 +137,33 @@ def test_bind_prefix_copies(dtype, Dh, B, P, Pmax):
         ae.close()
 
 
+def test_bind_prefix_refuses_a_captured_stream():
+    """The context notes batch and lengths on the host, which a replay would not do; the capture itself goes on."""
+    torch = torch_cuda()
+    from paper_2607_12659_amd import jpi
+    from paper_2607_12659_amd.expert import to_device
+    wl, inp, _ = _case("w256", 2)
+    K, V = to_device(inp.K), to_device(inp.V)
+    ae = make_expert(wl, inp.weights)
+    try:
+        want = run(ae, inp.K, inp.V, inp.noise, wl.n_steps, prefix_len=inp.prefix_len)
+        t, graph, s = torch.zeros(4, device="cuda"), torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=s):
+            t += 1
+            st = jpi.jpi_bind_prefix(ae.ctx, K, V, [1, 2], 2, wl.prefix, s.cuda_stream)
+        assert st == jpi.JPI_ERR_STATE
+        graph.replay()
+        torch.cuda.synchronize()
+        assert t.tolist() == [1.0] * 4
+        noise = to_device(np.ascontiguousarray(inp.noise, np.float32))
+        out = ae.denoise(noise, wl.n_steps)  # the earlier binding holds
+        ae.sync()
+        assert np.array_equal(out.cpu().numpy().astype(np.float64), want)
+    finally:
+        ae.close()
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_bind_prefix_from_any_element(dtype):
     """K and V that start one element past a 16-byte boundary give the same actions."""
