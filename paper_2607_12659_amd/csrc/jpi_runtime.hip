@@ -653,12 +653,20 @@ jpi_status jpi_debug_prefix_vt(jpi_ctx* c, void** vt_out, int* ld_out) {
 
 namespace {
 
+constexpr int SMALL_ROWS = 512;  // see use_small
+
+// The action-time variant's eight-launch layers read the row-major buffers only (the state token's key and value are
+// put there), so past SMALL_ROWS its prefix has no use for blocks.
+bool blocks_wanted(const jpi_ctx* c, int batch) {
+  return c->cfg.variant != JPI_VARIANT_ACTION_TIME || batch * c->H <= SMALL_ROWS;
+}
+
 // The prefix's fragment-ordered blocks, kept where the five-launch layers can
 // run.  Where they do not fit in memory the kernels that read the row-major buffers run
 // (the next binding tries again).
-jpi_status ensure_blocks(jpi_ctx* c) {
+jpi_status ensure_blocks(jpi_ctx* c, int batch) {
   c->no_small = false;
-  if (c->kvf || c->Pmax < 1 || !small_supported(c->dt, c->W, c->nH, c->Dh, c->F)) return JPI_OK;
+  if (c->kvf || c->Pmax < 1 || !small_supported(c->dt, c->W, c->nH, c->Dh, c->F) || !blocks_wanted(c, batch)) return JPI_OK;
   const size_t blk = kv_block_elems(c->Dh) * c->esz, S = c->H + c->Cmax;
   c->NBmax = kv_blocks(c->Pmax);
   const size_t own = (size_t)c->Bmax * ((S + 31) / 32) * blk;
@@ -678,7 +686,7 @@ BindLaunch bind_launch(const jpi_ctx* c, int batch, int prefix) {
   b.kp = c->kp;
   b.vp = c->vp;
   b.vpt = c->vpt;
-  b.kvf = c->kvf;
+  b.kvf = blocks_wanted(c, batch) ? c->kvf : nullptr;
   b.L = c->L;
   b.B = batch;
   b.P = prefix;
@@ -727,7 +735,7 @@ jpi_status jpi_bind_prefix(jpi_ctx* c, const void* k, const void* v, const int32
   HIPCHK(c, hipStreamIsCapturing(s, &cap));
   if (cap != hipStreamCaptureStatusNone)
     return fail(c, JPI_ERR_STATE, "jpi_bind_prefix: the stream is being captured");
-  TRY(ensure_blocks(c));
+  TRY(ensure_blocks(c, batch));
   BindLaunch bl = bind_launch(c, batch, prefix);
   bl.k = k;
   bl.v = v;
@@ -850,7 +858,6 @@ bool use_persist(jpi_ctx* c, int batch) {
 // JPI_PERSIST=1 and a wait bound set for its test ask for the single-launch kernel, JPI_PERSIST=0 for the
 // eight-launch layers.  The single-launch kernel also serves the shapes of at most 64 rows that it supports
 // and these layers do not.
-constexpr int SMALL_ROWS = 512;
 bool use_small(const jpi_ctx* c, int batch) {
   const char* e = getenv("JPI_PERSIST");
   if ((e && (e[0] == '0' || e[0] == '1')) || c->persist_spin != 0 || c->no_small) return false;
@@ -1852,7 +1859,7 @@ jpi_status jpi::ae_prefix_target(jpi_ctx* c, int L, int Dh, jpi_dtype dt, int ba
     *why = "hipSetDevice of the action expert's device failed";
     return JPI_ERR_HIP;
   }
-  const jpi_status st = ensure_blocks(c);
+  const jpi_status st = ensure_blocks(c, batch);
   if (st != JPI_OK) return st;
   t->blocks = bind_launch(c, batch, prefix);
   t->rope_tab = c->rope_tab;

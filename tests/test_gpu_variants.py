@@ -268,3 +268,48 @@ def test_action_time_full_prefix_of_whole_blocks(width, heads, Dh, horizon, max_
     finally:
         ae.close()
     assert_bf16(got, opi0.denoise(wl.dims, w, noise, K, V, lens, wl.n_steps, st), "full prefix")
+
+
+# past the five-launch layers' 512 rows: 550 rows of the action-time variant, then a small batch on the same context and
+# back (its blocks are written by the bindings that use them only)
+def test_action_time_past_512_rows():
+    torch_cuda()
+    d = synth.Dims(n_layers=2, width=512, n_heads=4, n_kv_heads=1, head_dim=64, mlp_dim=512, action_dim=7, horizon=50)
+    B = 11
+    lens = [[70, 0, 33, 1, 64, 31, 32, 69, 63, 65][b % 10] for b in range(B)]
+    wl = synth.Workload("pi0-rows", d, prefix=70, batch=B, n_steps=2, n_fixed=3, dtype="bf16", prefix_len=tuple(lens))
+    print("case pi0-rows", B, flush=True)
+    w = spi0.make_pi0_weights(wl)
+    K, V = synth.make_prefix(wl)
+    noise, st, com = synth.make_noise(wl), spi0.make_state(wl), synth.make_committed(wl)
+    ref = opi0.denoise(d, w, noise, K, V, lens, wl.n_steps, st, committed=com, n_fixed=3)
+    ae = _pi0_expert(wl, w, B, 75)
+    try:
+        for pick in (slice(0, B), slice(2, 5), slice(0, B), slice(5, 6)):
+            got = _pi0_run(ae, K[:, pick], V[:, pick], noise[pick], wl.n_steps, lens[pick], st[pick], com[pick], 3)
+            assert_bf16(got, ref[pick], "rows %s" % pick, reg_rel=4e-3)
+    finally:
+        ae.close()
+
+
+# committed rows at t = 0 past 512 rows, with and without correction rows
+@pytest.mark.parametrize("n_corr", [0, 3])
+def test_committed_rows_at_t0_past_512_rows(n_corr):
+    torch_cuda()
+    d = synth.Dims(n_layers=2, width=256, n_heads=4, n_kv_heads=1, head_dim=64, mlp_dim=512, action_dim=7, horizon=25)
+    B = 21
+    lens = tuple([40, 0, 33, 1, 32][b % 5] for b in range(B))
+    wl = synth.Workload("t0-rows", d, prefix=40, batch=B, n_steps=2, n_fixed=9, dtype="bf16", prefix_len=lens, mod_gain=8.0)
+    inp = Inputs(wl)
+    corr = sc.make_item(wl.seed, B, n_corr, 256) if n_corr else None
+    print("case t0-rows", n_corr, flush=True)
+    ae = make_expert(wl, inp.weights, max_corr=n_corr)
+    try:
+        ae.set_committed_t0(True)
+        got = run_env(ae, None, inp.K, inp.V, inp.noise, 2, prefix_len=lens, committed=inp.committed, n_fixed=9, corr=corr)
+    finally:
+        ae.close()
+    ref = oracle.denoise(oracle.Expert(d, inp.weights), inp.noise, inp.K, inp.V, lens, 2, committed=inp.committed, n_fixed=9,
+                         corr=corr, committed_t0=True)
+    assert_bf16(got, ref, "t0 rows", reg_rel=4e-3)
+    assert np.array_equal(got[:, :9].astype(np.float32), inp.committed.astype(np.float32))
