@@ -29,7 +29,6 @@ using namespace jpi;
 namespace {
 
 constexpr int NBLK = 4;
-constexpr int XKV_SPLIT = 4;  // K slices of the VLM tokens' key and value product (d_VLM is a multiple of 256)
 const char* block_prefix[NBLK] = {"qformer.", "action_block.", "blocks.0.", "blocks.1."};
 enum { BLK_QF, BLK_ACT, BLK_J0, BLK_J1 };
 enum BKind { B_ATTN_NORM, B_Q, B_K, B_V, B_O, B_MLP_NORM, B_GATE, B_UP, B_DOWN, B_N };
@@ -562,8 +561,8 @@ jpi_status jpi_corr_create(const jpi_corr_config* cfg, int device, jpi_corr** ou
   alloc(&m->vst, B * Dh * ((m->Hmax + 7) / 8 * 8) * 2);
   alloc(&m->xk, B * m->Tmax * Dh * 2);
   alloc(&m->xvt, B * Dh * m->Tpad * 2);
-  // split-K slices of a block, or of the VLM tokens' keys and values (XKV_SPLIT slices)
-  alloc((void**)&m->partial, std::max((size_t)16 * M * W, (size_t)XKV_SPLIT * B * m->Tmax * 2 * Dh) * 4);
+  // split-K slices of a block, or of the VLM tokens' keys and values
+  alloc((void**)&m->partial, std::max((size_t)16 * M * W, xkv_slice_elems(B * m->Tmax, 2 * Dh, m->n_cu)) * 4);
   alloc((void**)&m->opart, attn_q > attn_b ? attn_q : attn_b);
   alloc((void**)&m->ones, W * 4);
   const size_t n_zero = std::max(std::max(W, 2 * F), (nH + 2) * Dh);
@@ -709,26 +708,55 @@ jpi_status jpi_corr_compress(jpi_corr* m, const void* vlm_state, int batch, int 
   CCHK(m, hipSetDevice(m->device));
   hipStream_t s = (hipStream_t)stream;
   const int W = m->W, Dh = m->Dh, T = m->T;
-  if (m->small) {
-    // the VLM tokens' keys and values: split over K (816 tokens, K 2048: 52 tiles of 64 x 64 in all), summed into blocks
-    GemmLaunch g{};
-    g.A = vlm_state;
-    g.W = m->w_xkv;
-    g.M = batch * n_tokens;
-    g.N = 2 * Dh;
-    g.K = m->V;
-    g.splitk = g.M > 64 ? XKV_SPLIT : 1;
-    g.n_cu = m->n_cu;
+  // the VLM tokens' keys and values (no query heads, no rotation)
+  GemmLaunch g{};
+  g.A = vlm_state;
+  g.W = m->w_xkv;
+  g.M = batch * n_tokens;
+  g.N = 2 * Dh;
+  g.K = m->V;
+  g.splitk = m->small ? xkv_slices(g.M, g.N, m->n_cu) : 1;
+  g.n_cu = m->n_cu;
+  g.epi = EPI_QKV;
+  g.ep.q = nullptr;
+  g.ep.ks = m->xk;
+  g.ep.ks_bstride = (int64_t)m->Tmax * Dh;
+  g.ep.vst = m->xvt;
+  g.ep.vst_ld = m->Tpad;
+  g.ep.rope = m->rope_id;
+  g.ep.n_heads = 0;
+  g.ep.head_dim = Dh;
+  g.ep.horizon = n_tokens;
+  if (g.splitk > 1) {
     g.epi = EPI_STORE_F32;
     g.ep.out_f32 = m->partial;
-    CCHK(m, launch_gemm(JPI_BF16, g, s));
-    const int64_t bstride = (int64_t)m->NBmax * kv_block_elems(Dh);
-    const dim3 grid((n_tokens + 31) / 32, batch, 2 * Dh / 32);
-    if (g.splitk == 1)
-      hipLaunchKernelGGL(k_xkv_blocks<1>, grid, dim3(256), 0, s, m->partial, g.M, n_tokens, Dh, m->kvf, bstride);
-    else
-      hipLaunchKernelGGL(k_xkv_blocks<XKV_SPLIT>, grid, dim3(256), 0, s, m->partial, g.M, n_tokens, Dh, m->kvf, bstride);
-    CCHK(m, hipGetLastError());
+  }
+  CCHK(m, launch_gemm(JPI_BF16, g, s));
+  if (m->small) {
+    // their blocks: from the slices, or from the keys and values themselves
+    if (g.splitk > 1) {
+      const int64_t bstride = (int64_t)m->NBmax * kv_block_elems(Dh);
+      const dim3 grid((n_tokens + 31) / 32, batch, 2 * Dh / 32);
+      if (g.splitk == 2)
+        hipLaunchKernelGGL(k_xkv_blocks<2>, grid, dim3(256), 0, s, m->partial, g.M, n_tokens, Dh, m->kvf, bstride);
+      else
+        hipLaunchKernelGGL(k_xkv_blocks<4>, grid, dim3(256), 0, s, m->partial, g.M, n_tokens, Dh, m->kvf, bstride);
+      CCHK(m, hipGetLastError());
+    } else {
+      BindLaunch bl{};
+      bl.kp = m->xk;
+      bl.vpt = m->xvt;
+      bl.kvf = m->kvf;
+      bl.L = 1;
+      bl.B = batch;
+      bl.P = n_tokens;
+      bl.Dh = Dh;
+      bl.Bmax = m->Bmax;
+      bl.Pmax = m->Tmax;
+      bl.Ppad = m->Tpad;
+      bl.NBmax = m->NBmax;
+      CCHK(m, launch_kv_blocks(bl, s));
+    }
     // the learned queries' block over them; its residual rows are the result
     SmallLayer y = small_base(m, BLK_QF, batch, T);
     y.own_done = true;
@@ -743,26 +771,6 @@ jpi_status jpi_corr_compress(jpi_corr* m, const void* vlm_state, int batch, int 
     return JPI_OK;
   }
   CCHK(m, launch_fill_i32(m->tlen, batch, n_tokens, s));
-  // the VLM tokens' keys and values (no query heads, no rotation)
-  GemmLaunch g{};
-  g.A = vlm_state;
-  g.W = m->w_xkv;
-  g.M = batch * n_tokens;
-  g.N = 2 * Dh;
-  g.K = m->V;
-  g.splitk = 1;
-  g.n_cu = m->n_cu;
-  g.epi = EPI_QKV;
-  g.ep.q = nullptr;
-  g.ep.ks = m->xk;
-  g.ep.ks_bstride = (int64_t)m->Tmax * Dh;
-  g.ep.vst = m->xvt;
-  g.ep.vst_ld = m->Tpad;
-  g.ep.rope = m->rope_id;
-  g.ep.n_heads = 0;
-  g.ep.head_dim = Dh;
-  g.ep.horizon = n_tokens;
-  CCHK(m, launch_gemm(JPI_BF16, g, s));
   // learned queries -> one block whose rows also see the VLM tokens
   CCHK(m, launch_bcast_rows(m->query, m->h, batch * T, T, W, s));
   CCHK(m, launch_norm_rows(m->h, m->norms, m->y, batch * T, W, m->cfg.rms_eps, s));

@@ -24,6 +24,21 @@ PROGRAMS = {
           }
       }
 """,
+    # the slices of every batch of tokens fit the buffer, which stays small however many tokens a module is made for
+    "xkv_slices": """
+  for (int n_cu : {64, 256, 304})
+    for (int N = 128; N <= 512; N *= 2) {
+      const size_t Mmax = 1u << 20, room = jpi::xkv_slice_elems(Mmax, N, n_cu);
+      CHECK(room <= (size_t)32768 * n_cu);
+      for (int M = 1; M <= (1 << 20); M += M < 20000 ? 1 : 997) {
+        const int s = jpi::xkv_slices(M, N, n_cu);
+        CHECK(s == 1 || s == 2 || s == 4);
+        CHECK(s == 1 || (size_t)s * M * N <= room);
+        CHECK(s == 1 || (size_t)s * M * N <= jpi::xkv_slice_elems(M, N, n_cu));
+        CHECK(M > 64 || s == 1);
+      }
+    }
+""",
     # z holds the GeGLU output of every row and, in the action-time variant, the action-time MLP's W columns
     "z_columns": """
   for (size_t W = 64; W <= 4096; W += 64)
@@ -40,7 +55,7 @@ PROGRAMS = {
 @pytest.mark.parametrize("name", sorted(PROGRAMS))
 def test_bounds(name, tmp_path):
     src, exe = tmp_path / "t.cpp", tmp_path / "t"
-    src.write_text('#include <cstdio>\n#include "jpi_bounds.h"\n'
+    src.write_text('#include <cstdio>\n#include <initializer_list>\n#include "jpi_bounds.h"\n'
                    '#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\\n", __LINE__, #x); return 1; } } while (0)\n'
                    "int main() {" + PROGRAMS[name] + "  return 0;\n}\n")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)], check=True)

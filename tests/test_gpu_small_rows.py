@@ -217,8 +217,10 @@ def test_correction_inputs_from_any_element():
         m.close()
 
 
-# action rows 1, 75, 200 and 513 (past the five-launch layers); one token, a block's edge, several blocks
-@pytest.mark.parametrize("batch,n_actions,tokens", [(1, 1, 1), (3, 25, 33), (8, 25, 64), (2, 10, 130), (27, 19, 5)])
+# action rows 1, 75, 200 and 513 (past the five-launch layers); one token, a block's edge, several blocks; the tokens'
+# product in one slice (few and very many tokens), four and two
+@pytest.mark.parametrize("batch,n_actions,tokens", [(1, 1, 1), (3, 25, 33), (8, 25, 64), (2, 10, 130), (27, 19, 5),
+                                                    (5, 3, 1003), (11, 2, 1499)])
 def test_correction_rows_match_oracle(batch, n_actions, tokens):
     torch = torch_cuda()
     import synth.correction as sc
