@@ -108,7 +108,6 @@ struct jpi_ctx {
   void* vpt = nullptr;                 // [L][Bmax][Dh][Ppad] prefix V transposed at bind time
   int Ppad = 0;                        // Pmax + horizon rounded up to a multiple of 8
   int* d_prefix_len = nullptr;
-  int* h_prefix_len = nullptr;  // pinned staging
   int batch = 0, prefix = 0;
   bool prefix_bound = false;
   float2* rope_tab = nullptr;  // [batch][n_corr + H][Dh/2] at positions prefix_len + r
@@ -316,7 +315,6 @@ jpi_status jpi_destroy(jpi_ctx* c) {
                   c->zsw, c->qsw, c->ptrace, c->ssq, c->kvf, c->skvf, c->w_atm_a_frag, c->w_atm_out_frag};
   for (void* p : bufs)
     if (p) (void)hipFree(p);
-  if (c->h_prefix_len) (void)hipHostFree(c->h_prefix_len);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   delete c;
   return JPI_OK;
@@ -469,11 +467,6 @@ jpi_status jpi_create(const jpi_config* cfg, int device, jpi_ctx** out) {
   }
 #undef ALLOC
   if (hipMemset(c->perr, 0, 256) != hipSuccess) return cleanup_fail(fail(c, JPI_ERR_HIP, "hipMemset"));
-  if (hipHostMalloc((void**)&c->h_prefix_len, c->Bmax * sizeof(int)) != hipSuccess) {
-    (void)hipGetLastError();
-    c->h_prefix_len = nullptr;
-    return cleanup_fail(fail(c, JPI_ERR_OOM, "pinned prefix_len staging"));
-  }
   *out = c;
   return JPI_OK;
 }
@@ -741,8 +734,7 @@ jpi_status jpi_bind_prefix(jpi_ctx* c, const void* k, const void* v, const int32
   bl.v = v;
   bl.in_place = in_place;
   HIPCHK(c, launch_bind(c->dt, bl, s));
-  memcpy(c->h_prefix_len, lens.data(), batch * sizeof(int));
-  HIPCHK(c, launch_set_i32(c->d_prefix_len, c->h_prefix_len, batch, s));
+  HIPCHK(c, launch_set_i32(c->d_prefix_len, lens.data(), batch, s));
   if (c->batch != batch) {  // state rows were bound for another batch
     c->n_fixed = c->n_corr = 0;
     c->state_bound = false;

@@ -498,9 +498,8 @@ __global__ __launch_bounds__(S::NT) void k_small_ring(SmallGemm g) {
 // sums of squares (do_in).  Correction rows restart from their token.  Every
 // operand that does not depend on the row's chain (W_out, W_in, biases) is
 // requested before it starts.
-template <int NJ>
 __global__ __launch_bounds__(256) void k_small_head(SmallHead a) {
-  __shared__ __attribute__((aligned(16))) float ys[1024 * NJ];
+  __shared__ __attribute__((aligned(16))) float ys[1024];  // W <= 1024: four columns per thread
   __shared__ float xs[64], dots[64], red[4];
   const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int W = a.W, A = a.A, b = m / a.seq, i = m % a.seq - a.n_lead;  // i < 0: a correction row
@@ -509,43 +508,35 @@ __global__ __launch_bounds__(256) void k_small_head(SmallHead a) {
   if (i >= 0 && tid < A) xs[tid] = a.x[xrow + tid];
   // the first eight outputs' rows of W_out per wave (all of them at A = 32)
   constexpr int NO = 8;
-  bf16x8 wo[NO][2 * NJ];
+  bf16x8 wo[NO][2];
   if (a.do_out && i >= 0) {
 #pragma unroll
     for (int o = 0; o < NO; ++o)
 #pragma unroll
-      for (int j = 0; j < 2 * NJ; ++j)
+      for (int j = 0; j < 2; ++j)
         wo[o][j] = *reinterpret_cast<const bf16x8*>(a.w_out + (size_t)min(wave + 4 * o, A - 1) * W + min(8 * lane + 512 * j, W - 8));
   }
+  const int k = 4 * tid;  // this thread's columns
   if (a.do_out && i >= 0) {
-    f32x4 hv[NJ], sc[NJ], sh[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int k = 4 * tid + 1024 * j;
-      if (k >= W) continue;
-      hv[j] = *reinterpret_cast<const f32x4*>(a.h + (size_t)m * W + k);
-      sc[j] = *reinterpret_cast<const f32x4*>(a.scale_f + t0 * a.t0_delta + k);
-      sh[j] = *reinterpret_cast<const f32x4*>(a.shift_f + t0 * a.t0_delta + k);
-    }
+    f32x4 hv, sc, sh;
     float ss = 0.f;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-      if (4 * tid + 1024 * j < W) ss += hv[j][0] * hv[j][0] + hv[j][1] * hv[j][1] + hv[j][2] * hv[j][2] + hv[j][3] * hv[j][3];
-    const float r = 1.0f / sqrtf(block_sum_256(ss, red) * a.inv_w + a.eps);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int k = 4 * tid + 1024 * j;
-      if (k < W) *reinterpret_cast<f32x4*>(ys + k) = hv[j] * r * (1.0f + sc[j]) + sh[j];
+    if (k < W) {
+      hv = *reinterpret_cast<const f32x4*>(a.h + (size_t)m * W + k);
+      sc = *reinterpret_cast<const f32x4*>(a.scale_f + t0 * a.t0_delta + k);
+      sh = *reinterpret_cast<const f32x4*>(a.shift_f + t0 * a.t0_delta + k);
+      ss = hv[0] * hv[0] + hv[1] * hv[1] + hv[2] * hv[2] + hv[3] * hv[3];
     }
+    const float r = 1.0f / sqrtf(block_sum_256(ss, red) * a.inv_w + a.eps);
+    if (k < W) *reinterpret_cast<f32x4*>(ys + k) = hv * r * (1.0f + sc) + sh;
     __syncthreads();
     // wave w: outputs w, w + 4, ..; lane: columns 8 lane + 512 j .. + 7
-    auto dot = [&](const bf16x8 (&w)[2 * NJ]) {
+    auto dot = [&](const bf16x8 (&w)[2]) {
       float p = 0.f;
 #pragma unroll
-      for (int j = 0; j < 2 * NJ; ++j) {
-        const int k = 8 * lane + 512 * j;
-        if (k >= W) continue;
-        const f32x4 y0 = *reinterpret_cast<const f32x4*>(ys + k), y1 = *reinterpret_cast<const f32x4*>(ys + k + 4);
+      for (int j = 0; j < 2; ++j) {
+        const int c = 8 * lane + 512 * j;
+        if (c >= W) continue;
+        const f32x4 y0 = *reinterpret_cast<const f32x4*>(ys + c), y1 = *reinterpret_cast<const f32x4*>(ys + c + 4);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           p = fmaf(y0[e], (float)w[j][e], p);
@@ -560,9 +551,9 @@ __global__ __launch_bounds__(256) void k_small_head(SmallHead a) {
       if (lane == 0 && wave + 4 * o < A) dots[wave + 4 * o] = p;
     }
     for (int o = wave + 4 * NO; o < A; o += 4) {
-      bf16x8 w[2 * NJ];
+      bf16x8 w[2];
 #pragma unroll
-      for (int j = 0; j < 2 * NJ; ++j)
+      for (int j = 0; j < 2; ++j)
         w[j] = *reinterpret_cast<const bf16x8*>(a.w_out + (size_t)o * W + min(8 * lane + 512 * j, W - 8));
       const float p = dot(w);
       if (lane == 0) dots[o] = p;
@@ -576,10 +567,7 @@ __global__ __launch_bounds__(256) void k_small_head(SmallHead a) {
   }
   if (!a.do_in) return;
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int k = 4 * tid + 1024 * j;
-    if (k >= W) continue;
+  if (k < W) {
     f32x4 h;
     if (i < 0) {
       h = *reinterpret_cast<const f32x4*>(a.corr + ((size_t)b * a.n_lead + m % a.seq) * W + k);
@@ -873,9 +861,8 @@ hipError_t enqueue_small_layer(const SmallLayer& y, hipStream_t s) {
 }
 
 hipError_t launch_small_head(const SmallHead& a, hipStream_t s) {
-  if (a.M < 1 || a.W > 2048 || a.W % 32 != 0 || a.A < 1 || a.A > 64 || a.seq <= a.n_lead) return hipErrorInvalidValue;
-  if (a.W <= 1024) hipLaunchKernelGGL(k_small_head<1>, dim3(a.M), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(k_small_head<2>, dim3(a.M), dim3(256), 0, s, a);
+  if (a.M < 1 || a.W > 1024 || a.W % 32 != 0 || a.A < 1 || a.A > 64 || a.seq <= a.n_lead) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_small_head, dim3(a.M), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
