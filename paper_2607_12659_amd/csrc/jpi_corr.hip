@@ -691,6 +691,7 @@ jpi_status jpi_corr_finalize_weights(jpi_corr* m, void* stream) {
         return cfail(m, JPI_ERR_STATE, std::string("missing tensor ") + block_prefix[bl] + bkind_suffix[k]);
   for (int k = 0; k < G_N; ++k)
     if (!m->have[(size_t)NBLK * B_N + k]) return cfail(m, JPI_ERR_STATE, std::string("missing tensor ") + gkind_name[k]);
+  if (m->finalized) return JPI_OK;  // no weight since: calls in flight keep their buffers
   CCHK(m, hipSetDevice(m->device));
   m->small = false;
   CCHK(m, ready_small(m, (hipStream_t)stream));

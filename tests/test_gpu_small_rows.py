@@ -217,6 +217,37 @@ def test_correction_inputs_from_any_element():
         m.close()
 
 
+def test_correction_finalize_again_touches_nothing():
+    """Finalizing without a new weight does no device work (calls in flight use the module's buffers): it can even be
+    called while its stream is being captured.  A new weight is taken up by the next one."""
+    torch = torch_cuda()
+    import synth.correction as sc
+    from gpu_util import Corr
+    from paper_2607_12659_amd.expert import to_device
+    wl = sc.CORR_WORKLOADS["corr-tiny"]
+    w, x = sc.make_corr_weights(wl, std=0.08), to_device(sc.make_vlm_state(wl))
+    m = Corr(wl.dims, w, wl.batch, 8, wl.vlm_tokens)
+    try:
+        first = m.compress(x, wl.batch, wl.vlm_tokens)
+        t, graph, s = torch.zeros(4, device="cuda"), torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=s):
+            t += 1
+            st = m.jpi.jpi_corr_finalize_weights(m.ctx, s.cuda_stream)
+        assert st == m.jpi.JPI_OK
+        assert torch.equal(first, m.compress(x, wl.batch, wl.vlm_tokens))
+        q = np.ascontiguousarray(-w["qformer.query"])
+        assert m.jpi.jpi_corr_set_weight(m.ctx, "qformer.query", q, q.size, m.jpi.JPI_F32, 0) == m.jpi.JPI_OK
+        assert m.jpi.jpi_corr_compress(m.ctx, x, wl.batch, wl.vlm_tokens, first.clone()) == m.jpi.JPI_ERR_STATE
+        assert m.jpi.jpi_corr_finalize_weights(m.ctx) == m.jpi.JPI_OK
+        other = Corr(wl.dims, {**w, "qformer.query": q}, wl.batch, 8, wl.vlm_tokens)
+        got, want = m.compress(x, wl.batch, wl.vlm_tokens), other.compress(x, wl.batch, wl.vlm_tokens)
+        assert torch.equal(got, want) and not torch.equal(got, first)
+        other.close()
+    finally:
+        m.close()
+
+
 # action rows 1, 75, 200 and 513 (past the five-launch layers); one token, a block's edge, several blocks; the tokens'
 # product in one slice (few and very many tokens), four and two
 @pytest.mark.parametrize("batch,n_actions,tokens", [(1, 1, 1), (3, 25, 33), (8, 25, 64), (2, 10, 130), (27, 19, 5),
