@@ -13,6 +13,10 @@
 //   r = 1 / sqrt(mean h^2 + eps) and adds c[n] = sum_k shift[k] W[n][k], which
 //   depends on the weights and the step only and comes from a table:
 //   sum_k (r h_k (1 + scale_k) + shift_k) W[n][k] = r sum_k u_k W[n][k] + c[n].
+//   What is rounded to bf16 is h (1 + scale), not the normalised value: where a
+//   shift cancels a large activation the product's error is 2^-9 of the
+//   activation (cancelled 4 / 16 times over: 2.7 / 6 times the error of the
+//   eight-launch layers), where a shift dominates it is smaller than theirs.
 // * O and Down are not split over workgroups: a workgroup computes a tile over
 //   the whole contraction, so it can update the residual stream in its epilogue.
 // * A workgroup's waves split the contraction; each wave issues every load of
@@ -733,8 +737,12 @@ bool small_supported(jpi_dtype dt, int W, int nH, int Dh, int F) {
 //   O (N 1024, K 2048):    16x16 3.5 4.4 5.4 6.4 9.5   32x16 4.2 4.2 5.1 5.4 8.7   64x32 6.4 6.3 6.2 6.3 6.5
 //   Down (N 1024, K 4096): 16x16 5.0 6.8 9.0 11 18     32x16 6.0 5.9 8.8 9.0 16    64x16 8.6 8.1 8.0 8.1 16   64x32 9.8 9.5 9.4 9.5 10
 //   gate/up (N 8192, K 1024): 64x32 6.8 10 13          64x64 8.2 8.1 12 12 22
-// The smallest tile that still gives at most about one and a half workgroups
-// per compute unit wins; past that each workgroup's operands are read too often.
+// At these widths, on 256 units, the smallest tile that still gives at most about
+// one and a half workgroups per unit wins; past that each workgroup's operands
+// are read too often.  The rule below is that choice written as row-group
+// thresholds: it looks at the rows (and at the contraction's length), not at N or
+// the unit count, so narrower products (the correction module's N 1536, 1024 and
+// 4096, experts below width 1024) take the tiles of the widths above unmeasured.
 hipError_t launch_small(SmallEpi epi, const SmallGemm& g, hipStream_t s) {
   const int RG = (g.M + 15) / 16;
   const bool k32 = g.KS % 32 == 0;  // the wide variants take 32 steps a turn (64 or 128 below)

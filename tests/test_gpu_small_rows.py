@@ -279,6 +279,43 @@ def test_correction_rows_match_oracle(batch, n_actions, tokens):
         m.close()
 
 
+@pytest.mark.parametrize("kappa", [1, 4, 16])
+def test_small_rows_shift_cancels_the_activation(kappa):
+    """These layers round u = h (1 + scale) and add the shift's part to the product, where the eight-launch layers round
+    the sum: the error of a product is 2^-9 of r |h (1 + scale)|, not of the normalised value.  Here the shift of every
+    norm takes away the part of h that all rows share, kappa times what is left.  Errors are taken of what the sublayers
+    do to the actions: 4e-3 where every product's inputs are rounded to 2^-9 of themselves (as REL), kappa times that
+    here (measured 3.1e-3, 6.3e-3 and 1.0e-2, against 2.3e-3, 2.3e-3 and 1.6e-3)."""
+    d = synth.Dims(n_layers=2, width=512, n_heads=4, n_kv_heads=1, head_dim=64, mlp_dim=1024, action_dim=7, horizon=20)
+    wl = synth.Workload("cancel", d, prefix=1, batch=3, n_steps=2, n_fixed=0, dtype="bf16", prefix_len=(0, 0, 0))
+    inp = Inputs(wl)
+    w = {k: v.copy() for k, v in inp.weights.items()}
+    own = 1.0 / kappa  # rms of what differs between rows; the shared part has rms 1
+    shared = synth.normal_f32(wl.seed, "shared", 1.0, (d.width,))
+    w["action_in.w"] = synth.f32_to_bf16_bits(synth.normal_f32(wl.seed, "own", own / np.sqrt(7.0), (d.width, 7)))
+    w["action_in.b"] = shared
+    for l in range(2):
+        for mod in ("attn_mod.b", "mlp_mod.b"):
+            w["layers.%d.%s" % (l, mod)] = np.concatenate(
+                [np.zeros(d.width), -shared / np.sqrt(1 + own * own), np.full(d.width, 0.5)]).astype(np.float32)
+    print("case shift against activation", kappa, flush=True)
+    ae = make_expert(wl, w)
+    try:
+        five = run_env(ae, None, inp.K, inp.V, inp.noise, 2, prefix_len=inp.prefix_len)
+        eight = run_env(ae, "0", inp.K, inp.V, inp.noise, 2, prefix_len=inp.prefix_len)
+    finally:
+        ae.close()
+    ref = oracle.denoise(oracle.Expert(d, w), inp.noise, inp.K, inp.V, inp.prefix_len, 2)
+    for l in range(2):
+        for mod in ("attn_mod", "mlp_mod"):  # no sublayer reaches the actions
+            w["layers.%d.%s.b" % (l, mod)][2 * d.width:] = 0
+            w["layers.%d.%s.w" % (l, mod)][2 * d.width:] = 0
+    effect = np.linalg.norm(ref - oracle.denoise(oracle.Expert(d, w), inp.noise, inp.K, inp.V, inp.prefix_len, 2))
+    err5, err8 = np.linalg.norm(five - ref) / effect, np.linalg.norm(eight - ref) / effect
+    print("kappa %d, of the sublayers' effect: five-launch %.2e, eight-launch %.2e" % (kappa, err5, err8), flush=True)
+    assert err8 <= REL and err5 <= kappa * REL
+
+
 def _wide(B, lens, nH=1, Dh=256, horizon=20):
     """One layer, one step: a row's attention output reaches that row's action only."""
     d = synth.Dims(n_layers=1, width=512, n_heads=nH, n_kv_heads=1, head_dim=Dh, mlp_dim=512, action_dim=7, horizon=horizon)
