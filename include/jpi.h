@@ -116,9 +116,12 @@ const char* jpi_last_error(const jpi_ctx* ctx);
  * 64, mlp_dim a multiple of 64, max_corr in [0, 64], variant known, state_dim
  * in [1, 4096] for the action-time variant (which also needs max_corr 0 and
  * max_prefix >= 1) and 0 otherwise (JPI_ERR_ARG otherwise).  All resident buffers
- * (max_batch x max_prefix prefix KV, activations, partial sums, weights) are
- * allocated here and owned by the context (Section "System Design":
- * GPU-resident intermediate buffers).  On failure *out is NULL. */
+ * (max_batch x max_prefix prefix KV, activations, weights) are allocated here
+ * and owned by the context (Section "System Design": GPU-resident
+ * intermediate buffers); the first jpi_bind_prefix adds the prefix's
+ * fragment-ordered blocks (as much again as its K and V; the action-time
+ * variant up to 512 rows), the first jpi_denoise of a size its scratch, tables
+ * and a fragment-ordered copy of the layer weights.  On failure *out is NULL. */
 jpi_status jpi_create(const jpi_config* cfg, int device, jpi_ctx** out);
 
 /* Free everything the context owns.  NULL is accepted. */
@@ -217,8 +220,8 @@ jpi_status jpi_set_committed_t0(jpi_ctx* ctx, int enable);
  * run, and x is written to actions_dev.  noise_dev, actions_dev: device
  * [batch][H][A] fp32 (may alias).  Stream-ordered and asynchronous.  The first
  * call per (batch, prefix, n_steps, n_fixed, n_corr) builds the
- * modulation tables for the N step times and captures the N-step loop into a
- * HIP graph; later calls replay it.  Errors: JPI_ERR_STATE (weights not
+ * modulation tables for the N step times (kept per N until a weight changes)
+ * and captures the N-step loop into a HIP graph; later calls replay it.  Errors: JPI_ERR_STATE (weights not
  * finalized or no prefix bound), JPI_ERR_ARG (NULL, n_steps < 1).
  *
  * Paths, all captured once and replayed: the five-launch layers (bf16,
