@@ -25,6 +25,7 @@
 // the prefix (masked past prefix_len[b]).  The softmax does not depend on the
 // order.  Masked keys get probability 0 and their V entries are zeroed, so
 // stale or non-finite memory in unused slots never reaches the output.
+#include <algorithm>
 #include <math.h>
 
 #include "jpi_device.h"
@@ -495,22 +496,21 @@ static hipError_t launch_merge(const AttnLaunch& a, int S, const bf16* part, con
 // as long as six 32-key blocks and several ranges cost a merge (three more).  A count just past a whole round was the
 // costly case of "enough workgroups to cover the chip once": the 816-token prefill's 51 tiles at 6 ranges are 306
 // workgroups in two rounds, at 5 ranges 255 in one.
-int flash_splits(int B, int nH, int H, int P, int n_cu) {
-  const int KB = 32;
-  const int nqt = (nH * H + 127) / 128;
-  const int nb = (H + KB - 1) / KB + (P + KB - 1) / KB;
-  int best = 1;
-  long best_cost = -1;
+struct Ranges {
+  int S;      // key ranges
+  long cost;  // the estimate of the launch that they make least
+};
+static Ranges flash_ranges(int B, int nH, int H, int P, int n_cu) {
+  const int nqt = (nH * H + 127) / 128, nb = kv_blocks(H) + kv_blocks(P);
+  Ranges best{1, -1};
   for (int s = 1; s <= FLASH_MAX_SPLITS && (s == 1 || s <= nb / 2); ++s) {
     const long rounds = ((long)B * nqt * s + n_cu - 1) / n_cu;
     const long cost = rounds * (6 + (nb + s - 1) / s) + (s > 1 ? 3 : 0);
-    if (best_cost < 0 || cost < best_cost) {
-      best = s;
-      best_cost = cost;
-    }
+    if (best.cost < 0 || cost < best.cost) best = Ranges{s, cost};
   }
   return best;
 }
+int flash_splits(int B, int nH, int H, int P, int n_cu) { return flash_ranges(B, nH, H, P, n_cu).S; }
 
 template <int DH>
 static hipError_t launch_flash_t(const AttnLaunch& a, int S, hipStream_t s) {
@@ -723,19 +723,30 @@ __global__ __launch_bounds__(64 * ROWS_NW, 2) void k_flash_rows(AttnLaunch a, in
 // 12.4, 10.7, 13.6; five 13.7, 13.6, 17.1; eight 13.4, 18.7.  With "enough for the chip" (three rollouts four
 // ranges, eight two) batch 8 took 11.65 ms instead of 11.13 and batch 3 9.74 instead of 9.54.  Eight waves a
 // workgroup and 32 rows a workgroup were slower throughout.
-int flash_rows_splits(int B, int nH, int H, int P, int Dh, int n_cu) {
-  const int ntile = (nH * H + 15) / 16, nb = (H + 31) / 32 + (P + 31) / 32;
-  int best = 1;
-  long best_cost = -1;
+static Ranges rows_ranges(int B, int nH, int H, int P, int Dh, int n_cu) {
+  const int ntile = (nH * H + 15) / 16, nb = kv_blocks(H) + kv_blocks(P);
+  Ranges best{1, -1};
   for (int s = 1; s <= 8 && (s == 1 || 2 * s < nb); s *= 2) {
     const long rounds = ((long)B * ntile * s + n_cu - 1) / n_cu;
     const long cost = rounds * (52 + (6 + 6 * Dh / 256) * ((nb + ROWS_NW * s - 1) / (ROWS_NW * s))) + (s > 1 ? 35 : 0);
-    if (best_cost < 0 || cost < best_cost) {
-      best = s;
-      best_cost = cost;
-    }
+    if (best.cost < 0 || cost < best.cost) best = Ranges{s, cost};
   }
   return best;
+}
+int flash_rows_splits(int B, int nH, int H, int P, int Dh, int n_cu) { return rows_ranges(B, nH, H, P, Dh, n_cu).S; }
+
+// Whether layers with this kernel are faster than the eight-launch layers with k_flash.  Every 16-row tile reads all
+// of its rollout's keys (128 rows share them there), so many tiles over a long prefix are bound by those reads, about
+// 16 TB/s from the L2s; k_flash's unit above is 0.3 + 0.9 Dh / 256 us, and the eight-launch layers cost about 18 us a
+// layer more elsewhere.  Fitted to 240 shapes (Dh 64, 128, 256; 1 .. 50 rollouts, up to 500 rows; 256 .. 25600
+// tokens), wrong by at most 6 %.  us a layer, these / those: Dh 256, 50 rows a rollout, 10 rollouts of 1600 tokens
+// 70 / 87, of 4800 115 / 102, of 25600 357 / 217; 4 of 25600 198 / 120; 1 of 25600 61 / 106; Dh 128, 16 rows, 32 of
+// 12800 152 / 103.
+bool flash_rows_pays(int B, int nH, int H, int P, int Dh, int n_cu) {
+  const double tiles = (double)B * ((nH * H + 15) / 16), nb = kv_blocks(H) + kv_blocks(P);
+  const double reads = tiles * nb * kv_block_elems(Dh) * 2 / (16e6 * n_cu / 256);  // us
+  const double rows = std::max(0.1 * (double)rows_ranges(B, nH, H, P, Dh, n_cu).cost, reads);
+  return rows <= (0.3 + 0.9 * Dh / 256) * (double)flash_ranges(B, nH, H, P, n_cu).cost + 18.0;
 }
 
 template <int DH, typename TO>

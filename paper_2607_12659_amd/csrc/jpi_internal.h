@@ -237,6 +237,7 @@ size_t flash_scratch_bytes(int B, int nH, int H, int Dh, int S);
 hipError_t launch_flash(const AttnLaunch& a, int S, hipStream_t s);
 // bf16 attention for few query rows: S key ranges (1, 2, 4 or 8) per 16-row tile
 int flash_rows_splits(int B, int nH, int H, int P, int Dh, int n_cu);
+bool flash_rows_pays(int B, int nH, int H, int P, int Dh, int n_cu);  // against the layers with launch_flash
 hipError_t launch_flash_rows(const AttnLaunch& a, int S, hipStream_t s);
 
 // Persistent single-launch denoise (jpi_persist.hip), M <= 64, bf16.

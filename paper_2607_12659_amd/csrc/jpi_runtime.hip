@@ -815,6 +815,11 @@ jpi_status ensure_table(jpi_ctx* c, int n_steps, hipStream_t s, float** out) {
   return JPI_OK;
 }
 
+// Keys that a rollout's rows may see in the prefix slots (a bound on prefix_len, and on the state token's slot).
+int prefix_keys(const jpi_ctx* c) {
+  return key_bound(c->prefix, c->Pmax, c->cfg.variant == JPI_VARIANT_ACTION_TIME);
+}
+
 struct StepGemms {
   int M;
   int s_o, s_d;  // split-K of the O and Down projections (QKV and GateUp are not split)
@@ -846,14 +851,16 @@ bool use_persist(jpi_ctx* c, int batch) {
 // call on one MI355X, pi0.5 shape, 816 tokens: 1 rollout 6.6 ms against 7.75 (single
 // launch), 3 rollouts 9.5 against 11.3 and 8 (400 rows) 11.1 against 13.1 (eight launches per layer); the tiny bf16 expert,
 // 4 rollouts, 10 steps 0.59 against 0.91 (single launch).  Past 512 rows the
-// tiles of the eight-launch layers share their operands better.
+// tiles of the eight-launch layers share their operands better, and with many keys
+// their attention does (flash_rows_pays).
 // JPI_PERSIST=1 and a wait bound set for its test ask for the single-launch kernel, JPI_PERSIST=0 for the
 // eight-launch layers.  The single-launch kernel also serves the shapes of at most 64 rows that it supports
 // and these layers do not.
 bool use_small(const jpi_ctx* c, int batch) {
   const char* e = getenv("JPI_PERSIST");
   if ((e && (e[0] == '0' || e[0] == '1')) || c->persist_spin != 0 || c->no_small) return false;
-  return c->kvf && batch * (c->H + c->n_corr) <= SMALL_ROWS;
+  const int S = c->H + c->n_corr;
+  return c->kvf && batch * S <= SMALL_ROWS && flash_rows_pays(batch, c->nH, S, prefix_keys(c), c->Dh, c->n_cu);
 }
 
 StepGemms plan_gemms(jpi_ctx* c, int batch) {
@@ -876,11 +883,6 @@ StepGemms plan_gemms(jpi_ctx* c, int batch) {
     p.s_sd = gemm_pick_splitk(c->dt, batch, c->W, c->F, c->n_cu);
   }
   return p;
-}
-
-// Keys that a rollout's rows may see in the prefix slots (a bound on prefix_len, and on the state token's slot).
-int prefix_keys(const jpi_ctx* c) {
-  return key_bound(c->prefix, c->Pmax, c->cfg.variant == JPI_VARIANT_ACTION_TIME);
 }
 
 // Buffers that only the five-launch layers need (sets *changed where a captured graph may hold the old one).

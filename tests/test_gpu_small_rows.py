@@ -78,6 +78,25 @@ def test_small_rows_key_ranges(shape, batch, lens):
         ae.close()
 
 
+# (rollouts, tokens): a long prefix for three rollouts goes to the eight-launch layers, for one rollout, and a short one, not
+@pytest.mark.parametrize("batch,prefix,eight", [(3, 12800, True), (1, 12800, False), (3, 1600, False)])
+def test_long_prefixes_take_the_faster_layers(batch, prefix, eight):
+    d = synth.Dims(n_layers=1, width=512, n_heads=8, n_kv_heads=1, head_dim=256, mlp_dim=512, action_dim=7, horizon=50)
+    lens = [prefix, prefix - 1, 77][:batch]
+    wl = synth.Workload("long-b%d-p%d" % (batch, prefix), d, prefix=prefix, batch=batch, n_steps=2, n_fixed=0, dtype="bf16",
+                        prefix_len=tuple(lens), mod_gain=8.0)
+    inp = Inputs(wl)
+    print("case", wl.name, flush=True)
+    ae = make_expert(wl, inp.weights)
+    try:
+        got = run_env(ae, None, inp.K, inp.V, inp.noise, 2, prefix_len=lens)
+        other = run_env(ae, "0", inp.K, inp.V, inp.noise, 2, prefix_len=lens)
+        assert_bf16(got, _oracle(wl, inp, None), wl.name, reg_rel=REL, reg_abs=ABS)
+        assert np.array_equal(got, other) == eight
+    finally:
+        ae.close()
+
+
 def test_small_rows_after_longer_rows():
     """Own-key blocks keep what a longer call left behind their last key; it must not show."""
     wl, inp, corr = _case("w1024", 2, 0, 4)
