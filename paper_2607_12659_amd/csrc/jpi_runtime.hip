@@ -646,7 +646,7 @@ jpi_status jpi_debug_prefix_vt(jpi_ctx* c, void** vt_out, int* ld_out) {
 
 namespace {
 
-constexpr int SMALL_ROWS = 512;  // see use_small
+constexpr int SMALL_ROWS = 512, SMALL_WIDE_ROWS = 64, SMALL_WIDE_MLP = 12288;  // see use_small
 
 // The action-time variant's eight-launch layers read the row-major buffers only (the state token's key and value are
 // put there), so past SMALL_ROWS its prefix has no use for blocks.
@@ -852,7 +852,9 @@ bool use_persist(jpi_ctx* c, int batch) {
 // launch), 3 rollouts 9.5 against 11.3 and 8 (400 rows) 11.1 against 13.1 (eight launches per layer); the tiny bf16 expert,
 // 4 rollouts, 10 steps 0.59 against 0.91 (single launch).  Past 512 rows the
 // tiles of the eight-launch layers share their operands better, and with many keys
-// their attention does (flash_rows_pays).
+// their attention does (flash_rows_pays).  A very wide MLP makes Down's unsplit contraction long (us a layer, here / eight
+// launches: W 512, F 16384 47 / 49 at 70 rows, 77 / 68 at 260; W 768, F 12288 71 / 76 at 260; W 1024, F 16384 82 / 74 at
+// 130, 123 / 111 at 510).
 // JPI_PERSIST=1 and a wait bound set for its test ask for the single-launch kernel, JPI_PERSIST=0 for the
 // eight-launch layers.  The single-launch kernel also serves the shapes of at most 64 rows that it supports
 // and these layers do not.
@@ -860,7 +862,8 @@ bool use_small(const jpi_ctx* c, int batch) {
   const char* e = getenv("JPI_PERSIST");
   if ((e && (e[0] == '0' || e[0] == '1')) || c->persist_spin != 0 || c->no_small) return false;
   const int S = c->H + c->n_corr;
-  return c->kvf && batch * S <= SMALL_ROWS && flash_rows_pays(batch, c->nH, S, prefix_keys(c), c->Dh, c->n_cu);
+  if (!c->kvf || batch * S > (c->F > SMALL_WIDE_MLP ? SMALL_WIDE_ROWS : SMALL_ROWS)) return false;
+  return flash_rows_pays(batch, c->nH, S, prefix_keys(c), c->Dh, c->n_cu);
 }
 
 StepGemms plan_gemms(jpi_ctx* c, int batch) {

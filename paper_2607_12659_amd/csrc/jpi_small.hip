@@ -753,7 +753,13 @@ hipError_t launch_small(SmallEpi epi, const SmallGemm& g, hipStream_t s) {
       if (RG > 12) return launch_ring<Ring64, SE_QKV>(g, s);
       return RG <= 4 ? launch_t<1, 2, 8, 4, SE_QKV>(g, s) : launch_t<2, 4, 8, 4, SE_QKV>(g, s);
     case SE_GEGLU:
-      if (!k32) return launch_t<2, 2, 8, 1, SE_GEGLU>(g, s);
+      if (!k32) {
+        // narrow experts (W 256, 512, 768): small tiles up to about six workgroups per unit, past that the rings (us a layer,
+        // small tiles / rings: W 512, F 2048 at 260 rows 30.6 / 32.0, F 4096 at 190 rows 38.5 / 37.0 and 510 rows 51.4 / 44.9,
+        // F 8192 at 510 rows 71 / 60; W 256, F 1024 at 510 rows 26.4 / 27.5)
+        if (RG <= 4 || (g.N / 32) * ((RG + 1) / 2) <= 1536) return launch_t<2, 2, 8, 1, SE_GEGLU>(g, s);
+        return RG <= 16 || g.N < 8192 ? launch_ring<Ring64, SE_GEGLU>(g, s) : launch_ring<Ring128, SE_GEGLU>(g, s);
+      }
       if (RG == 1) return launch_t<1, 2, 8, 4, SE_GEGLU>(g, s);
       if (RG <= 4) return launch_t<4, 2, 16, 2, SE_GEGLU>(g, s);
       return RG <= 16 ? launch_ring<Ring64, SE_GEGLU>(g, s) : launch_ring<Ring128, SE_GEGLU>(g, s);

@@ -20,6 +20,9 @@ SHAPES = {
     "w256": synth.Dims(n_layers=2, width=256, n_heads=4, n_kv_heads=1, head_dim=64, mlp_dim=512, action_dim=7, horizon=10),
     # Dh 128, contractions of 16 and 40 steps
     "w512": synth.Dims(n_layers=2, width=512, n_heads=10, n_kv_heads=1, head_dim=128, mlp_dim=1280, action_dim=24, horizon=17),
+    # narrow, with a wide MLP: gate/up on the rings past 48 and 272 rows; and widths whose contraction is 24 steps
+    "w256f": synth.Dims(n_layers=2, width=256, n_heads=4, n_kv_heads=1, head_dim=64, mlp_dim=12288, action_dim=7, horizon=10),
+    "w768": synth.Dims(n_layers=2, width=768, n_heads=4, n_kv_heads=1, head_dim=64, mlp_dim=3072, action_dim=14, horizon=16),
     "w1024": synth.Dims(n_layers=2, width=1024, n_heads=8, n_kv_heads=1, head_dim=256, mlp_dim=4096, action_dim=32, horizon=50),
 }
 LENS = [70, 0, 33, 1, 64, 31, 32, 69, 63, 65]
@@ -42,6 +45,8 @@ def _oracle(wl, inp, corr, t0=False):
 # rows: 10, 30, 130, 510 | 17, 34 .. 289 | 50, 100, 200, 250, 300, 500 and with correction tokens 53, 159, 424
 @pytest.mark.parametrize("shape,batch,n_fixed,n_corr,t0", [
     ("w256", 1, 0, 0, False), ("w256", 3, 4, 0, True), ("w256", 13, 0, 3, False), ("w256", 51, 2, 0, False),
+    ("w256f", 4, 0, 0, False), ("w256f", 11, 2, 0, True), ("w256f", 27, 0, 3, False), ("w256f", 51, 0, 0, False),
+    ("w768", 1, 0, 0, False), ("w768", 17, 3, 0, True), ("w768", 31, 0, 0, False),
     ("w512", 1, 0, 0, False), ("w512", 4, 3, 2, True), ("w512", 17, 0, 0, False),
     ("w1024", 1, 0, 0, False), ("w1024", 1, 10, 3, True), ("w1024", 2, 0, 0, False), ("w1024", 3, 7, 3, False),
     ("w1024", 4, 0, 0, False), ("w1024", 5, 7, 0, True), ("w1024", 6, 0, 0, False), ("w1024", 8, 5, 3, True),
