@@ -225,9 +225,10 @@ jpi_status jpi_set_committed_t0(jpi_ctx* ctx, int enable);
  * finalized or no prefix bound), JPI_ERR_ARG (NULL, n_steps < 1).
  *
  * Paths, all captured once and replayed: the five-launch layers (bf16,
- * batch * (n_corr + H) <= 512, max_prefix >= 1, width, mlp_dim and
- * n_heads * head_dim multiples of 256, width <= 1024, memory for the prefix's
- * blocks); where they do not apply, the single-launch kernel for at most 64
+ * batch * (n_corr + H) <= 512 -- 64 where mlp_dim > 12288 -- max_prefix >= 1,
+ * width, mlp_dim and n_heads * head_dim multiples of 256, width <= 1024,
+ * memory for their buffers, and not a long prefix of several rollouts, where
+ * the eight-launch layers are faster); where they do not apply, the single-launch kernel for at most 64
  * bf16 rows of the shapes it supports (n_heads even; width, mlp_dim and
  * n_heads * head_dim multiples of 128, width <= 2048: so also by default for
  * widths 1280 .. 2048); the eight-launch layers otherwise.  JPI_PERSIST in
